@@ -25,6 +25,9 @@ __device__ __forceinline__ u64 readlane64(u64 v, int l) {
 }
 __device__ __forceinline__ uint32_t readfirst(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
 
+// v_writelane_b32: `old` with lane l's value replaced by the uniform `v`.
+__device__ int write_lane(int v, int l, int old) __asm("llvm.amdgcn.writelane.i32");
+
 // v from lane (lane - 1); lane 0 keeps its own value.
 __device__ __forceinline__ u64 shift_up64(u64 v) {
     int l = lane_id();
