@@ -119,7 +119,7 @@ __global__ __launch_bounds__(kBlock) void scan_topk_kernel(const uint4 *__restri
 // Tiles of 16 queries on the matrix cores.  A wave keeps the 16 queries of
 // its tile in registers and streams its slice of rows 16 at a time.  The
 // 16 x 16 overlap counts of a group are one chain of 32 FP4 matrix steps
-// (expand_a / expand_b of mfma_tile.h): lane l (row or query l % 16, lane
+// (expand_q / expand_r of mfma_tile.h): lane l (row or query l % 16, lane
 // group g = l / 16) loads the 16-byte pieces 4i + g, i = 0..7, of its row,
 // and step 4i + c takes word c of piece i, so the four lane groups of a step
 // cover four different words and the 32 steps cover all 128.  One load
@@ -207,10 +207,7 @@ __global__ __launch_bounds__(kBlock) void scan_small_mfma_kernel(const uint4 *__
 #pragma unroll
             for (int c = 0; c < 4; c++) {
                 tp += __popc(w4[c]);
-                // formats 4 = e2m1 for both operands; scales 127 = 2^0
-                acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(mt::expand_a(qw[4 * i + c]),
-                                                                       mt::expand_b(w4[c]), acc, 4, 4, 0, 127, 0,
-                                                                       127);
+                acc = mt::mma16(mt::expand_q(qw[4 * i + c]), mt::expand_r(w4[c]), acc);
             }
         }
         tp += (uint32_t)__shfl_xor((int)tp, 16);

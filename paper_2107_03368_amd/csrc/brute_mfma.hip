@@ -59,17 +59,17 @@ __global__ __launch_bounds__(mt::kThreads) void scan_mfma_kernel(const uint4 *__
         nq = min(nq, *nq_dev);
         n_qtiles = (nq + MQ - 1) / MQ;
     }
-    // Per tile row (queries 0..255, then rows): |q| or |t|, and for queries the
-    // candidate bound and the least overlap that can reach it (the row half of
-    // these two is written but not read, so every thread stores alike).  Two
-    // sets: the current tile's, and the next tile's, written during the current tile.
+    // Per tile row (queries 0..255, then rows): |q| and the candidate bound
+    // (the row half of these two is written but not read, so every thread
+    // stores alike), and the pass test's bound or |t|.  Two sets: the current
+    // tile's, and the next tile's, written during the current tile.
     __shared__ uint32_t s_p[2][MQ + MR];
     __shared__ u64 s_th[2][MQ + MR];
-    __shared__ __align__(16) float s_cmin[2][MQ + MR];
+    __shared__ __align__(16) float s_v[2][MQ + MR];
     // per wave: the tile's passing (query, key, row) entries, appended in order
     // and written out together, so the candidate slots' atomics overlap
     // instead of waiting one after another
-    constexpr uint32_t kQueue = 320;  // room for one (a, rr) group's 256 entries past the flush mark
+    constexpr uint32_t kQueue = 320;  // room for four rows' 256 entries past the flush mark
     __shared__ uint32_t s_cq[mt::kThreads / 64][kQueue][3];
     const int r = mt::own_row();
     const bool arow = r < MQ;  // the same in a whole wave
@@ -118,18 +118,12 @@ __global__ __launch_bounds__(mt::kThreads) void scan_mfma_kernel(const uint4 *__
     auto publish = [&](const Part &p, int h) {  // read after the next barrier; no branch
         const uint32_t pv = p.ok ? lp : 0;
         const u64 th = p.ok && arow ? lt : 0;
-        // K = |q|*wB + |t|*wA - C*(wA + wB) >= |q|*wB - C*(wA + wB): a row
-        // with C*(wA + wB) below X = |q|*wB - (the bound's key) has K above
-        // it.  wA + wB is 4096, or 4097 when |q| is 0 or 4096, so a row can
-        // only pass with C >= ceil(X / 4097) = cmin (a division by a
-        // constant, a multiply and a shift; the exact key test follows)
         const uint32_t wb = (QD_BITS - pv) > 1 ? QD_BITS - pv : 1;
-        const uint32_t P = __umul24(pv, wb), Kb = (uint32_t)(th >> 32);  // |q|*wB <= 2^22
-        const uint32_t X = P - (P < Kb ? P : Kb);                          // max(P - Kb, 0)
-        const uint32_t cmin = (X + 4096u) / 4097u;
+        const float qb = p.ok ? mt::pass_bound(pv, wb, (uint32_t)(th >> 32)) : mt::kNoBound;
+        const float tp = p.ok ? (float)pv : mt::kNoRow;
         s_p[h][r] = pv;
         s_th[h][r] = th;
-        s_cmin[h][r] = p.ok ? (float)cmin : 1e30f;
+        s_v[h][r] = arow ? qb : tp;
     };
     __shared__ uint32_t s_claim[2];
     if (r == 0) {
@@ -152,7 +146,7 @@ __global__ __launch_bounds__(mt::kThreads) void scan_mfma_kernel(const uint4 *__
         uint32_t claim = 0;
         if (r == 0 && more) claim = atomicAdd(ctr, 1u);
         const bool nzero = !more || !nx.ok;
-        mt::v4f acc[8][4];
+        mt::Acc acc;
         // the next tile's metadata: loaded after every window and stored after
         // the next one (a window later, so no store waits for its load) into
         // the other set, which the previous tile's epilogue finished reading;
@@ -169,7 +163,7 @@ __global__ __launch_bounds__(mt::kThreads) void scan_mfma_kernel(const uint4 *__
         const uint32_t q0 = qt * MQ;
         const uint64_t t0 = rt * MR;
 
-        // epilogue: keys of this lane's 32 queries x 4 rows
+        // epilogue: this lane's 4 queries x 32 rows
         const int lane = r & 63;
         uint32_t (*cq)[3] = s_cq[r >> 6];
         uint32_t nqe = 0;  // entries in this wave's queue (the same in every lane)
@@ -181,61 +175,53 @@ __global__ __launch_bounds__(mt::kThreads) void scan_mfma_kernel(const uint4 *__
             }
             nqe = 0;
         };
-        // this lane's four rows: their popcounts and whether they exist, the
-        // same for every query group of the tile
-        uint32_t tpv[4];
-        bool rv[4];
 #pragma unroll
-        for (int b = 0; b < 4; b++) {
-            tpv[b] = s_p[h][MQ + mt::acc_brow(b)];
-            rv[b] = t0 + (uint64_t)mt::acc_brow(b) < n;
-        }
-        // a group's four query slots are consecutive: their least overlaps
-        // are one 16-byte read, issued a group ahead of the test
-        float4 cm_next = *reinterpret_cast<const float4 *>(&s_cmin[h][mt::acc_arow(0, 0)]);
-#pragma unroll
-        for (int a = 0; a < 8; a++) {
-            // one group of queries at a time, so their metadata loads stay next to their use
+        for (int a = 0; a < mt::QF; a++) {
+            // one fragment of queries at a time, so their metadata loads stay next to their use
             __builtin_amdgcn_sched_barrier(0);
-            const float4 cm = cm_next;
-            if (a < 7) cm_next = *reinterpret_cast<const float4 *>(&s_cmin[h][mt::acc_arow(a + 1, 0)]);
+            const int ai = mt::acc_query(a);
+            const float bound = s_v[h][ai];
+            const uint32_t qi = q0 + ai, pq = s_p[h][ai];
+            const uint32_t wa = pq > 1 ? pq : 1, wb = (QD_BITS - pq) > 1 ? QD_BITS - pq : 1;
+            const float nratio = -(float)wa * mt::inv_sw(pq);
 #pragma unroll
-            for (int rr = 0; rr < 4; rr++) {
-                const int ai = mt::acc_arow(a, rr);
-                // test this lane's 4 rows of the query at once (most miss by far)
-                const float mx = fmaxf(fmaxf(acc[a][0][rr], acc[a][1][rr]), fmaxf(acc[a][2][rr], acc[a][3][rr]));
-                const uint32_t qi = q0 + ai;
-                // (a slot past the last query has least overlap 1e30)
-                const bool act = mx >= (rr == 0 ? cm.x : rr == 1 ? cm.y : rr == 2 ? cm.z : cm.w);
-                if (ballot(act) == 0) continue;
-                const uint32_t pq = s_p[h][ai];
-                const uint32_t wa = pq > 1 ? pq : 1, wb = (QD_BITS - pq) > 1 ? QD_BITS - pq : 1;
+            for (int b = 0; b < mt::RF; b++) {
+                // 16 rows at once, then four at a time, then one (most miss by far)
+                mt::Quad v[4];
+#pragma unroll
+                for (int g = 0; g < 4; g++)
+                    v[g] = mt::quad_test(acc[a][b], g, *reinterpret_cast<const float4 *>(&s_v[h][MQ + mt::quad_row(b, g)]),
+                                         nratio);
+                const float mx = fmaxf(fmaxf(v[0].max(), v[1].max()), fmaxf(v[2].max(), v[3].max()));
+                if (ballot(mx >= bound) == 0) continue;
                 const u64 th = s_th[h][ai];
-                // K = |q|*wB + |t|*wA - C*(wA + wB): the first two terms per
-                // row once per group, then one 24-bit multiply-add per pair
-                // (C <= 4096 and wA + wB <= 4097; every term below 2^26)
+                // K = |q|*wB + |t|*wA - C*(wA + wB): 24-bit multiplies (C <= 4096
+                // and wA + wB <= 4097; every term below 2^26)
                 const uint32_t P = __umul24(pq, wb);
                 const int nsw = -(int)(wa + wb);
-                uint32_t PT[4];
 #pragma unroll
-                for (int b = 0; b < 4; b++) PT[b] = P + __umul24(tpv[b], wa);
+                for (int g = 0; g < 4; g++) {
+                    if (ballot(v[g].max() >= bound) == 0) continue;
+                    const int r0 = mt::quad_row(b, g);
 #pragma unroll
-                for (int b = 0; b < 4; b++) {
-                    const uint64_t t = t0 + mt::acc_brow(b);
-                    const uint32_t C = mt::count(acc[a][b][rr]);
-                    const uint32_t K = (uint32_t)((int)PT[b] + __mul24((int)C, nsw));
-                    const u64 key = ((u64)K << 32) | (uint32_t)t;
-                    const bool pass = act & rv[b] & (key <= th);  // no short-circuit: no branch per test
-                    const u64 pm = ballot(pass);
-                    if (pass) {
-                        const uint32_t e = nqe + lanes_below(pm);
-                        cq[e][0] = qi;
-                        cq[e][1] = K;
-                        cq[e][2] = (uint32_t)t;
+                    for (int e = 0; e < 4; e++) {
+                        const bool act = v[g].v[e] >= bound;
+                        if (ballot(act) == 0) continue;
+                        const uint32_t t = (uint32_t)t0 + r0 + e, tp = (uint32_t)s_v[h][MQ + r0 + e];
+                        const uint32_t C = mt::count(acc[a][b][4 * g + e]);
+                        const uint32_t K = (uint32_t)((int)(P + __umul24(tp, wa)) + __mul24((int)C, nsw));
+                        const bool pass = act & ((((u64)K << 32) | t) <= th);
+                        const u64 pm = ballot(pass);
+                        if (pass) {
+                            const uint32_t at = nqe + lanes_below(pm);
+                            cq[at][0] = qi;
+                            cq[at][1] = K;
+                            cq[at][2] = t;
+                        }
+                        nqe += (uint32_t)__popcll(pm);
                     }
-                    nqe += (uint32_t)__popcll(pm);
+                    if (nqe > kQueue - 256) flush();  // the next four rows add at most 4 x 64
                 }
-                if (nqe > kQueue - 256) flush();  // the next group adds at most 4 x 64
             }
         }
         flush();

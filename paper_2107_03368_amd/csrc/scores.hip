@@ -34,18 +34,6 @@ constexpr uint64_t kMinKBytes = 1ull << 30;    // minK of one batch
 constexpr uint64_t kMaxBatch = 1ull << 18;     // query descriptors per batch
 constexpr uint32_t kMaxObjects = 65536;        // object ids are uint16
 
-// Smallest of the 16 values of a row of lanes (every lane of the row gets it).
-__device__ __forceinline__ uint32_t min16(uint32_t v) {
-    uint32_t t = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, false);  // quad_perm 1,0,3,2
-    v = t < v ? t : v;
-    t = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, false);  // quad_perm 2,3,0,1
-    v = t < v ? t : v;
-    t = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x141, 0xF, 0xF, false);  // row_half_mirror
-    v = t < v ? t : v;
-    t = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x140, 0xF, 0xF, false);  // row_mirror
-    return t < v ? t : v;
-}
-
 __global__ void fill_u32_kernel(uint32_t *p, uint64_t n, uint32_t v) {
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
         p[i] = v;
@@ -127,7 +115,8 @@ __global__ __launch_bounds__(mt::kThreads) void objscan_kernel(
     const uint64_t *__restrict__ roff, const uint32_t *__restrict__ toff, uint32_t n_obj, const uint4 *__restrict__ q,
     uint32_t nq, const uint16_t *__restrict__ qpop, uint32_t n_qtiles, uint32_t *__restrict__ minK) {
     __shared__ mt::Smem sm;
-    __shared__ uint32_t s_pq[MQ], s_tp[MR], s_min[MQ];
+    __shared__ uint32_t s_pq[MQ], s_min[MQ];
+    __shared__ __align__(16) float s_tp[MR];
     const uint64_t n_tiles = (uint64_t)n_qtiles * toff[n_obj];
     const int lane = threadIdx.x & 63;
     for (uint64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
@@ -157,41 +146,45 @@ __global__ __launch_bounds__(mt::kThreads) void objscan_kernel(
             ok = (uint32_t)(r - MQ) < nb;
             const uint32_t t = ok ? order[r0 + (r - MQ)] : order[r0];
             row = db + (uint64_t)t * 32;
-            s_tp[r - MQ] = ok ? tpop[t] : 0;
+            s_tp[r - MQ] = ok ? (float)tpop[t] : 32767.f;
         }
-        mt::v4f acc[8][4];
+        mt::Acc acc;
         mt::overlap_tile(row, !ok, sm, acc);  // its barriers also publish the metadata above
 
-        // this lane's 32 descriptors x 4 rows: smallest key per descriptor.
+        // this lane's 4 descriptors x 32 rows: smallest key per descriptor.
         // K = |q|*wB - (C*(wA + wB) - |t|*wA), so the smallest K is |q|*wB
         // minus the largest C*(wA + wB) - |t|*wA; rows past the tile's end
-        // get |t| = 32767, which no real row's value can lose to.
-        int32_t tpv[4];
+        // have |t| = 32767, which no real row's value can lose to.  In fp32
+        // every value is exact: integers below 2^24, but for C = 4096 and
+        // |q| = 4096, where C*(wA + wB) = 4096 * 4097 < 2^25 is even.
+        float wa[mt::QF], sw[mt::QF], vmax[mt::QF];
 #pragma unroll
-        for (int b = 0; b < 4; b++) {
-            const int bi = mt::acc_brow(b);
-            tpv[b] = (uint32_t)bi < nb ? (int32_t)s_tp[bi] : 32767;
+        for (int a = 0; a < mt::QF; a++) {
+            const uint32_t pq = s_pq[mt::acc_query(a)];
+            const uint32_t w = pq > 1 ? pq : 1;
+            wa[a] = -(float)w;
+            sw[a] = (float)(w + ((QD_BITS - pq) > 1 ? QD_BITS - pq : 1));
+            vmax[a] = -1e30f;
         }
 #pragma unroll
-        for (int a = 0; a < 8; a++) {
-            // one group of queries at a time, so their metadata loads stay next to their use
-            __builtin_amdgcn_sched_barrier(0);
+        for (int b = 0; b < mt::RF; b++)
 #pragma unroll
-            for (int rr = 0; rr < 4; rr++) {
-                const int ai = mt::acc_arow(a, rr);
-                const uint32_t pq = s_pq[ai];
-                const int32_t wa = pq > 1 ? (int32_t)pq : 1, wb = (QD_BITS - pq) > 1 ? (int32_t)(QD_BITS - pq) : 1;
-                int32_t vmax = (int32_t)mt::count(acc[a][0][rr]) * (wa + wb) - tpv[0] * wa;
+            for (int g = 0; g < 4; g++) {
+                const float4 t4 = *reinterpret_cast<const float4 *>(&s_tp[mt::quad_row(b, g)]);
+                const float tp[4] = {t4.x, t4.y, t4.z, t4.w};
 #pragma unroll
-                for (int b = 1; b < 4; b++) {
-                    const int32_t v = (int32_t)mt::count(acc[a][b][rr]) * (wa + wb) - tpv[b] * wa;
-                    vmax = v > vmax ? v : vmax;
-                }
-                uint32_t m = (uint32_t)((int32_t)pq * wb - vmax);
-                // the 16 lanes of a row hold the same descriptors, 16 rows each
-                m = min16(m);
-                if ((lane & 15) == 0) atomicMin(&s_min[ai], m);  // the 4 waves of this descriptor half
+                for (int a = 0; a < mt::QF; a++)
+#pragma unroll
+                    for (int e = 0; e < 4; e++)
+                        vmax[a] = fmaxf(vmax[a], __builtin_fmaf(tp[e], wa[a], acc[a][b][4 * g + e] * sw[a]));
             }
+#pragma unroll
+        for (int a = 0; a < mt::QF; a++) {
+            const int ai = mt::acc_query(a);
+            const float v = fmaxf(vmax[a], __shfl_xor(vmax[a], 32));  // the other 32 rows of the wave
+            const uint32_t pq = s_pq[ai];
+            const int32_t m = (int32_t)(pq * ((QD_BITS - pq) > 1 ? QD_BITS - pq : 1)) - (int32_t)v;
+            if (lane < 32) atomicMin(&s_min[ai], (uint32_t)m);  // the 4 waves of this descriptor half
         }
         __syncthreads();
         if (r < MQ && q0 + r < nq) atomicMin(&minK[(uint64_t)(q0 + r) * n_obj + o], s_min[r]);

@@ -129,6 +129,10 @@ __global__ __launch_bounds__(64) void block_image_kernel(const uint64_t *__restr
     }
 }
 
+// Length of a query's row of levels (lbq): four consecutive blocks are stored
+// as one aligned 8-byte word.
+__host__ __device__ __forceinline__ uint64_t lbq_stride(uint64_t nblk) { return (nblk + 3) / 4 * 4; }
+
 // Bound level L of every (query, block) pair in a tile of 256 queries x 256
 // blocks: every row of the block has key >= L * wB.  With the sum image
 // alone L = A_lb = |q| - ov (ov = popcount(q AND image)); with the block's
@@ -144,7 +148,8 @@ __global__ __launch_bounds__(mt::kThreads) void bound_kernel(const uint4 *__rest
                                                              uint16_t *__restrict__ lbq, uint16_t *__restrict__ lbb,
                                                              const uint32_t *__restrict__ nq_dev) {
     __shared__ mt::Smem sm;
-    __shared__ uint32_t s_pq[mt::MA], s_dm[mt::MA], s_pmin[mt::MB], s_pmax[mt::MB];
+    __shared__ uint32_t s_pq[mt::MA], s_dm[mt::MA];
+    __shared__ __align__(16) uint32_t s_pmin[mt::MB], s_pmax[mt::MB];
     if (nq_dev) nqb = min(nqb, *nq_dev);  // the batch's size on the device (captured graphs)
     const uint64_t n_tiles = (uint64_t)n_qtiles * ((nblk + mt::MB - 1) / mt::MB);
     for (uint64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
@@ -172,37 +177,42 @@ __global__ __launch_bounds__(mt::kThreads) void bound_kernel(const uint4 *__rest
             s_pmin[own - mt::MA] = ok && bpop ? bpop[2 * (b0 + (own - mt::MA))] : 0;
             s_pmax[own - mt::MA] = ok && bpop ? bpop[2 * (b0 + (own - mt::MA)) + 1] : QD_BITS;
         }
-        mt::v4f acc[8][4];
+        mt::Acc acc;
         mt::overlap_tile(row, !ok, sm, acc);  // its barriers also publish s_pq, s_pmin, s_pmax
 #pragma unroll
-        for (int a = 0; a < 8; a++) {
-            // one group of queries at a time, so their metadata loads stay next to their use
+        for (int a = 0; a < mt::QF; a++) {
+            // one fragment of queries at a time, so their metadata loads stay next to their use
             __builtin_amdgcn_sched_barrier(0);
+            const int ai = mt::acc_query(a);
+            const uint32_t qi = q0 + ai;  // this lane's query
+            const bool in = qi < nqb;
+            const uint32_t pq = s_pq[ai], dm = s_dm[ai], wa = weight_a(pq);
 #pragma unroll
-            for (int bb = 0; bb < 4; bb++) {
-                const uint64_t blk = b0 + mt::acc_brow(bb);
-                if (blk >= nblk) continue;
-                const uint32_t pmin = s_pmin[mt::acc_brow(bb)], pmax = s_pmax[mt::acc_brow(bb)];
-                const uint32_t qa = q0 + mt::acc_arow(a, 0);  // this lane's 4 consecutive queries
-                u64 packed = 0;
+            for (int bb = 0; bb < mt::RF; bb++)
 #pragma unroll
-                for (int r = 0; r < 4; r++) {
-                    const uint32_t qi = qa + r;
-                    uint32_t v = 0xFFFFu;
-                    if (qi < nqb) {
-                        const uint32_t pq = s_pq[qi - q0], dm = s_dm[qi - q0], ov = mt::count(acc[a][bb][r]);
-                        const uint32_t al = pq - (ov < pmax ? ov : pmax);
-                        const uint32_t bl = pmin > ov ? pmin - ov : 0;
+                for (int g = 0; g < 4; g++) {
+                    const int br = mt::quad_row(bb, g);  // four consecutive blocks
+                    const uint64_t blk = b0 + br;
+                    if (blk >= nblk) continue;
+                    const uint4 mn = *reinterpret_cast<const uint4 *>(&s_pmin[br]);
+                    const uint4 mx = *reinterpret_cast<const uint4 *>(&s_pmax[br]);
+                    const uint32_t pmin[4] = {mn.x, mn.y, mn.z, mn.w}, pmax[4] = {mx.x, mx.y, mx.z, mx.w};
+                    u64 packed = 0;
+#pragma unroll
+                    for (int e = 0; e < 4; e++) {
+                        const uint32_t ov = mt::count(acc[a][bb][4 * g + e]);
+                        const uint32_t al = pq - (ov < pmax[e] ? ov : pmax[e]);
+                        const uint32_t bl = pmin[e] > ov ? pmin[e] - ov : 0;
                         // floor(bl * wA / wB); bl * wA <= 2^24
-                        const uint32_t x = __umul24(bl, weight_a(pq));
-                        v = al + (uint32_t)(((uint64_t)x * (dm & 0x3FFFFFFu)) >> (25 + (dm >> 26)));
-                        v = v < QD_BITS ? v : QD_BITS;
-                        lbq[(uint64_t)qi * nblk + blk] = (uint16_t)v;
+                        const uint32_t x = __umul24(bl, wa);
+                        uint32_t v = al + (uint32_t)(((uint64_t)x * (dm & 0x3FFFFFFu)) >> (25 + (dm >> 26)));
+                        v = in ? (v < QD_BITS ? v : QD_BITS) : 0xFFFFu;
+                        if (blk + e < nblk) lbb[(blk + e) * nqp + qi] = (uint16_t)v;  // 32 queries in a row
+                        packed |= (u64)v << (16 * e);
                     }
-                    packed |= (u64)v << (16 * r);
+                    // (a row's length is a multiple of 4; entries past the last block are not read)
+                    if (in) *reinterpret_cast<u64 *>(lbq + (uint64_t)qi * lbq_stride(nblk) + blk) = packed;
                 }
-                *reinterpret_cast<u64 *>(lbb + blk * nqp + qa) = packed;
-            }
         }
         __syncthreads();  // the next tile rewrites s_pq
     }
@@ -224,7 +234,7 @@ __global__ __launch_bounds__(256) void plan_kernel(const uint16_t *__restrict__ 
     // queries on average
     if (t2 == 0) t2 = (128 * nblk + nqb - 1) / nqb;
     if (t2 < 2 * (uint64_t)m1) t2 = 2 * (uint64_t)m1;
-    const uint16_t *row = lbq + (uint64_t)qi * nblk;
+    const uint16_t *row = lbq + (uint64_t)qi * lbq_stride(nblk);
     for (uint32_t i = tid; i < kLevels; i += 256) cum[i] = 0;
     if (tid == 0) s_bcut = kInf;
     __syncthreads();
@@ -780,11 +790,10 @@ __global__ __launch_bounds__(1024) void tile_scan_kernel(const uint32_t *__restr
 // off[b] <= x < off[b + 1] (the last block whose prefix is at most x: a
 // block without tiles has the same prefix as the next one), found by
 // bisection; tinfo[x] = (block, offset of the tile's first query in the
-// block's list, queries in the tile, the block's smallest popcount).  The
-// grid strides over the tiles the prefix counted.
+// block's list, queries in the tile).  The grid strides over the tiles the
+// prefix counted.
 __global__ __launch_bounds__(256) void tile_info_kernel(const uint32_t *__restrict__ cnt,
                                                         const uint32_t *__restrict__ off, uint64_t nblk,
-                                                        const uint16_t *__restrict__ bpop,
                                                         const uint32_t *__restrict__ ntiles,
                                                         uint4 *__restrict__ tinfo) {
     const uint32_t total = *ntiles;
@@ -802,7 +811,7 @@ __global__ __launch_bounds__(256) void tile_info_kernel(const uint32_t *__restri
         const uint32_t listed = c - short_pairs(c);  // the list's short rest is not in a tile
         const uint32_t t0 = ((uint32_t)x - off[lo]) * mt::MA;
         const uint32_t m = listed - t0 < (uint32_t)mt::MA ? listed - t0 : (uint32_t)mt::MA;
-        tinfo[x] = make_uint4((uint32_t)lo, t0, m, bpop ? bpop[2 * lo] : 0u);
+        tinfo[x] = make_uint4((uint32_t)lo, t0, m, 0u);
     }
 }
 
@@ -890,13 +899,15 @@ __global__ __launch_bounds__(mt::kThreads) void eval_kernel(const uint4 *__restr
                                                             const uint32_t *__restrict__ thrk,
                                                             uint32_t *__restrict__ ccnt, u64 *__restrict__ cand) {
     __shared__ mt::Smem sm;
-    // two copies (tiles alternate): query slot's query, |q|, k-th key; row's |t|
-    __shared__ uint32_t s_qi[2][mt::MA], s_pq[2][mt::MA], s_th[2][mt::MA], s_tp[2][mt::MB];
-    __shared__ __align__(16) float s_cmin[2][mt::MA];  // per query slot: the least overlap that can reach its k-th key
+    // two copies (tiles alternate): query slot's query, |q|, k-th key and pass
+    // test's bound; row's |t|
+    __shared__ uint32_t s_qi[2][mt::MA], s_pq[2][mt::MA], s_th[2][mt::MA];
+    __shared__ __align__(16) float s_tp[2][mt::MB];
+    __shared__ float s_bound[2][mt::MA];
     // per wave: the tile's passing (query, key, row) entries, appended in order
     // and written out together, so the candidate slots' atomics overlap
     // instead of waiting one after another
-    constexpr uint32_t kQueue = 320;  // room for one (a, rr) group's 256 entries past the flush mark
+    constexpr uint32_t kQueue = 320;  // room for four rows' 256 entries past the flush mark
     __shared__ uint32_t s_cq[mt::kThreads / 64][kQueue][3];
     const uint32_t total = *ntiles;  // written by the tile prefix
     const uint64_t vend = mt::xcd_grid(total);
@@ -906,8 +917,7 @@ __global__ __launch_bounds__(mt::kThreads) void eval_kernel(const uint4 *__restr
     // scalar load shares its completion counter with the LDS reads)
     const uint32_t vz = __builtin_amdgcn_mbcnt_lo(0u, 0u);
     // A tile's fetch is three dependent loads: its record (block b, list
-    // offset t0, queries m, the block's smallest popcount), then this thread's
-    // list entry (A rows) or row popcount (B rows), then the query's |q| and
+    // offset t0, queries m), then this thread's list entry (queries) or row popcount (rows), then the query's |q| and
     // k-th key.  Every load is unconditional and in bounds (a row past m or n
     // reads a valid entry and is masked when used).
     uint4 info;          // the record
@@ -933,30 +943,19 @@ __global__ __launch_bounds__(mt::kThreads) void eval_kernel(const uint4 *__restr
         pq = arow && ok ? pc : 0;
         th = arow && ok ? pd : 0;
     };
-    // K = |q|*wB + |t|*wA - C*(wA + wB) with |t| >= the block's smallest
-    // popcount: a row with C*(wA + wB) below X = |q|*wB + min|t|*wA - (the
-    // k-th key) has K above the k-th key.  wA + wB is 4096, or 4097 when |q|
-    // is 0 or 4096, so a row can only pass with C >= ceil(X / 4097) = cmin
-    // (a division by a constant; the exact key test follows)
-    auto cmin_of = [&](const uint4 &in) -> float {
-        const uint32_t wa = weight_a(pq), wb = weight_b(pq);
-        const uint32_t S = __umul24(pq, wb) + __umul24(in.w, wa);  // |q|*wB + min|t|*wA < 2^25
-        const uint32_t X = S - (S < th ? S : th);                    // max(S - k-th key, 0)
-        const uint32_t cmin = (X + 4096u) / 4097u;
-        return arow && ok ? (float)cmin : 1e30f;
-    };
+    auto bound_of = [&]() -> float { return arow && ok ? mt::pass_bound(pq, weight_b(pq), th) : mt::kNoBound; };
     auto row_of = [&](const uint4 &in) -> const uint4 * {
         const uint64_t r0 = (uint64_t)in.x * kBlk;
         return arow ? q + (uint64_t)qi * 32 : sorted + (ok ? r0 + (r - mt::MA) : 0) * 32;
     };
-    auto publish = [&](float cmin, int pb) {  // read after the next barrier
+    auto publish = [&](float bound, int pb) {  // read after the next barrier
         if (arow) {
             s_qi[pb][r] = qi;
             s_pq[pb][r] = pq;
             s_th[pb][r] = th;
-            s_cmin[pb][r] = cmin;
+            s_bound[pb][r] = bound;
         } else {
-            s_tp[pb][r - mt::MA] = tp;
+            s_tp[pb][r - mt::MA] = ok ? (float)tp : mt::kNoRow;
         }
     };
 
@@ -972,7 +971,7 @@ __global__ __launch_bounds__(mt::kThreads) void eval_kernel(const uint4 *__restr
     const uint4 *row = row_of(cur);
     bool cur_ok = ok;
     int par = 0;  // metadata copy of the current tile
-    publish(cmin_of(cur), par);
+    publish(bound_of(), par);
     mt::Stream st;
     mt::stream_begin(row, !cur_ok, sm, st);  // its barrier also publishes the metadata
     const int wv = r >> 6, lane = r & 63;
@@ -993,12 +992,12 @@ __global__ __launch_bounds__(mt::kThreads) void eval_kernel(const uint4 *__restr
         uint4 pa = info;      // the next tile's record, in flight
         const uint4 *nrow = row;
         bool nok = false;
-        float ncmin = 0.f;
-        mt::v4f acc[8][4];
+        float nbound = 0.f;
+        mt::Acc acc;
         // after window w: take what window w - 1 loaded (the window's own store
         // waited for every earlier load), then issue the next loads
         bool nzero = true;
-        // the waves of A rows 128..255 have nothing to multiply when the tile
+        // the waves of query slots 128..255 have nothing to multiply when the tile
         // lists at most 128 queries
         const bool idle = (r >> 8) == 1 && cur.z <= (uint32_t)(mt::MA / 2);
         mt::stream_tile(row, !cur_ok, nrow, nzero, sm, st, acc, [&](int win) {
@@ -1007,7 +1006,7 @@ __global__ __launch_bounds__(mt::kThreads) void eval_kernel(const uint4 *__restr
             if (win == 2) take_b(info);
             if (win == 3) {
                 take_c();
-                ncmin = cmin_of(info);
+                nbound = bound_of();
                 nrow = row_of(info);
                 nok = ok;
                 nzero = !more || !ok;
@@ -1017,20 +1016,8 @@ __global__ __launch_bounds__(mt::kThreads) void eval_kernel(const uint4 *__restr
             issue_c();
         }, idle);
         const uint64_t r0 = (uint64_t)cur.x * kBlk;
-        const uint32_t *t_qi = s_qi[par], *t_pq = s_pq[par], *t_th = s_th[par], *t_tp = s_tp[par];
-        const float *t_cmin = s_cmin[par];
-        // this lane's four rows: their popcounts and whether they exist, the
-        // same for every query group of the tile
-        uint32_t tpv[4];
-        bool rv[4];
-#pragma unroll
-        for (int bb = 0; bb < 4; bb++) {
-            tpv[bb] = t_tp[mt::acc_brow(bb)];
-            rv[bb] = r0 + (uint64_t)mt::acc_brow(bb) < n;
-        }
-        // a group's four query slots are consecutive: their least overlaps
-        // are one 16-byte read, issued a group ahead of the test
-        float4 cm_next = *reinterpret_cast<const float4 *>(t_cmin + mt::acc_arow(0, 0));
+        const uint32_t *t_qi = s_qi[par], *t_pq = s_pq[par], *t_th = s_th[par];
+        const float *t_tp = s_tp[par], *t_bound = s_bound[par];
         uint32_t nq = 0;  // entries in this wave's queue (the same in every lane)
         auto flush = [&]() {
             for (uint32_t e = lane; e < nq; e += 64) {
@@ -1041,48 +1028,52 @@ __global__ __launch_bounds__(mt::kThreads) void eval_kernel(const uint4 *__restr
             nq = 0;
         };
 #pragma unroll
-        for (int a = 0; a < 8; a++) {
-            // one group of queries at a time, so their metadata loads stay next to their use
+        for (int a = 0; a < mt::QF; a++) {
+            // one fragment of queries at a time, so their metadata loads stay next to their use
             __builtin_amdgcn_sched_barrier(0);
-            const float4 cm = cm_next;
-            if (a < 7) cm_next = *reinterpret_cast<const float4 *>(t_cmin + mt::acc_arow(a + 1, 0));
+            const int i = mt::acc_query(a);
+            const float bound = t_bound[i];
+            const uint32_t pk = t_pq[i], wa = weight_a(pk), wb = weight_b(pk);
+            const float nratio = -(float)wa * mt::inv_sw(pk);
 #pragma unroll
-            for (int rr = 0; rr < 4; rr++) {
-                const uint32_t i = (uint32_t)mt::acc_arow(a, rr);
-                // most (query, row) pairs miss the k-th key by far: test this
-                // lane's 4 rows at once against the least useful overlap
-                const float mx = fmaxf(fmaxf(acc[a][0][rr], acc[a][1][rr]), fmaxf(acc[a][2][rr], acc[a][3][rr]));
-                // (a slot past the tile's queries has least overlap 1e30)
-                const bool act = mx >= (rr == 0 ? cm.x : rr == 1 ? cm.y : rr == 2 ? cm.z : cm.w);
-                if (ballot(act) == 0) continue;
-                const uint32_t qk = t_qi[i];
-                const uint32_t pk = t_pq[i];
-                const uint32_t wa = weight_a(pk), wb = weight_b(pk);
-                const uint32_t tk = t_th[i];
-                // K = |q|*wB + |t|*wA - C*(wA + wB): the first two terms per
-                // row once per group, then one 24-bit multiply-add per pair
-                // (C <= 4096 and wA + wB <= 4097; every term below 2^26)
+            for (int b = 0; b < mt::RF; b++) {
+                // most (query, row) pairs miss the k-th key by far: 16 rows of
+                // the lane's query at once, then four at a time, then one
+                mt::Quad v4[4];
+#pragma unroll
+                for (int g = 0; g < 4; g++)
+                    v4[g] = mt::quad_test(acc[a][b], g, *reinterpret_cast<const float4 *>(t_tp + mt::quad_row(b, g)),
+                                          nratio);
+                const float mx = fmaxf(fmaxf(v4[0].max(), v4[1].max()), fmaxf(v4[2].max(), v4[3].max()));
+                if (ballot(mx >= bound) == 0) continue;
+                const uint32_t qk = t_qi[i], tk = t_th[i];
+                // K = |q|*wB + |t|*wA - C*(wA + wB): 24-bit multiplies (C <= 4096
+                // and wA + wB <= 4097; every term below 2^26)
                 const uint32_t P = __umul24(pk, wb);
                 const int nsw = -(int)(wa + wb);
-                uint32_t PT[4];
 #pragma unroll
-                for (int bb = 0; bb < 4; bb++) PT[bb] = P + __umul24(tpv[bb], wa);
+                for (int g = 0; g < 4; g++) {
+                    if (ballot(v4[g].max() >= bound) == 0) continue;
+                    const int rq = mt::quad_row(b, g);
 #pragma unroll
-                for (int bb = 0; bb < 4; bb++) {
-                    const uint64_t rw = r0 + mt::acc_brow(bb);
-                    const uint32_t C = mt::count(acc[a][bb][rr]);
-                    const uint32_t K = (uint32_t)((int)PT[bb] + __mul24((int)C, nsw));
-                    const bool pass = act & rv[bb] & (K <= tk);  // no short-circuit: no branch per test
-                    const u64 pm = ballot(pass);
-                    if (pass) {
-                        const uint32_t e = nq + lanes_below(pm);
-                        cq[e][0] = qk;
-                        cq[e][1] = K;
-                        cq[e][2] = (uint32_t)rw;
+                    for (int e = 0; e < 4; e++) {
+                        const bool act = v4[g].v[e] >= bound;
+                        if (ballot(act) == 0) continue;
+                        const uint32_t tpe = (uint32_t)t_tp[rq + e];
+                        const uint32_t C = mt::count(acc[a][b][4 * g + e]);
+                        const uint32_t K = (uint32_t)((int)(P + __umul24(tpe, wa)) + __mul24((int)C, nsw));
+                        const bool pass = act & (K <= tk);
+                        const u64 pm = ballot(pass);
+                        if (pass) {
+                            const uint32_t at = nq + lanes_below(pm);
+                            cq[at][0] = qk;
+                            cq[at][1] = K;
+                            cq[at][2] = (uint32_t)r0 + rq + e;
+                        }
+                        nq += (uint32_t)__popcll(pm);
                     }
-                    nq += (uint32_t)__popcll(pm);
+                    if (nq > kQueue - 256) flush();  // the next four rows add at most 4 x 64
                 }
-                if (nq > kQueue - 256) flush();  // the next group adds at most 4 x 64
             }
         }
         if (nq > 64) {
@@ -1100,7 +1091,7 @@ __global__ __launch_bounds__(mt::kThreads) void eval_kernel(const uint4 *__restr
             break;
         }
         par ^= 1;
-        publish(ncmin, par);  // the other copy: this tile's may still be read
+        publish(nbound, par);  // the other copy: this tile's may still be read
         cur = info;
         row = nrow;
         cur_ok = nok;
@@ -1212,7 +1203,7 @@ __global__ __launch_bounds__(256) void select_kernel(uint32_t k, const uint16_t 
             uint32_t clear = 0;
             for (uint32_t j = 0; j < 32; j++) {
                 const uint64_t b = wd * 32 + j;
-                if (b < nblk && range_key(lbq[(uint64_t)qi * nblk + b], (uint32_t)b) > end) clear |= 1u << j;
+                if (b < nblk && range_key(lbq[(uint64_t)qi * lbq_stride(nblk) + b], (uint32_t)b) > end) clear |= 1u << j;
             }
             done[(uint64_t)wd * nqp + qi] &= ~clear;
         }
@@ -1371,7 +1362,7 @@ BlockedLayout blocked_layout(qd_tree_t t, uint32_t nq, uint32_t k, bool model) {
         return at;
     };
     L.qpop = take(P * 2);
-    L.lbq = take(P * nblk * 2);
+    L.lbq = take(P * lbq_stride(nblk) * 2);
     L.lbb = take(P * nblk * 2);
     L.list = take(P * nblk * 2);
     L.cuts = take(P * (kRounds + 1) * 8);
@@ -1541,7 +1532,7 @@ int blocked_batch(qd_tree_t t, const BlockedLayout &L, char *ws, const uint64_t 
                                nqp, act, nact, rec, frange, donebits, list, cnt, want_stats ? qst : nullptr);
             hipLaunchKernelGGL(tile_scan_kernel, dim3(1), dim3(1024), 0, s, cnt, nblk, off, voff, ctr + 2);
             hipLaunchKernelGGL(tile_info_kernel, dim3((uint32_t)info_grid), dim3(256), 0, s, cnt, off, nblk,
-                               t->d_bpop, ctr + 2, tinfo);
+                               ctr + 2, tinfo);
         }
         if (!graph) {
             hipError_t e = hipMemcpyAsync(hb, nact, 4, hipMemcpyDeviceToHost, s);
