@@ -241,77 +241,148 @@ __global__ __launch_bounds__(kBlock) void scan_small_mfma_kernel(const uint4 *__
     }
 }
 
+// Ascending order of a[0 .. n) in place, n <= the block's threads: every thread
+// finds its entry's rank by counting (ties by position), so it takes two
+// barriers where a sorting network takes one per step.
+__device__ __forceinline__ void rank_sort(u64 *a, uint32_t n) {
+    const uint32_t i = threadIdx.x;
+    const u64 mine = i < n ? a[i] : 0;
+    uint32_t rank = 0;
+    if (i < n)
+        for (uint32_t j = 0; j < n; j++) rank += a[j] < mine || (a[j] == mine && j < i);
+    __syncthreads();
+    if (i < n) a[rank] = mine;
+    __syncthreads();
+}
+
+// Sorts a[0 .. n); a must have room for the next power of two.
+__device__ inline void sort_keys(u64 *a, uint32_t n) {
+    if (n <= kBlock) {
+        rank_sort(a, n);
+        return;
+    }
+    const uint32_t np = next_pow2(n);
+    for (uint32_t i = n + threadIdx.x; i < np; i += kBlock) a[i] = KEY_NONE;
+    __syncthreads();
+    block_bitonic_sort(a, np);
+}
+
 // One block per query: exact top k from n_parts sorted lists of k keys, then
-// the result rows.  U = the k-th smallest list head bounds the k-th key from
+// the result rows.  The k-th smallest list head U bounds the k-th key from
 // above (those k heads are k distinct candidates), and only lists whose head
-// is <= U (at most k of them: keys are distinct) can hold keys <= U, so at
-// most k*k candidates are gathered and sorted.  The lists are first read
-// only at their heads, then the qualifying lists' entries all at once.
+// is <= U (at most k of them: keys are distinct) can hold keys <= U.
+//  1. Every thread loads its heads (i, i + 256, ...) and keeps their least;
+//     the k-th smallest K among the 256 least ones, found by bisection in
+//     every wave, bounds U, so usually only a few more than k heads are left
+//     (all of them only when they tie).
+//  2. Those heads are sorted; the first k of them name the lists.
+//  3. The lists' entries <= U are gathered (at most k * k) and sorted.
+// Bound by the latency of its three dependent loads (heads, entries, rows).
+// 8 queries x 2,048 lists, k = 10: 12 us; sorting every head in LDS and one
+// thread per result row took 49 us.
 __global__ __launch_bounds__(kBlock) void merge_emit_kernel(const u64 *__restrict__ part, uint32_t n_parts,
                                                             uint32_t k, const uint64_t *__restrict__ q,
                                                             const uint64_t *__restrict__ db, uint32_t *idx,
                                                             int32_t *missed, int32_t *extra, float *dist,
                                                             const uint32_t *__restrict__ nq_dev) {
     if (nq_dev && blockIdx.x >= *nq_dev) return;  // whole block
-    __shared__ u64 heads[kMaxParts];
-    __shared__ u64 cand[kMaxCand];
-    __shared__ uint32_t qual[QD_MAX_K];
-    __shared__ uint32_t ncand, nqual;
-    const uint32_t qi = blockIdx.x;
+    constexpr uint32_t kHeads = kMaxParts / kBlock;
+    __shared__ u64 least[kBlock];
+    __shared__ u64 cand[kMaxCand];        // the heads left, then the candidates
+    __shared__ uint16_t qual[QD_MAX_K];
+    __shared__ uint32_t nleft, ncand, nqual;
+    static_assert(kMaxCand >= kMaxParts, "every head fits");
+    const uint32_t qi = blockIdx.x, tid = threadIdx.x;
+    const int lane = lane_id();
     const u64 *lists = part + (uint64_t)qi * n_parts * k;
-    const uint32_t hp = next_pow2(n_parts < 2 ? 2 : n_parts);
-    for (uint32_t i = threadIdx.x; i < hp; i += blockDim.x) heads[i] = i < n_parts ? lists[(uint64_t)i * k] : KEY_NONE;
-    if (threadIdx.x == 0) ncand = nqual = 0;
+    u64 h[kHeads], mn = KEY_NONE;
+#pragma unroll
+    for (uint32_t i = 0; i < kHeads; i++) {
+        h[i] = i * kBlock + tid < n_parts ? lists[(uint64_t)(i * kBlock + tid) * k] : KEY_NONE;
+        mn = h[i] < mn ? h[i] : mn;
+    }
+    least[tid] = mn;
+    if (tid == 0) nleft = ncand = nqual = 0;
     __syncthreads();
-    block_bitonic_sort(heads, hp);
-    const u64 U = k <= n_parts ? heads[k - 1] : KEY_NONE;
-    for (uint32_t p = threadIdx.x; p < n_parts; p += blockDim.x) {
-        const u64 h = lists[(uint64_t)p * k];
-        if (h != KEY_NONE && h <= U) {
-            const uint32_t at = atomicAdd(&nqual, 1u);
-            if (at < QD_MAX_K) qual[at] = p;
+    // the k-th smallest K of the 256 least heads (keys are below 2^25 << 32)
+    u64 U1 = KEY_NONE;
+    {
+        uint32_t kv[4], real = 0;
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            kv[i] = (uint32_t)(least[64 * i + lane] >> 32);
+            real += (uint32_t)__popcll(ballot(kv[i] != 0xFFFFFFFFu));
+        }
+        if (real >= k) {
+            uint32_t lo = 0, hi = (1u << 25) - 1;
+            while (lo < hi) {
+                const uint32_t mid = (lo + hi) / 2;
+                uint32_t c = 0;
+#pragma unroll
+                for (int i = 0; i < 4; i++) c += (uint32_t)__popcll(ballot(kv[i] <= mid));
+                if (c >= k)
+                    hi = mid;
+                else
+                    lo = mid + 1;
+            }
+            U1 = ((u64)lo << 32) | 0xFFFFFFFFu;
         }
     }
+#pragma unroll
+    for (uint32_t i = 0; i < kHeads; i++)
+        if (h[i] != KEY_NONE && h[i] <= U1) cand[atomicAdd(&nleft, 1u)] = h[i];
     __syncthreads();
-    const uint32_t nl = nqual < (uint32_t)QD_MAX_K ? nqual : (uint32_t)QD_MAX_K;
-    for (uint32_t i = threadIdx.x; i < nl * k; i += blockDim.x) {
+    const uint32_t nh = nleft;
+    u64 U = KEY_NONE;
+    if (nh > k) {
+        sort_keys(cand, nh);
+        U = cand[k - 1];
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < kHeads; i++)
+        if (h[i] != KEY_NONE && h[i] <= U && h[i] <= U1) qual[atomicAdd(&nqual, 1u)] = (uint16_t)(i * kBlock + tid);
+    __syncthreads();  // also: every thread has read U before cand is rewritten
+    const uint32_t nl = nqual;  // <= k
+    for (uint32_t i = tid; i < nl * k; i += kBlock) {
         const u64 e = lists[(uint64_t)qual[i / k] * k + i % k];
         if (e != KEY_NONE && e <= U) cand[atomicAdd(&ncand, 1u)] = e;  // a prefix of each list
     }
     __syncthreads();
     const uint32_t nc = ncand;
-    const uint32_t cp = next_pow2(nc < 2 ? 2 : nc);
-    for (uint32_t i = nc + threadIdx.x; i < cp; i += blockDim.x) cand[i] = KEY_NONE;
-    __syncthreads();
-    block_bitonic_sort(cand, cp);
-    if (threadIdx.x < k) {
-        const uint32_t r = threadIdx.x;
+    sort_keys(cand, nc);
+    // the result rows: 8 lanes each, 32 rows at a time
+    const int j = lane & 7;
+    const uint4 *q4 = reinterpret_cast<const uint4 *>(q) + (uint64_t)qi * 32;
+    uint4 qv[4];
+    uint32_t pq = 0;
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        qv[i] = q4[j + 8 * i];
+        pq += popc4(qv[i]);
+    }
+    pq = sum8(pq);
+    const uint32_t wa = pq > 1 ? pq : 1, wb = (QD_BITS - pq) > 1 ? QD_BITS - pq : 1;
+    for (uint32_t r = tid >> 3; r < k; r += kBlock / 8) {  // the same r in 8 lanes
         const uint64_t o = (uint64_t)qi * k + r;
         const u64 e = r < nc ? cand[r] : KEY_NONE;
-        if (e == KEY_NONE) {
-            idx[o] = QD_PAD_IDX;
-            missed[o] = -1;
-            extra[o] = -1;
-            dist[o] = __builtin_inff();
-        } else {
-            const uint32_t row = (uint32_t)e;
-            const uint64_t *qq = q + (uint64_t)qi * QD_WORDS;
-            const uint64_t *tt = db + (uint64_t)row * QD_WORDS;
-            uint32_t a = 0, b = 0, pqv = 0;
-            for (int w = 0; w < QD_WORDS; w++) {
-                const uint64_t x = qq[w], y = tt[w];
-                a += __popcll(x & ~y);
-                b += __popcll(~x & y);
-                pqv += __popcll(x);
-            }
-            const uint32_t wav = pqv > 1 ? pqv : 1;
-            const uint32_t wbv = (QD_BITS - pqv) > 1 ? QD_BITS - pqv : 1;
-            const uint32_t K = a * wbv + b * wav;
-            idx[o] = row;
-            missed[o] = (int32_t)a;
-            extra[o] = (int32_t)b;
-            dist[o] = (float)((double)K / ((double)wav * (double)wbv));
+        const uint32_t row = e == KEY_NONE ? 0 : (uint32_t)e;
+        const uint4 *t4 = reinterpret_cast<const uint4 *>(db) + (uint64_t)row * 32;
+        uint32_t c = 0, tp = 0;
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const uint4 t = t4[j + 8 * i];
+            c += popc_and4(t, qv[i]);
+            tp += popc4(t);
         }
+        c = sum8(c);
+        tp = sum8(tp);
+        if (j != 0) continue;
+        const uint32_t a = pq - c, b = tp - c, K = a * wb + b * wa;
+        const bool none = e == KEY_NONE;
+        idx[o] = none ? QD_PAD_IDX : row;
+        missed[o] = none ? -1 : (int32_t)a;
+        extra[o] = none ? -1 : (int32_t)b;
+        dist[o] = none ? __builtin_inff() : (float)((double)K / ((double)wa * (double)wb));
     }
 }
 
@@ -389,11 +460,15 @@ BruteLaunch brute_launch_shape(uint64_t n, uint32_t nq, uint32_t k, uint32_t qt_
             parts = (want_waves + sh.n_qtiles - 1) / sh.n_qtiles;
         }
     }
-    const uint64_t max_by_rows = (n + 255) / 256;  // at least 256 rows per wave
+    // at least so many rows per wave: 256 where the caller asks for slices;
+    // else two steps of the wave's loop, so that a small database is spread
+    // over the chip (10,000 rows x 1 query: 5 us in 625 waves, 19 in 40)
+    const uint64_t step = matrix ? (uint64_t)kSmallRows : (uint64_t)kRowsPerStep;
+    const uint64_t least = parts_force ? 256 : 2 * step;
+    const uint64_t max_by_rows = (n + least - 1) / least;
     if (parts > max_by_rows) parts = max_by_rows;
     if (parts > kMaxParts) parts = kMaxParts;
     if (parts < 1) parts = 1;
-    const uint64_t step = matrix ? (uint64_t)kSmallRows : (uint64_t)kRowsPerStep;
     uint64_t rpp = (n + parts - 1) / parts;
     rpp = (rpp + step - 1) / step * step;
     sh.rows_per_part = rpp;
