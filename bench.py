@@ -657,7 +657,7 @@ def smallbatch_main(args, w, dev):
                 res["planes_scan_ms"] = ms / max(cnt, 1)
             else:
                 # the kernel that passes over all rows: the register-tiled scan, the
-                # 16-query matrix tiles, or (from 160 queries) the 256 x 256 tiles,
+                # 16-query matrix tiles, or (larger batches) the matrix pass,
                 # whose call also scans a sample of the rows first
                 (ms_b, cnt_b) = qd.profile_read("wh_scan_mfma")
                 (ms_v, cnt_v), (ms_m, cnt_m) = qd.profile_read("wh_scan_topk"), qd.profile_read("wh_scan_small_mfma")

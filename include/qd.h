@@ -483,8 +483,8 @@ int qd_model_train(qd_model_t m, qd_tree_t t, const uint64_t *d_q, uint32_t nq, 
  * schedule; a model only with the blocked order, where it sets the start of
  * round 1, its descent running on the plan's memory; no scores or traces);
  * query_tile picks the sequential
- * scan: 0 = the matrix cores when max_qdesc >= 160 over >= 65,536 rows (as
- * qd_knn_bruteforce decides for a batch of max_qdesc), else the row scan with
+ * scan: 0 = the matrix pass where qd_knn_bruteforce takes it for a batch of
+ * max_qdesc, else the row scan with
  * that query tile (as in qd_knn_bruteforce_shaped; 0 = the one
  * qd_knn_bruteforce picks for max_qdesc queries).  It allocates all its device memory at
  * creation and records one batch -- the k-NN of every descriptor, then the

@@ -39,7 +39,8 @@ __global__ __launch_bounds__(kBlock) void scan_topk_kernel(const uint4 *__restri
                                                            const uint4 *__restrict__ q, uint32_t nq, uint32_t k,
                                                            uint32_t n_qtiles, uint32_t n_parts,
                                                            uint64_t rows_per_part, u64 *__restrict__ part,
-                                                           const uint32_t *__restrict__ nq_dev) {
+                                                           const uint32_t *__restrict__ nq_dev,
+                                                           const uint32_t *__restrict__ qmap) {
     if (nq_dev) {
         nq = *nq_dev;  // size given on the device (captured graphs)
         if ((blockIdx.x % n_qtiles) * QT >= nq) return;  // whole block
@@ -59,10 +60,11 @@ __global__ __launch_bounds__(kBlock) void scan_topk_kernel(const uint4 *__restri
 #pragma unroll
     for (int t = 0; t < QT; t++) {
         const uint32_t qi = qtile * QT + t;
+        const uint64_t qr = qi < nq && qmap ? qmap[qi] : qi;  // the query's row
         uint32_t s = 0;
 #pragma unroll
         for (int i = 0; i < 4; i++) {
-            qv[t][i] = qi < nq ? q[(uint64_t)qi * 32 + j + 8 * i] : make_uint4(0, 0, 0, 0);
+            qv[t][i] = qi < nq ? q[qr * 32 + j + 8 * i] : make_uint4(0, 0, 0, 0);
             s += popc4(qv[t][i]);
         }
         pq[t] = readfirst(sum8(s));
@@ -241,20 +243,6 @@ __global__ __launch_bounds__(kBlock) void scan_small_mfma_kernel(const uint4 *__
     }
 }
 
-// Ascending order of a[0 .. n) in place, n <= the block's threads: every thread
-// finds its entry's rank by counting (ties by position), so it takes two
-// barriers where a sorting network takes one per step.
-__device__ __forceinline__ void rank_sort(u64 *a, uint32_t n) {
-    const uint32_t i = threadIdx.x;
-    const u64 mine = i < n ? a[i] : 0;
-    uint32_t rank = 0;
-    if (i < n)
-        for (uint32_t j = 0; j < n; j++) rank += a[j] < mine || (a[j] == mine && j < i);
-    __syncthreads();
-    if (i < n) a[rank] = mine;
-    __syncthreads();
-}
-
 // Sorts a[0 .. n); a must have room for the next power of two.
 __device__ inline void sort_keys(u64 *a, uint32_t n) {
     if (n <= kBlock) {
@@ -278,13 +266,15 @@ __device__ inline void sort_keys(u64 *a, uint32_t n) {
 //  2. Those heads are sorted; the first k of them name the lists.
 //  3. The lists' entries <= U are gathered (at most k * k) and sorted.
 // Bound by the latency of its three dependent loads (heads, entries, rows).
+// qmap (nullable): list set i belongs to row qmap[i] of q and of the outputs.
 // 8 queries x 2,048 lists, k = 10: 12 us; sorting every head in LDS and one
 // thread per result row took 49 us.
 __global__ __launch_bounds__(kBlock) void merge_emit_kernel(const u64 *__restrict__ part, uint32_t n_parts,
                                                             uint32_t k, const uint64_t *__restrict__ q,
                                                             const uint64_t *__restrict__ db, uint32_t *idx,
                                                             int32_t *missed, int32_t *extra, float *dist,
-                                                            const uint32_t *__restrict__ nq_dev) {
+                                                            const uint32_t *__restrict__ nq_dev,
+                                                            const uint32_t *__restrict__ qmap) {
     if (nq_dev && blockIdx.x >= *nq_dev) return;  // whole block
     constexpr uint32_t kHeads = kMaxParts / kBlock;
     __shared__ u64 least[kBlock];
@@ -350,40 +340,10 @@ __global__ __launch_bounds__(kBlock) void merge_emit_kernel(const u64 *__restric
     __syncthreads();
     const uint32_t nc = ncand;
     sort_keys(cand, nc);
-    // the result rows: 8 lanes each, 32 rows at a time
-    const int j = lane & 7;
-    const uint4 *q4 = reinterpret_cast<const uint4 *>(q) + (uint64_t)qi * 32;
-    uint4 qv[4];
-    uint32_t pq = 0;
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-        qv[i] = q4[j + 8 * i];
-        pq += popc4(qv[i]);
-    }
-    pq = sum8(pq);
-    const uint32_t wa = pq > 1 ? pq : 1, wb = (QD_BITS - pq) > 1 ? QD_BITS - pq : 1;
-    for (uint32_t r = tid >> 3; r < k; r += kBlock / 8) {  // the same r in 8 lanes
-        const uint64_t o = (uint64_t)qi * k + r;
-        const u64 e = r < nc ? cand[r] : KEY_NONE;
-        const uint32_t row = e == KEY_NONE ? 0 : (uint32_t)e;
-        const uint4 *t4 = reinterpret_cast<const uint4 *>(db) + (uint64_t)row * 32;
-        uint32_t c = 0, tp = 0;
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            const uint4 t = t4[j + 8 * i];
-            c += popc_and4(t, qv[i]);
-            tp += popc4(t);
-        }
-        c = sum8(c);
-        tp = sum8(tp);
-        if (j != 0) continue;
-        const uint32_t a = pq - c, b = tp - c, K = a * wb + b * wa;
-        const bool none = e == KEY_NONE;
-        idx[o] = none ? QD_PAD_IDX : row;
-        missed[o] = none ? -1 : (int32_t)a;
-        extra[o] = none ? -1 : (int32_t)b;
-        dist[o] = none ? __builtin_inff() : (float)((double)K / ((double)wa * (double)wb));
-    }
+    // (every list entry taken is a real key: the ranks past them are padded)
+    const uint64_t qr = qmap ? qmap[qi] : qi;
+    emit_rows(cand, nc, k, reinterpret_cast<const uint4 *>(q) + qr * 32, reinterpret_cast<const uint4 *>(db), qr * k, idx,
+              missed, extra, dist);
 }
 
 __global__ __launch_bounds__(kBlock) void popcount_rows_kernel(const uint4 *__restrict__ db, uint64_t n,
@@ -427,9 +387,10 @@ uint64_t small_mfma_resident_waves(uint32_t k) {
 
 template <int QT>
 void launch_scan(dim3 grid, hipStream_t s, const uint4 *db, uint64_t n, const uint4 *q, uint32_t nq, uint32_t k,
-                 uint32_t n_qtiles, uint32_t n_parts, uint64_t rpp, u64 *part, const uint32_t *nq_dev) {
+                 uint32_t n_qtiles, uint32_t n_parts, uint64_t rpp, u64 *part, const uint32_t *nq_dev,
+                 const uint32_t *qmap) {
     hipLaunchKernelGGL(scan_topk_kernel<QT>, grid, dim3(kBlock), 0, s, db, n, q, nq, k, n_qtiles, n_parts, rpp, part,
-                       nq_dev);
+                       nq_dev, qmap);
 }
 
 }  // namespace
@@ -481,7 +442,8 @@ BruteLaunch brute_launch_shape(uint64_t n, uint32_t nq, uint32_t k, uint32_t qt_
 
 int brute_launch(const BruteLaunch &sh, u64 *part, const uint64_t *d_db, uint64_t n, const uint64_t *d_q, uint32_t nq,
                  const uint32_t *nq_dev, uint32_t k, uint32_t *d_idx, int32_t *d_missed, int32_t *d_extra,
-                 float *d_dist, hipStream_t s, bool timed) {
+                 float *d_dist, hipStream_t s, bool timed, const uint32_t *qmap) {
+    if (qmap && sh.qt == QD_QUERY_TILE_MATRIX) return fail(QD_ERR_INVALID, "a query list takes the vector scan");
     // the dispatch packet holds the grid size in work-items as a 32-bit number
     if (sh.blocks * kBlock > 0xFFFFFFFFull) return fail(QD_ERR_UNSUPPORTED, "launch too large");
     const uint4 *db4 = reinterpret_cast<const uint4 *>(d_db);
@@ -494,18 +456,18 @@ int brute_launch(const BruteLaunch &sh, u64 *part, const uint64_t *d_db, uint64_
     } else {
         KernelTimer timer(timed ? "wh_scan_topk" : nullptr, s);
         switch (sh.qt) {
-            case 1: launch_scan<1>(grid, s, db4, n, q4, nq, k, sh.n_qtiles, sh.n_parts, sh.rows_per_part, part, nq_dev); break;
-            case 2: launch_scan<2>(grid, s, db4, n, q4, nq, k, sh.n_qtiles, sh.n_parts, sh.rows_per_part, part, nq_dev); break;
-            case 4: launch_scan<4>(grid, s, db4, n, q4, nq, k, sh.n_qtiles, sh.n_parts, sh.rows_per_part, part, nq_dev); break;
-            case 8: launch_scan<8>(grid, s, db4, n, q4, nq, k, sh.n_qtiles, sh.n_parts, sh.rows_per_part, part, nq_dev); break;
-            default: launch_scan<16>(grid, s, db4, n, q4, nq, k, sh.n_qtiles, sh.n_parts, sh.rows_per_part, part, nq_dev); break;
+            case 1: launch_scan<1>(grid, s, db4, n, q4, nq, k, sh.n_qtiles, sh.n_parts, sh.rows_per_part, part, nq_dev, qmap); break;
+            case 2: launch_scan<2>(grid, s, db4, n, q4, nq, k, sh.n_qtiles, sh.n_parts, sh.rows_per_part, part, nq_dev, qmap); break;
+            case 4: launch_scan<4>(grid, s, db4, n, q4, nq, k, sh.n_qtiles, sh.n_parts, sh.rows_per_part, part, nq_dev, qmap); break;
+            case 8: launch_scan<8>(grid, s, db4, n, q4, nq, k, sh.n_qtiles, sh.n_parts, sh.rows_per_part, part, nq_dev, qmap); break;
+            default: launch_scan<16>(grid, s, db4, n, q4, nq, k, sh.n_qtiles, sh.n_parts, sh.rows_per_part, part, nq_dev, qmap); break;
         }
     }
     QD_HIP_CHECK(hipGetLastError());
     {
         KernelTimer timer(timed ? "topk_merge" : nullptr, s);
         hipLaunchKernelGGL(merge_emit_kernel, dim3(nq), dim3(kBlock), 0, s, part, sh.n_parts, k, d_q, d_db, d_idx,
-                           d_missed, d_extra, d_dist, nq_dev);
+                           d_missed, d_extra, d_dist, nq_dev, qmap);
     }
     QD_HIP_CHECK(hipGetLastError());
     return QD_OK;
@@ -517,7 +479,7 @@ int merge_launch(const u64 *part, uint32_t n_parts, uint32_t k, const uint64_t *
                                                         kMaxParts);
     KernelTimer timer("topk_merge", s);
     hipLaunchKernelGGL(merge_emit_kernel, dim3(nq), dim3(kBlock), 0, s, part, n_parts, k, d_q, d_db, d_idx, d_missed,
-                       d_extra, d_dist, nullptr);
+                       d_extra, d_dist, nullptr, nullptr);
     QD_HIP_CHECK(hipGetLastError());
     return QD_OK;
 }
@@ -537,10 +499,6 @@ int popcount_rows_launch(const uint64_t *d_db, uint64_t n, uint16_t *d_pop, hipS
     return QD_OK;
 }
 
-// Batches of at least kMfmaMinQueries queries over at least kMfmaMinRows
-// rows use the matrix-core path (the overlap counts are then a dense
-// contraction).
-
 int knn_bruteforce_impl(const uint64_t *d_db, uint64_t n, const uint64_t *d_q, uint32_t nq, uint32_t k,
                         uint32_t *d_idx, int32_t *d_missed, int32_t *d_extra, float *d_dist, void *stream,
                         uint32_t qt_force, uint32_t parts_force) {
@@ -552,7 +510,7 @@ int knn_bruteforce_impl(const uint64_t *d_db, uint64_t n, const uint64_t *d_q, u
     if (qt_force && qt_force != 1 && qt_force != 2 && qt_force != 4 && qt_force != 8 && qt_force != 16 &&
         qt_force != QD_QUERY_TILE_MATRIX)
         return fail(QD_ERR_INVALID, "query tile %u not in {1,2,4,8,16,QD_QUERY_TILE_MATRIX}", qt_force);
-    if (qt_force == 0 && parts_force == 0 && nq >= kMfmaMinQueries && n >= kMfmaMinRows) {
+    if (qt_force == 0 && parts_force == 0 && mfma_eligible(n, nq, k)) {
         const int rc = knn_bruteforce_mfma(d_db, n, d_q, nq, k, d_idx, d_missed, d_extra, d_dist, stream);
         if (rc != QD_ERR_UNSUPPORTED) return rc;
         clear_error();

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "qd.h"
+
 namespace qd {
 
 typedef unsigned long long u64;
@@ -104,6 +106,56 @@ __device__ __forceinline__ uint32_t next_pow2(uint32_t v) {
     uint32_t p = 1;
     while (p < v) p <<= 1;
     return p;
+}
+
+// Ascending order of a[0 .. n) in place, n <= the block's threads: every thread
+// finds its entry's rank by counting (ties by position), so it takes two
+// barriers where a sorting network takes one per step.
+__device__ __forceinline__ void rank_sort(u64 *a, uint32_t n) {
+    const uint32_t i = threadIdx.x;
+    const u64 mine = i < n ? a[i] : 0;
+    uint32_t rank = 0;
+    if (i < n)
+        for (uint32_t j = 0; j < n; j++) rank += a[j] < mine || (a[j] == mine && j < i);
+    __syncthreads();
+    if (i < n) a[rank] = mine;
+    __syncthreads();
+}
+
+// A query's results from its sorted keys (K << 32 | row; keys[0 .. nc) in LDS,
+// the ranks past them padded) by the whole block: 8 lanes per result row.
+// q4, db4: the query's and the database's rows; out[o0 + rank].
+__device__ __forceinline__ void emit_rows(const u64 *keys, uint32_t nc, uint32_t k, const uint4 *q4, const uint4 *db4,
+                                          uint64_t o0, uint32_t *idx, int32_t *missed, int32_t *extra, float *dist) {
+    const int j = lane_id() & 7;
+    uint4 qv[4];
+    uint32_t pq = 0;
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        qv[i] = q4[j + 8 * i];
+        pq += popc4(qv[i]);
+    }
+    pq = sum8(pq);
+    const uint32_t wa = pq > 1 ? pq : 1, wb = (QD_BITS - pq) > 1 ? QD_BITS - pq : 1;
+    for (uint32_t r = threadIdx.x >> 3; r < k; r += blockDim.x >> 3) {  // the same r in 8 lanes
+        const bool none = r >= nc;
+        const uint32_t row = none ? 0 : (uint32_t)keys[r];
+        uint32_t c = 0, tp = 0;
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const uint4 t = db4[(uint64_t)row * 32 + j + 8 * i];
+            c += popc_and4(t, qv[i]);
+            tp += popc4(t);
+        }
+        c = sum8(c);
+        tp = sum8(tp);
+        if (j != 0) continue;
+        const uint32_t a = pq - c, b = tp - c, K = a * wb + b * wa;
+        idx[o0 + r] = none ? QD_PAD_IDX : row;
+        missed[o0 + r] = none ? -1 : (int32_t)a;
+        extra[o0 + r] = none ? -1 : (int32_t)b;
+        dist[o0 + r] = none ? __builtin_inff() : (float)((double)K / ((double)wa * (double)wb));
+    }
 }
 
 }  // namespace qd

@@ -63,25 +63,21 @@ struct BruteLaunch {
     size_t part_bytes = 0;
 };
 BruteLaunch brute_launch_shape(uint64_t n, uint32_t nq_max, uint32_t k, uint32_t qt_force, uint32_t parts_force);
+// qmap (nullable; vector-ALU tiles only): query i is row qmap[i] of d_q and of the outputs.
 int brute_launch(const BruteLaunch &L, u64 *part, const uint64_t *d_db, uint64_t n, const uint64_t *d_q, uint32_t nq,
                  const uint32_t *nq_dev, uint32_t k, uint32_t *d_idx, int32_t *d_missed, int32_t *d_extra,
-                 float *d_dist, hipStream_t s, bool timed = true);
+                 float *d_dist, hipStream_t s, bool timed = true, const uint32_t *qmap = nullptr);
 
-// The matrix-core sequential search on a workspace the caller owns.  Level
-// l searches the first rows[l] rows; every level but the last is a
-// matrix-core pass whose candidate bounds come from the next level (a
-// sample), the last level is the row scan.  Smaller batches take the row
-// scan alone: its 16-query matrix tiles make one pass over the rows per tile,
-// while the 256 x 256 tiles here cost the same for 1 to 256 queries; the two
-// break even at about 160 queries.
-constexpr uint32_t kMfmaMinQueries = 160;
-constexpr uint64_t kMfmaMinRows = 1u << 16;
-constexpr int kMaxLevels = 4;
+// The matrix-core sequential search on a workspace the caller owns: a sample
+// pass for the candidate bounds, then the matrix pass (brute_mfma.hip).
+// The row scan's 16-query matrix tiles alone serve smaller batches and
+// databases (mfma_eligible).
 struct MfmaLayout {
-    std::vector<uint64_t> rows;
-    BruteLaunch base, fb[kMaxLevels];
-    size_t tpop = 0, qpop = 0, cnt = 0, cand = 0, redo = 0, ctr = 0, thr[kMaxLevels] = {}, smp[kMaxLevels] = {},
-           base_part = 0, gq = 0, fbr = 0, fb_part = 0, bytes = 0;
+    uint64_t n = 0;
+    uint64_t sample_tiles = 0, sample_step = 1;  // every sample_step-th row tile is sampled
+    std::vector<uint64_t> ends;                  // the row tile each part of the pass ends before
+    BruteLaunch fb;                              // the fallback for overflowed queries
+    size_t minima = 0, thr = 0, cnt = 0, cand = 0, redo = 0, n_redo = 0, fb_part = 0, bytes = 0;
 };
 // Whether a batch of nq queries over n rows takes the matrix cores.
 bool mfma_eligible(uint64_t n, uint32_t nq, uint32_t k);
