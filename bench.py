@@ -310,8 +310,8 @@ def main():
             f"learned start {k1['blocked_learned']['ms']:.2f} ms "
             f"({k1['blocked_learned']['blocks_per_query']:.0f} blocks/query)")
 
-    # small-batch scan: HBM-bound regime (one pass over the rows serves <= 16
-    # queries: the vector-ALU scan for 1-2 queries, the matrix query tile above)
+    # small-batch scan: HBM-bound regime (one pass over the rows: the vector-ALU
+    # scan for 1-2 queries, the 16-query matrix tile, the matrix pass above)
     hbm = {}
     for qn in (1, 8, 16):
         fn = lambda: qd.knn_bruteforce(dbt, qt[:qn], k)
@@ -320,10 +320,12 @@ def main():
         qd.profile_enable(True)
         for _ in range(5):
             fn()
-        (ms_v, cnt_v), (ms_m, cnt_m) = qd.profile_read("wh_scan_topk"), qd.profile_read("wh_scan_small_mfma")
+        times = {kn: qd.profile_read(t) for kn, t in (("scan_mfma_kernel", "wh_scan_mfma"),
+                                                      ("scan_small_mfma_kernel", "wh_scan_small_mfma"),
+                                                      ("scan_topk_kernel", "wh_scan_topk"))}
         qd.profile_enable(False)
-        kname = "scan_small_mfma_kernel" if cnt_m else "scan_topk_kernel"
-        avg = (ms_v + ms_m) / (cnt_v + cnt_m)
+        kname = next(kn for kn, (_, cnt) in times.items() if cnt)
+        avg = times[kname][0] / times[kname][1]
         gbs = (n * ROW_BYTES + qn * ROW_BYTES) / (avg * 1e-3) / 1e9
         hbm[f"q{qn}"] = {"kernel": kname, "scan_ms": avg, "GB_s": gbs, "frac": gbs / HBM_PEAK_GBS}
         log(f"scan at {qn} queries ({kname}): {avg:.3f} ms, {gbs:.0f} GB/s ({gbs / HBM_PEAK_GBS:.1%} of HBM peak)")
