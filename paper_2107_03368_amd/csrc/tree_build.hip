@@ -26,6 +26,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <memory>
 #include <vector>
 
 #include "qd_device.h"
@@ -901,8 +902,8 @@ __global__ __launch_bounds__(kBlock) void big_scatter_kernel(const uint32_t *__r
                                                              const BigCut *__restrict__ cuts,
                                                              const uint32_t *__restrict__ nds,
                                                              const uint16_t *__restrict__ fr_pos,
-                                                             const uint32_t *__restrict__ doff) {
-    __shared__ uint32_t tally[kChunk / 64];
+                                                             const uint32_t *__restrict__ dcount) {
+    __shared__ uint32_t tally[kChunk / 64], part[kBlock / 64];
     const Item it = items[blockIdx.x];
     const uint64_t nb0 = nbegin[it.slot], begin = nb0 + it.first;
     const uint32_t limit = cuts[it.slot].limit, t = threadIdx.x, w = t >> 6, lane = t & 63;
@@ -914,9 +915,15 @@ __global__ __launch_bounds__(kBlock) void big_scatter_kernel(const uint32_t *__r
         dm[i] = ballot(r < it.count && fr_pos[begin + r] < limit);
         if (lane == 0) tally[i * 4 + w] = (uint32_t)__popcll(dm[i]);
     }
+    // dissimilar members of the node's earlier items, which come just before
+    // this one's (at most a few thousand)
+    uint32_t s = 0;
+    for (uint32_t i = t; i < it.first / kChunk; i += kBlock) s += dcount[blockIdx.x - it.first / kChunk + i];
+    s = wave_sum(s);
+    if (lane == 0) part[w] = s;
     __syncthreads();
     const uint32_t ns = ncount[it.slot] - nds[it.slot];
-    uint32_t before = doff[blockIdx.x], g = 0;
+    uint32_t before = part[0] + part[1] + part[2] + part[3], g = 0;
 #pragma unroll
     for (uint32_t i = 0; i < kPerThread; i++) {
         for (; g < i * 4 + w; g++) before += tally[g];
@@ -949,18 +956,17 @@ __device__ __forceinline__ void wave_min_max(uint32_t &mn, uint32_t &mx) {
     }
 }
 
-// One wave per leaf: OR / AND over its rows of the leaf-ordered copy, and
-// the popcount range of the rows (when pmin is given).
+// One wave per node, for the leaves: OR / AND over a leaf's rows of the
+// leaf-ordered copy, and the popcount range of the rows (when pmin is given).
 __global__ __launch_bounds__(kBlock) void leaf_images_kernel(const uint4 *__restrict__ sorted,
-                                                             const uint32_t *__restrict__ leaf_ids, uint32_t n_leaves,
+                                                             const int32_t *__restrict__ child, uint32_t n_nodes,
                                                              const uint32_t *__restrict__ begin,
                                                              const uint32_t *__restrict__ count,
                                                              uint4 *__restrict__ or_img, uint4 *__restrict__ and_img,
                                                              const uint16_t *__restrict__ pop,
                                                              uint16_t *__restrict__ pmin, uint16_t *__restrict__ pmax) {
-    const uint32_t w = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
-    if (w >= n_leaves) return;
-    const uint32_t node = leaf_ids[w];
+    const uint32_t node = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+    if (node >= n_nodes || child[2 * (uint64_t)node] >= 0) return;  // whole wave
     const int lane = threadIdx.x & 63;
     const uint32_t c = lane & 31, half = lane >> 5;
     const uint64_t b = begin[node];
@@ -994,26 +1000,39 @@ __global__ __launch_bounds__(kBlock) void leaf_images_kernel(const uint4 *__rest
     }
 }
 
-// Inner nodes of one level: images and popcount range combine the two
-// children's.
-__global__ __launch_bounds__(kBlock) void inner_images_kernel(const uint32_t *__restrict__ ids, uint32_t n_ids,
+// One level's nodes first .. first + n - 1: their depth, their children's
+// parent, and the inner ones' images and popcount range, which combine the
+// two children's.
+__global__ __launch_bounds__(kBlock) void inner_images_kernel(uint32_t first, uint32_t n, uint8_t level,
                                                               const int32_t *__restrict__ child,
                                                               uint4 *__restrict__ or_img, uint4 *__restrict__ and_img,
-                                                              uint16_t *__restrict__ pmin, uint16_t *__restrict__ pmax) {
+                                                              uint16_t *__restrict__ pmin, uint16_t *__restrict__ pmax,
+                                                              int32_t *__restrict__ parent,
+                                                              uint8_t *__restrict__ depth) {
     const uint64_t e = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (e >= (uint64_t)n_ids * 32) return;
-    const uint32_t node = ids[e >> 5], c = e & 31;
+    if (e >= (uint64_t)n * 32) return;
+    const uint32_t c = e & 31;
+    const uint64_t node = first + (e >> 5);
     const int32_t s = child[2 * node], d = child[2 * node + 1];
+    if (c == 0) depth[node] = level;
+    if (node == 0 && c == 1) parent[0] = -1;
+    if (s < 0) return;
     const uint4 x = or_img[(uint64_t)s * 32 + c], y = or_img[(uint64_t)d * 32 + c];
-    or_img[(uint64_t)node * 32 + c] = make_uint4(x.x | y.x, x.y | y.y, x.z | y.z, x.w | y.w);
+    or_img[node * 32 + c] = make_uint4(x.x | y.x, x.y | y.y, x.z | y.z, x.w | y.w);
     if (and_img) {
         const uint4 p = and_img[(uint64_t)s * 32 + c], r = and_img[(uint64_t)d * 32 + c];
-        and_img[(uint64_t)node * 32 + c] = make_uint4(p.x & r.x, p.y & r.y, p.z & r.z, p.w & r.w);
+        and_img[node * 32 + c] = make_uint4(p.x & r.x, p.y & r.y, p.z & r.z, p.w & r.w);
     }
+    if (c == 0) parent[s] = parent[d] = (int32_t)node;
     if (pmin && c == 0) {
         pmin[node] = pmin[s] < pmin[d] ? pmin[s] : pmin[d];
         pmax[node] = pmax[s] > pmax[d] ? pmax[s] : pmax[d];
     }
+}
+
+__global__ __launch_bounds__(kBlock) void identity_kernel(uint32_t *__restrict__ perm, uint64_t n) {
+    for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (uint64_t)gridDim.x * kBlock)
+        perm[i] = (uint32_t)i;
 }
 
 __global__ __launch_bounds__(kBlock) void invert_perm_kernel(const uint32_t *__restrict__ perm, uint64_t n,
@@ -1021,15 +1040,6 @@ __global__ __launch_bounds__(kBlock) void invert_perm_kernel(const uint32_t *__r
     for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (uint64_t)gridDim.x * kBlock)
         iperm[perm[i]] = (uint32_t)i;
 }
-
-template <class T>
-struct DevBuf {
-    T *p = nullptr;
-    ~DevBuf() {
-        if (p) (void)hipFree(p);
-    }
-    hipError_t alloc(size_t n) { return hipMalloc((void **)&p, std::max<size_t>(n, 1) * sizeof(T)); }
-};
 
 }  // namespace
 
@@ -1057,25 +1067,45 @@ int tree_build_impl(const uint64_t *d_db, uint64_t n, const qd_build_params *par
     hipStream_t s = (hipStream_t)stream;
     const uint4 *db4 = reinterpret_cast<const uint4 *>(d_db);
 
-    DevBuf<uint32_t> perm_a, perm_b;
-    DevBuf<uint16_t> fr_pos;
-    QD_HIP_CHECK(perm_a.alloc(n));
-    QD_HIP_CHECK(perm_b.alloc(n));
-    QD_HIP_CHECK(fr_pos.alloc(n));
-
-    // identity permutation
-    {
-        std::vector<uint32_t> id(n);
-        for (uint64_t i = 0; i < n; i++) id[i] = (uint32_t)i;
-        QD_HIP_CHECK(hipMemcpyAsync(perm_a.p, id.data(), n * sizeof(uint32_t), hipMemcpyHostToDevice, s));
-        QD_HIP_CHECK(hipStreamSynchronize(s));
-    }
+    // Scratch for all levels, in the memory of the leaf-ordered rows, which are
+    // written last: a level's split nodes are disjoint and hold more than
+    // max_leaf rows each (large ones more than kSmall), which bounds the lists
+    // and the large nodes' tables to some 50 bytes per row.  Buffers of each
+    // level's own (ten allocations and frees, each a wait), id lists for the
+    // images and an uploaded identity order left the GPU idle for 4.5 ms of a
+    // build of 1M rows that now takes 8; one allocation and free still took 0.6.
+    const uint64_t max_split = n / (max_leaf + 1) + 1, max_big = n / (kSmall + 1) + 1, max_items = n / kChunk + max_big;
+    size_t bytes = 0;
+    auto take = [&](size_t b) {
+        const size_t at = bytes;
+        bytes += (b + 255) & ~(size_t)255;
+        return at;
+    };
+    const size_t o_pa = take(n * 4), o_pb = take(n * 4), o_fr = take(n * 2), o_begin = take(max_split * 8),
+                 o_count = take(max_split * 4), o_nd = take(max_split * 4), o_items = take(max_items * sizeof(Item)),
+                 o_dc = take(max_items * 4), o_gc = take(max_big * QD_BITS * 4), o_gh = take(max_big * QD_BITS * 4),
+                 o_rank = take(max_big * QD_BITS * 2), o_mask = take(max_big * kMaskWords * 4),
+                 o_bh = take(max_big * kBands * 4), o_cuts = take(max_big * sizeof(BigCut));
+    std::unique_ptr<qd_tree_s, void (*)(qd_tree_s *)> tree(new qd_tree_s(), tree_release);
+    QD_HIP_CHECK(hipMalloc((void **)&tree->d_sorted, std::max<size_t>(n * 512, bytes)));
+    QD_HIP_CHECK(hipMalloc((void **)&tree->d_perm, n * 4));
+    char *const scratch = (char *)tree->d_sorted;
+    uint64_t *const d_begin = (uint64_t *)(scratch + o_begin);
+    uint32_t *const d_count = (uint32_t *)(scratch + o_count), *const d_nd = (uint32_t *)(scratch + o_nd),
+             *const dc = (uint32_t *)(scratch + o_dc), *const gc = (uint32_t *)(scratch + o_gc),
+             *const gh = (uint32_t *)(scratch + o_gh), *const mask = (uint32_t *)(scratch + o_mask),
+             *const bh = (uint32_t *)(scratch + o_bh);
+    uint16_t *const fr_pos = (uint16_t *)(scratch + o_fr), *const rank = (uint16_t *)(scratch + o_rank);
+    Item *const d_items = (Item *)(scratch + o_items);
+    BigCut *const cuts = (BigCut *)(scratch + o_cuts);
+    uint32_t *pin = (uint32_t *)(scratch + o_pa), *pout = (uint32_t *)(scratch + o_pb);
+    hipLaunchKernelGGL(identity_kernel, dim3((uint32_t)std::min<uint64_t>((n + kBlock - 1) / kBlock, 4096)),
+                       dim3(kBlock), 0, s, pin, n);
 
     std::vector<uint64_t> begin{0};
     std::vector<uint32_t> count{(uint32_t)n};
     std::vector<int32_t> child{-1, -1};
     std::vector<uint32_t> level_first{0};
-    uint32_t *pin = perm_a.p, *pout = perm_b.p;
     uint64_t lv0 = 0, lv1 = 1;
     while (lv0 < lv1) {
         if (abort_requested()) {  // between levels: nothing of this level is queued yet
@@ -1105,94 +1135,61 @@ int tree_build_impl(const uint64_t *d_db, uint64_t n, const qd_build_params *par
             hb[small.size() + i] = begin[big[i]];
             hc[small.size() + i] = count[big[i]];
         }
-        DevBuf<uint64_t> db_begin;
-        DevBuf<uint32_t> db_count, db_nd;
-        QD_HIP_CHECK(db_begin.alloc(nsplit));
-        QD_HIP_CHECK(db_count.alloc(nsplit));
-        QD_HIP_CHECK(db_nd.alloc(nsplit));
-        QD_HIP_CHECK(hipMemcpyAsync(db_begin.p, hb.data(), nsplit * 8, hipMemcpyHostToDevice, s));
-        QD_HIP_CHECK(hipMemcpyAsync(db_count.p, hc.data(), nsplit * 4, hipMemcpyHostToDevice, s));
+        QD_HIP_CHECK(hipMemcpyAsync(d_begin, hb.data(), nsplit * 8, hipMemcpyHostToDevice, s));
+        QD_HIP_CHECK(hipMemcpyAsync(d_count, hc.data(), nsplit * 4, hipMemcpyHostToDevice, s));
         auto split = [&](auto kernel, uint32_t threads, size_t first, size_t last) {
             if (first < last)
                 hipLaunchKernelGGL(kernel, dim3((uint32_t)(last - first)), dim3(threads), 0, s, db4, pin, pout,
-                                   db_begin.p + first, db_count.p + first, db_nd.p + first);
+                                   d_begin + first, d_count + first, d_nd + first);
         };
         split(split_small_kernel<4, kKept, true>, 256, 0, nkept);
         split(split_small_kernel<4, kMid, false>, 256, nkept, nmid);
         split(split_small_kernel<8, kSmall, false>, 512, nmid, small.size());
         QD_HIP_CHECK(hipGetLastError());
+        std::vector<Item> items;  // (the uploads' host copies live until the wait below)
         if (!big.empty()) {
             const size_t nbig = big.size();
-            std::vector<Item> items;
-            std::vector<uint32_t> item_node;
             for (size_t i = 0; i < nbig; i++) {
                 const uint32_t m = count[big[i]];
                 for (uint32_t f = 0; f < m; f += kChunk) items.push_back({(uint32_t)i, f, std::min(kChunk, m - f), 0});
             }
             const size_t ni = items.size();
-            DevBuf<Item> it_dev;
-            DevBuf<uint32_t> gc, gh, bh, dc, dof, mask;
-            DevBuf<uint16_t> rank;
-            DevBuf<BigCut> cu;
-            QD_HIP_CHECK(it_dev.alloc(ni));
-            QD_HIP_CHECK(gc.alloc(nbig * 4096));
-            QD_HIP_CHECK(gh.alloc(nbig * 4096));
-            QD_HIP_CHECK(bh.alloc(nbig * kBands));
-            QD_HIP_CHECK(dc.alloc(ni));
-            QD_HIP_CHECK(dof.alloc(ni));
-            QD_HIP_CHECK(cu.alloc(nbig));
-            QD_HIP_CHECK(rank.alloc(nbig * 4096));
-            QD_HIP_CHECK(mask.alloc(nbig * kMaskWords));
-            QD_HIP_CHECK(hipMemcpyAsync(it_dev.p, items.data(), ni * sizeof(Item), hipMemcpyHostToDevice, s));
-            QD_HIP_CHECK(hipMemsetAsync(gc.p, 0, nbig * 4096 * 4, s));
-            const uint64_t *bbeg = db_begin.p + small.size();
-            const uint32_t *bcnt = db_count.p + small.size();
-            uint32_t *bnd_out = db_nd.p + small.size();
-            hipLaunchKernelGGL(big_count_kernel, dim3((uint32_t)ni), dim3(kBlock), 0, s, db4, pin, bbeg, it_dev.p, gc.p);
+            QD_HIP_CHECK(hipMemcpyAsync(d_items, items.data(), ni * sizeof(Item), hipMemcpyHostToDevice, s));
+            QD_HIP_CHECK(hipMemsetAsync(gc, 0, nbig * QD_BITS * 4, s));
+            const uint64_t *bbeg = d_begin + small.size();
+            const uint32_t *bcnt = d_count + small.size();
+            uint32_t *bnd_out = d_nd + small.size();
+            hipLaunchKernelGGL(big_count_kernel, dim3((uint32_t)ni), dim3(kBlock), 0, s, db4, pin, bbeg, d_items,
+                               gc);
             // with the least popular bits; then, where they reach too few
             // members, with all bits (elsewhere these kernels end at once)
             for (uint32_t again = 0; again < 2; again++) {
-                hipLaunchKernelGGL(big_band_kernel, dim3((uint32_t)nbig), dim3(1024), 0, s, gc.p, bcnt,
-                                   again ? 0u : kLambdaBig, mask.p, bh.p, cu.p);
-                hipLaunchKernelGGL(big_first_kernel, dim3((uint32_t)ni), dim3(kBlock), 0, s, db4, pin, bbeg, it_dev.p,
-                                   mask.p, cu.p, again, fr_pos.p, bh.p);
-                hipLaunchKernelGGL(big_rank_kernel, dim3((uint32_t)nbig), dim3(1024), 0, s, gc.p, bcnt, mask.p, bh.p,
-                                   again, rank.p, gh.p, cu.p, bnd_out);
-                hipLaunchKernelGGL(big_refine_kernel, dim3((uint32_t)ni), dim3(kBlock), 0, s, db4, pin, bbeg, it_dev.p,
-                                   rank.p, mask.p, cu.p, again, fr_pos.p, gh.p);
-                hipLaunchKernelGGL(big_cut_kernel, dim3((uint32_t)nbig), dim3(kBlock), 0, s, gh.p, bcnt, again, cu.p,
+                hipLaunchKernelGGL(big_band_kernel, dim3((uint32_t)nbig), dim3(1024), 0, s, gc, bcnt,
+                                   again ? 0u : kLambdaBig, mask, bh, cuts);
+                hipLaunchKernelGGL(big_first_kernel, dim3((uint32_t)ni), dim3(kBlock), 0, s, db4, pin, bbeg, d_items,
+                                   mask, cuts, again, fr_pos, bh);
+                hipLaunchKernelGGL(big_rank_kernel, dim3((uint32_t)nbig), dim3(1024), 0, s, gc, bcnt, mask, bh,
+                                   again, rank, gh, cuts, bnd_out);
+                hipLaunchKernelGGL(big_refine_kernel, dim3((uint32_t)ni), dim3(kBlock), 0, s, db4, pin, bbeg, d_items,
+                                   rank, mask, cuts, again, fr_pos, gh);
+                hipLaunchKernelGGL(big_cut_kernel, dim3((uint32_t)nbig), dim3(kBlock), 0, s, gh, bcnt, again, cuts,
                                    bnd_out);
             }
-            hipLaunchKernelGGL(big_dcount_kernel, dim3((uint32_t)ni), dim3(kBlock), 0, s, bbeg, it_dev.p, cu.p,
-                               fr_pos.p, dc.p);
-            QD_HIP_CHECK(hipGetLastError());
-            std::vector<uint32_t> hdc(ni), hdoff(ni);
-            QD_HIP_CHECK(hipMemcpyAsync(hdc.data(), dc.p, ni * 4, hipMemcpyDeviceToHost, s));
-            QD_HIP_CHECK(hipStreamSynchronize(s));
-            uint32_t run = 0;
-            for (size_t i = 0; i < ni; i++) {
-                if (i == 0 || items[i].slot != items[i - 1].slot) run = 0;
-                hdoff[i] = run;
-                run += hdc[i];
-            }
-            QD_HIP_CHECK(hipMemcpyAsync(dof.p, hdoff.data(), ni * 4, hipMemcpyHostToDevice, s));
+            hipLaunchKernelGGL(big_dcount_kernel, dim3((uint32_t)ni), dim3(kBlock), 0, s, bbeg, d_items, cuts,
+                               fr_pos, dc);
             hipLaunchKernelGGL(big_scatter_kernel, dim3((uint32_t)ni), dim3(kBlock), 0, s, pin, pout, bbeg, bcnt,
-                               it_dev.p, cu.p, bnd_out, fr_pos.p, dof.p);
+                               d_items, cuts, bnd_out, fr_pos, dc);
             QD_HIP_CHECK(hipGetLastError());
-            QD_HIP_CHECK(hipStreamSynchronize(s));
         }
         std::vector<uint32_t> hnd(nsplit);
-        QD_HIP_CHECK(hipMemcpyAsync(hnd.data(), db_nd.p, nsplit * 4, hipMemcpyDeviceToHost, s));
+        QD_HIP_CHECK(hipMemcpyAsync(hnd.data(), d_nd, nsplit * 4, hipMemcpyDeviceToHost, s));
         QD_HIP_CHECK(hipStreamSynchronize(s));
         // children in breadth-first order: parents in id order, similar first
-        std::vector<std::pair<uint32_t, uint32_t>> split_nd;  // (node, nd)
-        split_nd.reserve(nsplit);
-        for (size_t i = 0; i < small.size(); i++) split_nd.push_back({small[i], hnd[i]});
-        for (size_t i = 0; i < big.size(); i++) split_nd.push_back({big[i], hnd[small.size() + i]});
-        std::sort(split_nd.begin(), split_nd.end());
+        std::vector<uint32_t> nd_of(lv1 - lv0, 0);
+        for (size_t i = 0; i < nsplit; i++) nd_of[(i < small.size() ? small[i] : big[i - small.size()]) - lv0] = hnd[i];
         const uint64_t next0 = begin.size();
-        for (auto &pn : split_nd) {
-            const uint32_t node = pn.first, nd = pn.second, m = count[node];
+        for (uint64_t node = lv0; node < lv1; node++) {
+            const uint32_t nd = nd_of[node - lv0], m = count[node];
             if (nd == 0 || nd >= m) continue;  // no split possible: the node stays a leaf
             const int32_t sid = (int32_t)begin.size();
             begin.push_back(begin[node]);
@@ -1215,15 +1212,11 @@ int tree_build_impl(const uint64_t *d_db, uint64_t n, const qd_build_params *par
 
     // The final permutation is in `pin`.
     const uint64_t nn = begin.size();
-    qd_tree_s *t = new qd_tree_s();
+    qd_tree_s *t = tree.release();
     t->n = n;
     t->n_nodes = nn;
     t->max_leaf = max_leaf;
     t->has_and = want_and;
-    if (hipMalloc((void **)&t->d_sorted, n * 512) != hipSuccess || hipMalloc((void **)&t->d_perm, n * 4) != hipSuccess) {
-        tree_release(t);
-        return fail(QD_ERR_OOM, "tree allocation failed");
-    }
     if (hipMemcpyAsync(t->d_perm, pin, n * 4, hipMemcpyDeviceToDevice, s) != hipSuccess) {
         tree_release(t);
         return fail(QD_ERR_DEVICE, "tree upload failed");
@@ -1257,30 +1250,32 @@ int tree_finish(qd_tree_s *t, const std::vector<int32_t> &child, const std::vect
         (want_pop && (hipMalloc((void **)&t->d_pmin, nn * 2) != hipSuccess ||
                       hipMalloc((void **)&t->d_pmax, nn * 2) != hipSuccess)))
         return cleanup(fail(QD_ERR_OOM, "tree allocation failed"));
-    std::vector<uint32_t> leaf_ids;
-    for (uint64_t i = 0; i < nn; i++)
-        if (child[2 * i] < 0) leaf_ids.push_back((uint32_t)i);
-    const uint32_t n_leaves = (uint32_t)leaf_ids.size();
+    if (hipMemcpyAsync(t->d_child, child.data(), nn * 8, hipMemcpyHostToDevice, s) != hipSuccess ||
+        hipMemcpyAsync(t->d_begin, begin.data(), nn * 4, hipMemcpyHostToDevice, s) != hipSuccess ||
+        hipMemcpyAsync(t->d_count, count.data(), nn * 4, hipMemcpyHostToDevice, s) != hipSuccess)
+        return cleanup(fail(QD_ERR_DEVICE, "tree upload failed"));
+    {
+        const int rc = qd_popcount_rows(t->d_sorted, n, t->d_pop, s);  // leaf-order rows
+        if (rc != QD_OK) return cleanup(rc);
+    }
+    hipLaunchKernelGGL(leaf_images_kernel, dim3((uint32_t)((nn + 3) / 4)), dim3(kBlock), 0, s,
+                       reinterpret_cast<const uint4 *>(t->d_sorted), t->d_child, (uint32_t)nn, t->d_begin, t->d_count,
+                       reinterpret_cast<uint4 *>(t->d_or), reinterpret_cast<uint4 *>(t->d_and), t->d_pop, t->d_pmin,
+                       t->d_pmax);
+    uint64_t n_leaves = 0;
+    for (uint64_t i = 0; i < nn; i++) n_leaves += child[2 * i] < 0;
     t->n_leaves = n_leaves;
     // breadth-first numbering: a level's nodes are consecutive, children after parents
-    std::vector<int32_t> parent(nn, -1);
     std::vector<uint32_t> level(nn, 0);
-    std::vector<uint8_t> depth(nn, 0);
     for (uint64_t i = 0; i < nn; i++)
-        if (child[2 * i] >= 0) {
-            parent[child[2 * i]] = parent[child[2 * i + 1]] = (int32_t)i;
-            level[child[2 * i]] = level[child[2 * i + 1]] = level[i] + 1;
-        }
+        if (child[2 * i] >= 0) level[child[2 * i]] = level[child[2 * i + 1]] = level[i] + 1;
     std::vector<uint32_t> level_first{0};
     for (uint64_t i = 1; i < nn; i++)
         if (level[i] != level[i - 1]) level_first.push_back((uint32_t)i);
     level_first.push_back((uint32_t)nn);
     t->depth = (uint32_t)level_first.size() - 1;
     t->level_max.assign(t->depth, 0);
-    for (uint64_t i = 0; i < nn; i++) {
-        depth[i] = (uint8_t)std::min<uint32_t>(255, level[i]);
-        t->level_max[level[i]] = std::max(t->level_max[level[i]], count[i]);
-    }
+    for (uint64_t i = 0; i < nn; i++) t->level_max[level[i]] = std::max(t->level_max[level[i]], count[i]);
     // The per-query search split into n subtree searches: position p (its
     // log2(n) bits from the most significant, 0 = the similar child) is the
     // node reached from the root along p's bits; a leaf met on the way is the
@@ -1313,39 +1308,15 @@ int tree_finish(qd_tree_s *t, const std::vector<int32_t> &child, const std::vect
     }
     if (hipMalloc((void **)&t->d_split_roots, 31 * 4) != hipSuccess)
         return cleanup(fail(QD_ERR_OOM, "tree allocation failed"));
-    if (hipMemcpyAsync(t->d_split_roots, split_roots.data(), 31 * 4, hipMemcpyHostToDevice, s) != hipSuccess ||
-        hipMemcpyAsync(t->d_parent, parent.data(), nn * 4, hipMemcpyHostToDevice, s) != hipSuccess ||
-        hipMemcpyAsync(t->d_depth, depth.data(), nn, hipMemcpyHostToDevice, s) != hipSuccess ||
-        hipMemcpyAsync(t->d_child, child.data(), nn * 8, hipMemcpyHostToDevice, s) != hipSuccess ||
-        hipMemcpyAsync(t->d_begin, begin.data(), nn * 4, hipMemcpyHostToDevice, s) != hipSuccess ||
-        hipMemcpyAsync(t->d_count, count.data(), nn * 4, hipMemcpyHostToDevice, s) != hipSuccess)
+    if (hipMemcpyAsync(t->d_split_roots, split_roots.data(), 31 * 4, hipMemcpyHostToDevice, s) != hipSuccess)
         return cleanup(fail(QD_ERR_DEVICE, "tree upload failed"));
-    DevBuf<uint32_t> lid;
-    if (lid.alloc(std::max<uint64_t>(n_leaves, nn)) != hipSuccess) return cleanup(fail(QD_ERR_OOM, "alloc"));
-    if (hipMemcpyAsync(lid.p, leaf_ids.data(), n_leaves * 4, hipMemcpyHostToDevice, s) != hipSuccess)
-        return cleanup(fail(QD_ERR_DEVICE, "upload"));
-    {
-        const int rc = qd_popcount_rows(t->d_sorted, n, t->d_pop, s);  // leaf-order rows
-        if (rc != QD_OK) return cleanup(rc);
-    }
-    hipLaunchKernelGGL(leaf_images_kernel, dim3((n_leaves + 3) / 4), dim3(kBlock), 0, s,
-                       reinterpret_cast<const uint4 *>(t->d_sorted), lid.p, n_leaves, t->d_begin, t->d_count,
-                       reinterpret_cast<uint4 *>(t->d_or), reinterpret_cast<uint4 *>(t->d_and), t->d_pop, t->d_pmin,
-                       t->d_pmax);
-    if (hipStreamSynchronize(s) != hipSuccess) return cleanup(fail(QD_ERR_DEVICE, "leaf images"));
     // inner nodes, deepest level first
     for (int L = (int)level_first.size() - 2; L >= 0; L--) {
-        std::vector<uint32_t> inner;
-        for (uint32_t i = level_first[L]; i < level_first[L + 1]; i++)
-            if (child[2 * i] >= 0) inner.push_back(i);
-        if (inner.empty()) continue;
-        if (hipMemcpyAsync(lid.p, inner.data(), inner.size() * 4, hipMemcpyHostToDevice, s) != hipSuccess)
-            return cleanup(fail(QD_ERR_DEVICE, "upload"));
-        const uint64_t work = (uint64_t)inner.size() * 32;
-        hipLaunchKernelGGL(inner_images_kernel, dim3((uint32_t)((work + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
-                           lid.p, (uint32_t)inner.size(), t->d_child, reinterpret_cast<uint4 *>(t->d_or),
-                           reinterpret_cast<uint4 *>(t->d_and), t->d_pmin, t->d_pmax);
-        if (hipStreamSynchronize(s) != hipSuccess) return cleanup(fail(QD_ERR_DEVICE, "inner images"));
+        const uint32_t first = level_first[L], m = level_first[L + 1] - first;
+        hipLaunchKernelGGL(inner_images_kernel, dim3((uint32_t)(((uint64_t)m * 32 + kBlock - 1) / kBlock)),
+                           dim3(kBlock), 0, s, first, m, (uint8_t)std::min(255, L), t->d_child,
+                           reinterpret_cast<uint4 *>(t->d_or), reinterpret_cast<uint4 *>(t->d_and), t->d_pmin,
+                           t->d_pmax, t->d_parent, t->d_depth);
     }
     hipLaunchKernelGGL(invert_perm_kernel, dim3((uint32_t)std::min<uint64_t>((n + kBlock - 1) / kBlock, 65535)),
                        dim3(kBlock), 0, s, t->d_perm, n, t->d_iperm);
