@@ -308,8 +308,8 @@ typedef struct {
        bound-ordered rounds, as with a model.  Results are identical. */
     uint32_t round1_start;
     /* QD_ORDER_BEST_FIRST / QD_ORDER_DEPTH_FIRST: concurrent searches per
-       query (0 = default 16; 1 = one wave searches the whole tree; else a
-       power of two up to 16).  With n > 1 the tree is cut log2(n) levels
+       query (0 = default: 16, or up to 64 for small batches and large trees;
+       1 = one wave searches the whole tree; else a power of two up to 16).  With n > 1 the tree is cut log2(n) levels
        below the root, each subtree is searched in the same order by its own
        wave, the searches of a query prune with the least k-th key any of them
        has reached (shared through device memory), and their k-lists are

@@ -12,6 +12,7 @@ namespace qd {
 struct TreeLaunch {
     uint64_t blocks = 0, slots = 0, pool_chunks = 0;
     uint32_t split = 1;  // concurrent subtree searches per query
+    int groups = 4;      // groups of 8 leaf rows loaded at once
     size_t head = 0, prev_bytes = 0, pool_bytes = 0;
     size_t split_bytes = 0;  // after the pool: the searches' lists and statistics, merged into the results
     size_t total() const { return head + prev_bytes + pool_bytes + split_bytes; }

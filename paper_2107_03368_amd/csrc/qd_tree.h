@@ -5,6 +5,11 @@
 
 #include "qd_internal.h"
 
+namespace qd {
+constexpr uint32_t kCutLevels = 6;             // deepest cut of a per-query search
+constexpr uint32_t kMaxCut = 1u << kCutLevels;  // its subtree searches
+}  // namespace qd
+
 struct qd_tree_s {
     int device = 0;
     uint64_t n = 0;         // database rows
@@ -30,11 +35,11 @@ struct qd_tree_s {
     uint64_t *d_blk = nullptr;     // n_blk x 64 words: OR image of each block's rows
     uint16_t *d_bpop = nullptr;    // n_blk x 2: smallest, largest row popcount of each block (null: plain)
     std::vector<uint32_t> level_max;  // host: most rows of any node of each level (root level 0)
-    // The per-query search split into n = 2^e subtree searches (e = 0..4):
-    // d_split_roots[n - 1 .. 2n - 2] are the n subtree roots (-1: none) and
+    // The per-query search split into n = 2^e subtree searches (e = 0 ..
+    // kCutLevels): d_split_roots[n - 1 .. 2n - 2] are the n subtree roots (-1: none) and
     // split_nodes[e] the most nodes any of them holds.
-    int32_t *d_split_roots = nullptr;  // 31 entries
-    uint64_t split_nodes[5] = {};
+    int32_t *d_split_roots = nullptr;  // 2 * kMaxCut - 1 entries
+    uint64_t split_nodes[qd::kCutLevels + 1] = {};
 };
 
 namespace qd {

@@ -1282,12 +1282,12 @@ int tree_finish(qd_tree_s *t, const std::vector<int32_t> &child, const std::vect
     // subtree of the first position below it, the other positions below it
     // are empty.  With the nodes under each node (children come after their
     // parents), the most nodes of any subtree bounds one search's queue.
-    std::vector<int32_t> split_roots(31, -1);
+    std::vector<int32_t> split_roots(2 * kMaxCut - 1, -1);
     {
         std::vector<uint32_t> under(nn, 1);
         for (uint64_t i = nn; i-- > 0;)
             if (child[2 * i] >= 0) under[i] = 1 + under[child[2 * i]] + under[child[2 * i + 1]];
-        for (uint32_t e = 0; e < 5; e++) {
+        for (uint32_t e = 0; e <= kCutLevels; e++) {
             const uint32_t ns = 1u << e;
             uint64_t most = 0;
             for (uint32_t p = 0; p < ns; p++) {
@@ -1306,9 +1306,9 @@ int tree_finish(qd_tree_s *t, const std::vector<int32_t> &child, const std::vect
             t->split_nodes[e] = most;
         }
     }
-    if (hipMalloc((void **)&t->d_split_roots, 31 * 4) != hipSuccess)
+    if (hipMalloc((void **)&t->d_split_roots, split_roots.size() * 4) != hipSuccess)
         return cleanup(fail(QD_ERR_OOM, "tree allocation failed"));
-    if (hipMemcpyAsync(t->d_split_roots, split_roots.data(), 31 * 4, hipMemcpyHostToDevice, s) != hipSuccess)
+    if (hipMemcpyAsync(t->d_split_roots, split_roots.data(), split_roots.size() * 4, hipMemcpyHostToDevice, s) != hipSuccess)
         return cleanup(fail(QD_ERR_DEVICE, "tree upload failed"));
     // inner nodes, deepest level first
     for (int L = (int)level_first.size() - 2; L >= 0; L--) {

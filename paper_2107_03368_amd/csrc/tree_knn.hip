@@ -1,6 +1,5 @@
 // Dissimilarity Tree k-NN search (Section 4.2, Listing 2) as a persistent
-// kernel: each wave takes queries from a global counter until none are left,
-// and searches one query at a time.
+// kernel: each wave takes searches from global counters until none are left.
 //
 // Node bound (minWHDist): a query 1-bit that is 0 in a node's sum image is a
 // type A error for every row under the node, so with
@@ -18,7 +17,7 @@
 //  best-first (the paper's priority queue): a bucket queue on
 //    floor(Kb / 2wB) (2 levels of A_lb per bucket for the sum-image bound
 //    alone: the buckets' state then takes half the LDS, so 16 waves fit on a
-//    CU instead of 8; registers hold 12); the search stops once the popped
+//    CU instead of 8); the search stops once the popped
 //    bucket's lower end exceeds the k-th key, and a popped node above the key
 //    is skipped, so the result stays exact.  Each bucket is a stack of
 //    16-entry chunks in the wave's global workspace, its (chunk, fill) word in
@@ -32,7 +31,7 @@
 // Both orders return exactly the sequential-search result.
 //
 // Intra-query split: one query's search can run as n concurrent tasks (n a
-// power of two up to 16), each searching one subtree of the tree cut at
+// power of two; up to 16 for callers, up to 64 by default), each searching one subtree of the tree cut at
 // depth log2(n) (a leaf above that depth is one task's whole subtree) in the
 // same order.  The subtrees partition the rows, so the query's k nearest are
 // the k smallest of the tasks' k-lists (merge_kernel).  Every task prunes
@@ -84,8 +83,14 @@ struct Scores {
     uint32_t n_scored;    // nodes 0 .. n_scored-1 carry a score
 };
 
-constexpr uint32_t kMaxSplit = 16;
-constexpr uint32_t kDefaultSplit = 16;
+// Smaller trees deal their tasks query by query from one counter: their rows
+// are in the caches in any order, and a query's searches that run together
+// share its k-th key early.  Dealt by subtree on each XCD instead, depth-first,
+// k = 10: 10k rows 509 queries 0.62 -> 0.77 ms, 2,048 1.86 -> 1.99; 30k rows
+// 0.88 -> 0.86 and 2.81 -> 2.15; 60k rows 1.53 -> 1.19 and 5.17 -> 3.17.
+constexpr uint64_t kByQueryRows = 20000;
+constexpr uint32_t kMaxSplit = 16;        // a caller's choice
+constexpr uint32_t kFineSplit = kMaxCut;  // the library's (one list per lane in merge_kernel)
 // The tasks' area, one allocation for nq_max queries of n tasks each:
 // subtree roots (n int32, -1: an empty task) | per query, the least k-th key
 // its tasks have published | per task, its k-list (k keys) | their payloads
@@ -108,13 +113,18 @@ __host__ __device__ inline SplitLayout split_layout(uint64_t nq_max, uint32_t n,
 
 __device__ __forceinline__ uint32_t sum32(uint32_t v) { return sum32_half(v); }
 
-template <bool kBest>
-__global__ __launch_bounds__(kBlock, kBest ? 3 : 4) void tree_knn_kernel(TreeView T, const uint4 *__restrict__ q, uint32_t nq,
+// Bound by reading the visited leaves' rows (22 on average) and by the latency
+// of one visit after another.  A leaf's rows are loaded in groups of 8, kGroups
+// of them before any is reduced.  4 make a leaf one round trip; beside the
+// best-first queue they leave registers for 12 waves per CU, 2 for 16, which is
+// better once there are more searches than waves (tree_launch).
+template <bool kBest, int kGroups>
+__global__ __launch_bounds__(kBlock, kBest && kGroups == 4 ? 3 : 4) void tree_knn_kernel(TreeView T, const uint4 *__restrict__ q, uint32_t nq,
                                                           uint32_t k, uint32_t *__restrict__ next_task,
                                                           u64 *__restrict__ pool, uint32_t *__restrict__ chunk_prev,
                                                           uint64_t pool_chunks, Scores S, uint32_t *trace,
                                                           uint32_t n_traced, const uint32_t *__restrict__ nq_dev,
-                                                          char *__restrict__ sw, uint32_t nsplit) {
+                                                          char *__restrict__ sw, uint32_t nsplit, uint32_t n_homes) {
     __shared__ uint32_t bstate_all[kBest ? kWaves * kBuckets : 1];
     __shared__ u64 stack_all[kBest ? kWaves * kHot : kWaves * kMaxStack];  // best-first: the hot bucket's entries
     __shared__ u64 sinfo_all[kBest ? kWaves * kHot : kWaves * kMaxStack];  // the entries' node info
@@ -133,19 +143,33 @@ __global__ __launch_bounds__(kBlock, kBest ? 3 : 4) void tree_knn_kernel(TreeVie
     const uint32_t nq_max = nq;  // the tasks' area is laid out for nq queries
     if (nq_dev) nq = readfirst(*nq_dev);  // size given on the device (captured graphs)
     const uint32_t tsh = (uint32_t)__builtin_ctz(nsplit);  // tasks per query = 1 << tsh
-    const uint64_t ntasks = (uint64_t)nq << tsh;
     uint32_t *const kshared = reinterpret_cast<uint32_t *>(sw + 256);  // the layout's first offset
 
+    // The tasks are dealt by subtree (n_homes 8): those of subtree s belong to
+    // XCD s % 8 (blocks go to the XCDs in turn), whose waves take all queries of
+    // one subtree, then of the next, and then help the other XCDs.  The rows that
+    // run together are then a few subtrees', which caches hold: 64 subtrees of
+    // 1M rows are 8 MB each, 11.8 ms for 509 queries; 12.6 with the subtrees in
+    // the same order on every XCD, 13.4 with one counter.  n_homes 1: one counter,
+    // a query's tasks together.
     for (;;) {
         // every lane takes part in the atomic (lane 0 adds 1, the others 0) so
         // that no lane-dependent branch guards the loop head; control values
         // below are passed through readfirstlane so the compiler keeps the
-        // whole traversal wave-uniform.  A query's tasks are consecutive.
-        const uint32_t task = readfirst(atomicAdd(next_task, lane == 0 ? 1u : 0u));
-        if (task >= ntasks) break;
-        const uint32_t qi = task >> tsh;
+        // whole traversal wave-uniform.  (A `continue` here instead of the
+        // inner loop made the traversal three times slower.)
+        uint32_t home, turn, other = 0;
+        do {
+            home = readfirst((blockIdx.x + other) & (n_homes - 1));
+            turn = readfirst(atomicAdd(next_task + home, lane == 0 ? 1u : 0u));
+            if (turn < (uint64_t)nq * ((nsplit + n_homes - 1 - home) / n_homes)) break;
+            other = readfirst(other + 1);
+        } while (other < n_homes);
+        if (other >= n_homes) break;
+        const uint32_t sub = n_homes == 1 ? turn & (nsplit - 1) : home + 8 * (turn / nq);
+        const uint32_t qi = n_homes == 1 ? turn >> tsh : turn % nq, task = (qi << tsh) + sub;
         const int32_t root =
-            nsplit == 1 ? 0 : (int32_t)readfirst((uint32_t) reinterpret_cast<const int32_t *>(sw)[task & (nsplit - 1)]);
+            nsplit == 1 ? 0 : (int32_t)readfirst((uint32_t) reinterpret_cast<const int32_t *>(sw)[sub]);
         // this task's list and statistics, for merge_kernel
         auto put = [&](u64 key, uint32_t pay, uint32_t visited, uint32_t leaves, uint32_t bounds, uint32_t dists,
                        uint32_t pq) {
@@ -367,12 +391,10 @@ __global__ __launch_bounds__(kBlock, kBest ? 3 : 4) void tree_knn_kernel(TreeVie
                 leaves++;
                 const uint32_t b0 = readfirst((uint32_t)ninfo), m = readfirst((uint32_t)(ninfo >> 32) & 0x7FFFFFFFu);
                 dists += m;
-                for (uint32_t base0 = 0; base0 < m; base0 += 32) {
-                    // up to 32 rows (4 groups of 8) loaded before any is reduced,
-                    // so a whole leaf costs one round trip to memory
-                    uint32_t cs[4], tps[4], rows[4];
+                for (uint32_t base0 = 0; base0 < m; base0 += 8 * kGroups) {
+                    uint32_t cs[kGroups], tps[kGroups], rows[kGroups];
 #pragma unroll
-                    for (int u = 0; u < 4; u++) {
+                    for (int u = 0; u < kGroups; u++) {
                         const uint32_t r = base0 + 8 * u + (uint32_t)g;
                         const uint64_t pos = (uint64_t)b0 + (r < m ? r : 0);
                         uint4 tv[4];
@@ -384,7 +406,7 @@ __global__ __launch_bounds__(kBlock, kBest ? 3 : 4) void tree_knn_kernel(TreeVie
                         rows[u] = T.perm[pos];
                     }
 #pragma unroll
-                    for (int u = 0; u < 4; u++) {
+                    for (int u = 0; u < kGroups; u++) {
                     const uint32_t base = base0 + 8 * u;
                     if (base >= m) break;
                     const uint32_t r = base + (uint32_t)g;
@@ -482,13 +504,13 @@ __device__ __forceinline__ u64 shfl_xor64(u64 v, int m) {
 // the tasks (n = 1: a copy).  One wave per query: the lists go to LDS, then
 // k steps each take the least head among the lists (the keys are distinct:
 // the subtrees partition the rows).
-constexpr int kMergeWaves = 4;
+template <int kMergeWaves, int kLists>  // waves per block, lists per query at most
 __global__ __launch_bounds__(64 * kMergeWaves) void merge_kernel(uint32_t nq, const uint32_t *__restrict__ nq_dev,
                                                                  uint32_t k, uint32_t n, const char *__restrict__ sw,
                                                                  uint32_t *idx, int32_t *missed, int32_t *extra,
                                                                  float *dist, uint32_t *qstats) {
-    __shared__ u64 s_key[kMergeWaves][kMaxSplit * QD_MAX_K];
-    __shared__ uint32_t s_pay[kMergeWaves][kMaxSplit * QD_MAX_K];
+    __shared__ u64 s_key[kMergeWaves][kLists * QD_MAX_K];
+    __shared__ uint32_t s_pay[kMergeWaves][kLists * QD_MAX_K];
     const int lane = lane_id(), w = (int)(threadIdx.x >> 6);
     const SplitLayout SL = split_layout(nq, n, k);  // laid out for nq queries
     const u64 *key = reinterpret_cast<const u64 *>(sw + SL.key);
@@ -580,26 +602,49 @@ __global__ void zero_words_kernel(uint32_t *p, uint32_t n) {
     for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0;
 }
 
+// Subtree searches per query where the caller leaves the choice: at least 16,
+// and up to 64 while the subtrees keep 8,192 rows, or 1,024 where the batch would
+// leave most waves without a search, for at most 2^18 lists (the workspace).  A
+// batch ends with its longest search, which at 16 is longer than all the rest for
+// up to some 100 queries.  Measured at 16 / 32 / 64, best-first, k = 10, 1M rows:
+// 1 query 8.2 / 5.4 / 3.2 ms, 128 queries 10.7 / 7.0 / 6.2, 509 16.6 / 14.5 /
+// 13.7, 4,096 93.3 / 91.7 / 91.7; 100k rows: 16 queries 1.03 / 0.64 / 0.49,
+// 128 1.31 / 0.98 / 1.19, 4,096 13.3 / 13.3 / 15.4.
+static uint32_t default_split(qd_tree_t t, uint64_t nq_max) {
+    uint32_t n = kMaxSplit;
+    for (; n < kFineSplit; n *= 2) {
+        const uint64_t tasks = nq_max * 2 * n;
+        if (tasks > (1u << 18) || t->n / (2 * n) < (tasks > 4096 ? 8192 : 1024)) break;
+    }
+    return n;
+}
+
 bool depth_first_fits(qd_tree_t t) { return t->depth + 2 <= (uint32_t)kMaxStack; }
 
 TreeLaunch tree_launch_shape(qd_tree_t t, uint32_t nq_max, uint32_t k, int order, uint32_t waves_per_cu,
                              uint32_t split) {
     TreeLaunch L;
     const int cus = device_cus();
-    if (waves_per_cu == 0) waves_per_cu = order == QD_ORDER_BEST_FIRST ? 12 : 16;  // as many as registers hold
-    if (split == 0) split = kDefaultSplit;
+    if (split == 0) split = default_split(t, nq_max);
     L.split = split;
+    // best-first: while every search has a wave of its own at 12 waves per CU,
+    // only its latency counts (1 query, 16 searches of 1M rows: 8.2 ms with 4
+    // groups, 9.3 with 2); with more, 16 waves do more (509 queries: 11.8 ms
+    // with 4 groups and 12 waves, 10.9 with 2 and 16)
+    const bool wide = order != QD_ORDER_BEST_FIRST || (uint64_t)nq_max * split <= (uint64_t)cus * 12;
+    L.groups = wide ? 4 : 2;
+    if (waves_per_cu == 0) waves_per_cu = order == QD_ORDER_BEST_FIRST && wide ? 12 : 16;  // as many as registers hold
     uint64_t blocks = ((uint64_t)cus * waves_per_cu + kWaves - 1) / kWaves;
     const uint64_t need = ((uint64_t)(nq_max ? nq_max : 1) * split + kWaves - 1) / kWaves;
     if (blocks > need) blocks = need;
     L.blocks = blocks;
     L.slots = blocks * kWaves;
-    // A search queues each node of its subtree at most once.  Live chunks: a
-    // bucket holds at most one partly filled chunk (or one kept empty chunk)
-    // besides full ones, and emptied chunks go to a free list, so (the
-    // subtree's nodes)/kChunk + 2 per bucket chunks never run out.
+    // A search queues each node of its subtree at most once.  Of a bucket's
+    // chunks all but the newest are full (the newest may be empty but kept) and
+    // emptied ones go to a free list, so the subtree's nodes / kChunk chunks
+    // and one per bucket touched never run out.
     const uint64_t sub = t->split_nodes[__builtin_ctz(split)];
-    L.pool_chunks = order == QD_ORDER_BEST_FIRST ? sub / kChunk + 2 * kBuckets + 2 : 1;
+    L.pool_chunks = order == QD_ORDER_BEST_FIRST ? sub / kChunk + std::min<uint64_t>(kBuckets, sub) + 2 : 1;
     L.head = 256;  // [counter | pad | stats x4 | pad]
     L.prev_bytes = (size_t)(L.slots * L.pool_chunks * 8 + 255) / 256 * 256;  // prev + free list
     L.pool_bytes = (size_t)L.slots * L.pool_chunks * kChunk * 16;  // 16-byte records: entry, node info
@@ -634,20 +679,29 @@ int tree_launch(qd_tree_t t, const TreeLaunch &L, char *ws, const uint64_t *d_q,
     }
     {
         KernelTimer timer("tree_knn", s);
-        if (order == QD_ORDER_BEST_FIRST)
-            hipLaunchKernelGGL(tree_knn_kernel<true>, dim3((uint32_t)L.blocks), dim3(kBlock), 0, s, T,
+        // dealt by query too while every search has a wave from the start
+        const uint32_t n_homes = t->n < kByQueryRows || (uint64_t)nq * L.split <= L.slots ? 1 : 8;
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((uint32_t)L.blocks), dim3(kBlock), 0, s, T,
                                reinterpret_cast<const uint4 *>(d_q), nq, k, counter, pool, chunk_prev, L.pool_chunks,
-                               S, d_trace, n_traced, nq_dev, sw, L.split);
+                               S, d_trace, n_traced, nq_dev, sw, L.split, n_homes);
+        };
+        if (order != QD_ORDER_BEST_FIRST)
+            launch(tree_knn_kernel<false, 4>);
+        else if (L.groups == 4)
+            launch(tree_knn_kernel<true, 4>);
         else
-            hipLaunchKernelGGL(tree_knn_kernel<false>, dim3((uint32_t)L.blocks), dim3(kBlock), 0, s, T,
-                               reinterpret_cast<const uint4 *>(d_q), nq, k, counter, pool, chunk_prev, L.pool_chunks,
-                               S, d_trace, n_traced, nq_dev, sw, L.split);
+            launch(tree_knn_kernel<true, 2>);
     }
     QD_HIP_CHECK(hipGetLastError());
     {
         KernelTimer timer("tree_merge", s);
-        hipLaunchKernelGGL(merge_kernel, dim3((nq + kMergeWaves - 1) / kMergeWaves), dim3(64 * kMergeWaves), 0, s,
-                           nq, nq_dev, k, L.split, sw, d_idx, d_missed, d_extra, d_dist, d_qstats);
+        if (L.split <= kMaxSplit)
+            hipLaunchKernelGGL((merge_kernel<4, kMaxSplit>), dim3((nq + 3) / 4), dim3(256), 0, s, nq, nq_dev, k,
+                               L.split, sw, d_idx, d_missed, d_extra, d_dist, d_qstats);
+        else
+            hipLaunchKernelGGL((merge_kernel<1, kFineSplit>), dim3(nq), dim3(64), 0, s, nq, nq_dev, k, L.split, sw,
+                               d_idx, d_missed, d_extra, d_dist, d_qstats);
     }
     QD_HIP_CHECK(hipGetLastError());
     return QD_OK;
@@ -675,8 +729,9 @@ int knn_tree_impl(qd_tree_t t, const uint64_t *d_q, uint32_t nq, uint32_t k, int
         return fail(QD_ERR_UNSUPPORTED, "tree depth %u exceeds the depth-first stack (%d)", t->depth, kMaxStack);
     if (n_traced > t->n_nodes) return fail(QD_ERR_INVALID, "n_traced above the node count");
     if (d_trace && n_traced) split = 1;  // traces follow the one-wave traversal
-    if ((uint64_t)nq * (split ? split : kDefaultSplit) > 0x7FFFFFFFull)
-        return fail(QD_ERR_INVALID, "%u queries x %u subtree searches: too many tasks", nq, split ? split : kDefaultSplit);
+    const uint32_t n_tasks = split ? split : default_split(t, nq);
+    if ((uint64_t)nq * n_tasks > 0x7FFFFFFFull)
+        return fail(QD_ERR_INVALID, "%u queries x %u subtree searches: too many tasks", nq, n_tasks);
     hipStream_t s = (hipStream_t)stream;
     const TreeLaunch L = tree_launch_shape(t, nq, k, order, waves_per_cu, split);
     char *ws = nullptr;
