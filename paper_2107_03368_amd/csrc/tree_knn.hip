@@ -161,8 +161,12 @@ __global__ __launch_bounds__(kBlock, kBest && kGroups == 4 ? 3 : 4) void tree_kn
         uint32_t home, turn, other = 0;
         do {
             home = readfirst((blockIdx.x + other) & (n_homes - 1));
-            turn = readfirst(atomicAdd(next_task + home, lane == 0 ? 1u : 0u));
-            if (turn < (uint64_t)nq * ((nsplit + n_homes - 1 - home) / n_homes)) break;
+            const uint32_t limit = nq * ((nsplit + n_homes - 1 - home) / n_homes);  // below 2^31
+            // (another XCD's counter is read first: thousands of waves adding to
+            // counters that have run out would take turns for 0.3 ms)
+            turn = other ? readfirst(__hip_atomic_load(next_task + home, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) : 0;
+            if (turn < limit) turn = readfirst(atomicAdd(next_task + home, lane == 0 ? 1u : 0u));
+            if (turn < limit) break;
             other = readfirst(other + 1);
         } while (other < n_homes);
         if (other >= n_homes) break;
