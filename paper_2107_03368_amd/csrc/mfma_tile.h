@@ -51,7 +51,7 @@
 // rows needs no exchange until its end.
 //
 // A missing row reads as zeros.  The tile is the same whether rows are contiguous
-// (sequential search) or gathered through a list (the blocked tree search).
+// (block bounds) or gathered through a list (object scores).
 #pragma once
 
 #include "qd.h"

@@ -77,6 +77,7 @@ constexpr uint32_t kMaxBatch = 16384;      // queries per batch (list entries ar
 // listed queries (measured at 10M rows x 8,192 queries: 12 and 16 fastest,
 // 24 0.4%, 32 0.9% and 48 2% slower).
 constexpr uint32_t kShortList = 16;
+constexpr uint32_t kNextItem = 8;  // counter of the evaluation's items, cleared by the tile prefix
 
 // Position of block b of bound level L in the per-query block order; a round
 // covers the keys in (lo, hi].  Key 0 is below every block.
@@ -783,6 +784,7 @@ __global__ __launch_bounds__(1024) void tile_scan_kernel(const uint32_t *__restr
         voff[nblk] = vall;
         total[0] = all;
         total[1] = vall;
+        total[kNextItem - 2] = 0;
     }
 }
 
@@ -875,228 +877,240 @@ __global__ __launch_bounds__(256) void eval_short_kernel(const uint4 *__restrict
     }
 }
 
-// Tiles of 256 listed queries of a block x the block's rows, in a persistent
-// grid: workgroup x takes tiles x, x + G, x + 2G, ... of the virtual tile
-// order (G = gridDim.x, a multiple of 8, so the workgroup stays on one XCD and
-// the XCD's tiles form one contiguous range of the tile list).  The tiles are
-// streamed: the next tile's first two windows are staged during the current
-// tile's last two, and its metadata is fetched during the current tile, one
-// dependent load per window, so the matrix cores do not wait for a tile to
-// start.  The metadata of consecutive tiles alternates between two LDS
-// copies, so no barrier closes a tile: a wave that finishes its epilogue
-// goes on to the next tile's first window while others still test their
-// pairs (the window buffers are free: every wave read them before the last
-// window's barrier).  A wave's passing pairs claim their candidate slots
-// (the atomics) at the end of its epilogue and are written during the next
-// tile's first window, once the slots have come back.
-__global__ __launch_bounds__(mt::kThreads) void eval_kernel(const uint4 *__restrict__ q, const uint4 *__restrict__ sorted,
-                                                            uint64_t n, uint32_t nqp, const uint32_t *__restrict__ ntiles,
-                                                            const uint16_t *__restrict__ list,
-                                                            const uint4 *__restrict__ tinfo,
-                                                            const uint16_t *__restrict__ tpop,
-                                                            const uint32_t *__restrict__ perm,
-                                                            const uint16_t *__restrict__ qpop,
-                                                            const uint32_t *__restrict__ thrk,
-                                                            uint32_t *__restrict__ ccnt, u64 *__restrict__ cand) {
-    __shared__ mt::Smem sm;
-    // two copies (tiles alternate): query slot's query, |q|, k-th key and pass
-    // test's bound; row's |t|
-    __shared__ uint32_t s_qi[2][mt::MA], s_pq[2][mt::MA], s_th[2][mt::MA];
-    __shared__ __align__(16) float s_tp[2][mt::MB];
-    __shared__ float s_bound[2][mt::MA];
-    // per wave: the tile's passing (query, key, row) entries, appended in order
-    // and written out together, so the candidate slots' atomics overlap
-    // instead of waiting one after another
-    constexpr uint32_t kQueue = 320;  // room for four rows' 256 entries past the flush mark
-    __shared__ uint32_t s_cq[mt::kThreads / 64][kQueue][3];
+// The listed queries of the blocks x the blocks' rows, on the matrix cores.
+// A workgroup of 4 waves keeps half a block's rows packed in LDS (two
+// workgroups fit on a CU, so one multiplies while the other fetches rows) and
+// streams the block's listed queries past them: a wave takes 64 queries at a
+// time straight from memory into the instruction's operand registers, against
+// 64 of the rows, 2 x 2 fragments.  Waves share nothing but the rows, so the
+// only barriers are around a change of rows.  The line layout, the order of
+// bits and the expansion between the multiplications are those of
+// scan_mfma_kernel with the roles exchanged; a lane holds one query per
+// fragment, whose |q| it counts from the words and whose k-th key it fetches
+// one unit ahead.
+// Work is dealt from a counter: up to kEvTiles consecutive tile records (one
+// block's share their rows), each once per half of the rows.
+// Bound by the matrix units and, a fifth, by the changes of rows: 10M rows x
+// 8,192 queries, k = 10 (15.0e9 pairs) take 20.8 ms, 5.9 PFLOP/s; 21.1 / 22.1 /
+// 23.9 ms with 4 / 2 / 1 records per item, and 23.1 with a 256 x 256 tile per
+// workgroup of 8 waves (queries and rows staged in LDS, a barrier per 512 bits).
+// A wave's passing pairs are appended to its queue in LDS and written out
+// together, so the candidate slots' atomics overlap.
+constexpr int kEvBlock = 256, kEvWaves = kEvBlock / 64;
+constexpr uint32_t kEvRows = 128;        // rows in LDS: half a block
+constexpr int kEvStride = 512 + 16;      // bytes per row in LDS: 16-byte reads of 32 rows on distinct banks
+constexpr uint32_t kEvQueue = 128;       // passing pairs per wave: room for one row's 64 past the flush mark
+constexpr uint32_t kEvTiles = 8;
+__global__ __launch_bounds__(kEvBlock, 2) void eval_kernel(const uint4 *__restrict__ q, const uint4 *__restrict__ sorted,
+                                                           uint64_t n, uint32_t nqp, const uint32_t *__restrict__ ntiles,
+                                                           const uint16_t *__restrict__ list,
+                                                           const uint4 *__restrict__ tinfo,
+                                                           const uint16_t *__restrict__ tpop,
+                                                           const uint32_t *__restrict__ perm,
+                                                           const uint32_t *__restrict__ thrk,
+                                                           uint32_t *__restrict__ next, uint32_t *__restrict__ ccnt,
+                                                           u64 *__restrict__ cand) {
+    __shared__ __align__(16) uint8_t s_rows[kEvRows * kEvStride];
+    __shared__ __align__(16) float s_tp[kEvRows];
+    __shared__ uint32_t s_cq[kEvWaves][kEvQueue][3];
+    __shared__ uint32_t s_item;
     const uint32_t total = *ntiles;  // written by the tile prefix
-    const uint64_t vend = mt::xcd_grid(total);
-    const int r = mt::own_row();
-    const bool arow = r < mt::MA;  // the same in a whole wave
-    // a lane-varying zero: keeps the per-tile record load a vector load (a
-    // scalar load shares its completion counter with the LDS reads)
-    const uint32_t vz = __builtin_amdgcn_mbcnt_lo(0u, 0u);
-    // A tile's fetch is three dependent loads: its record (block b, list
-    // offset t0, queries m), then this thread's list entry (queries) or row popcount (rows), then the query's |q| and
-    // k-th key.  Every load is unconditional and in bounds (a row past m or n
-    // reads a valid entry and is masked when used).
-    uint4 info;          // the record
-    uint32_t pb, pc, pd; // loads in flight: list entry or |t|; |q|; k-th key
-    uint32_t qi = 0, tp = 0, pq = 0, th = 0;
-    bool ok = false;
-    auto issue_b = [&](const uint4 &in) {
-        const uint64_t r0 = (uint64_t)in.x * kBlk;
-        pb = arow ? list[(uint64_t)in.x * nqp + in.y + r]  // t0 + 256 <= nqp: the entry exists
-                  : tpop[r0 + (r - mt::MA) < n ? r0 + (r - mt::MA) : n - 1];
-    };
-    auto take_b = [&](const uint4 &in) {
-        const uint64_t r0 = (uint64_t)in.x * kBlk;
-        ok = arow ? (uint32_t)r < in.z : r0 + (r - mt::MA) < n;
-        qi = arow && ok ? pb : 0;
-        tp = !arow && ok ? pb : 0;
-    };
-    auto issue_c = [&]() {
-        pc = qpop[qi];
-        pd = thrk[qi];
-    };
-    auto take_c = [&]() {
-        pq = arow && ok ? pc : 0;
-        th = arow && ok ? pd : 0;
-    };
-    auto bound_of = [&]() -> float { return arow && ok ? mt::pass_bound(pq, weight_b(pq), th) : mt::kNoBound; };
-    auto row_of = [&](const uint4 &in) -> const uint4 * {
-        const uint64_t r0 = (uint64_t)in.x * kBlk;
-        return arow ? q + (uint64_t)qi * 32 : sorted + (ok ? r0 + (r - mt::MA) : 0) * 32;
-    };
-    auto publish = [&](float bound, int pb) {  // read after the next barrier
-        if (arow) {
-            s_qi[pb][r] = qi;
-            s_pq[pb][r] = pq;
-            s_th[pb][r] = th;
-            s_bound[pb][r] = bound;
-        } else {
-            s_tp[pb][r - mt::MA] = ok ? (float)tp : mt::kNoRow;
-        }
-    };
-
-    uint64_t v = blockIdx.x, xt;
-    if (!(v < vend && mt::xcd_tile(v, total, xt))) return;  // whole workgroup: no tile
-    // the first tile: fetched here, waiting for each load
-    info = tinfo[xt + vz];
-    issue_b(info);
-    take_b(info);
-    issue_c();
-    take_c();
-    uint4 cur = info;
-    const uint4 *row = row_of(cur);
-    bool cur_ok = ok;
-    int par = 0;  // metadata copy of the current tile
-    publish(bound_of(), par);
-    mt::Stream st;
-    mt::stream_begin(row, !cur_ok, sm, st);  // its barrier also publishes the metadata
-    const int wv = r >> 6, lane = r & 63;
+    // fewer tiles per item where there are few, so that every workgroup gets some
+    const uint32_t per = max(1u, min(kEvTiles, total / 2048));
+    const uint64_t n_items = 2 * (uint64_t)((total + per - 1) / per);
+    const int t = (int)threadIdx.x, lane = t & 63, wv = (int)readfirst(t >> 6);
+    const int li = lane & 31, lh = lane >> 5;
+    const int rt = wv & 1, qfirst = wv >> 1;  // this wave's half of the rows, first 64 queries
     uint32_t (*cq)[3] = s_cq[wv];
-    // the previous tile's passing pairs still to be written: entry `lane` of
-    // this wave's queue, its claimed slot and its row's original index
-    uint32_t dn = 0, dpos = 0, dperm = 0;
-    auto store_claimed = [&]() {
-        if ((uint32_t)lane < dn && dpos < kCap)
-            cand[(uint64_t)cq[lane][0] * kCap + dpos] = ((u64)cq[lane][1] << 32) | dperm;
-        dn = 0;
+    uint32_t nqe = 0;  // entries in this wave's queue (the same in every lane)
+    auto flush = [&]() {
+        for (uint32_t e = lane; e < nqe; e += 64) {
+            const uint32_t qk = cq[e][0];
+            const uint32_t pos = atomicAdd(&ccnt[qk], 1u);
+            if (pos < kCap) cand[(uint64_t)qk * kCap + pos] = ((u64)cq[e][1] << 32) | perm[cq[e][2]];
+        }
+        nqe = 0;
     };
+    auto word = [](const uint4 &x, int c) { return c == 0 ? x.x : c == 1 ? x.y : c == 2 ? x.z : x.w; };
     for (;;) {
-        // tiles of this workgroup only run out at the end of its XCD's range
-        const uint64_t vn = v + gridDim.x;
-        const bool more = vn < vend && mt::xcd_tile(vn, total, xt);
-        const uint64_t xn = more ? xt : 0;
-        uint4 pa = info;      // the next tile's record, in flight
-        const uint4 *nrow = row;
-        bool nok = false;
-        float nbound = 0.f;
-        mt::Acc acc;
-        // after window w: take what window w - 1 loaded (the window's own store
-        // waited for every earlier load), then issue the next loads
-        bool nzero = true;
-        // the waves of query slots 128..255 have nothing to multiply when the tile
-        // lists at most 128 queries
-        const bool idle = (r >> 8) == 1 && cur.z <= (uint32_t)(mt::MA / 2);
-        mt::stream_tile(row, !cur_ok, nrow, nzero, sm, st, acc, [&](int win) {
-            if (win == 0) store_claimed();
-            if (win == 1) info = pa;
-            if (win == 2) take_b(info);
-            if (win == 3) {
-                take_c();
-                nbound = bound_of();
-                nrow = row_of(info);
-                nok = ok;
-                nzero = !more || !ok;
+        __syncthreads();  // every wave is done with the item before
+        if (t == 0) s_item = atomicAdd(next, 1u);
+        __syncthreads();
+        const uint32_t item = readfirst(s_item);
+        if (item >= n_items) break;
+        const uint32_t xe = min((item >> 1) * per + per, total);
+        for (uint32_t x = (item >> 1) * per; x < xe;) {
+            // the item's tiles of one block: consecutive parts of its list, all but the last full
+            const uint4 rec = tinfo[x];
+            const uint64_t blk = readfirst(rec.x);
+            const uint32_t x0 = x;
+            uint32_t m = readfirst(rec.z);
+            for (x++; x < xe; x++) {
+                const uint4 r2 = tinfo[x];
+                if (readfirst(r2.x) != blk) break;
+                m = (x - x0) * mt::MA + readfirst(r2.z);
             }
-            pa = tinfo[xn + vz];
-            issue_b(info);
-            issue_c();
-        }, idle);
-        const uint64_t r0 = (uint64_t)cur.x * kBlk;
-        const uint32_t *t_qi = s_qi[par], *t_pq = s_pq[par], *t_th = s_th[par];
-        const float *t_tp = s_tp[par], *t_bound = s_bound[par];
-        uint32_t nq = 0;  // entries in this wave's queue (the same in every lane)
-        auto flush = [&]() {
-            for (uint32_t e = lane; e < nq; e += 64) {
-                const uint32_t qk = cq[e][0], K = cq[e][1], rw = cq[e][2];
-                const uint32_t pos = atomicAdd(&ccnt[qk], 1u);
-                if (pos < kCap) cand[(uint64_t)qk * kCap + pos] = ((u64)K << 32) | perm[rw];
+            const uint64_t row0 = blk * kBlk + (item & 1) * kEvRows;
+            if (row0 >= n) continue;  // the last block's second half may hold no row
+            const uint16_t *const lst = list + blk * nqp + readfirst(rec.y);
+            const uint32_t n_qt = (m + 63) / 64;
+            uint32_t qt = (uint32_t)qfirst;
+            const bool work = qt < n_qt;
+            // the queries of a unit: fragment a's is lane li's (past the end: the last, masked in the test)
+            auto query_of = [&](uint32_t u, int a) { return (uint32_t)lst[min(64 * u + 32 * a + li, m - 1)]; };
+            uint4 v[2][2][4];  // [line parity][fragment][piece pair]
+            auto load = [&](const uint32_t (&qi)[2], int L, uint4 (&y)[2][4]) {
+#pragma unroll
+                for (int a = 0; a < 2; a++) {
+                    const uint4 *src = q + (uint64_t)qi[a] * 32 + 8 * L + lh;
+#pragma unroll
+                    for (int i = 0; i < 4; i++) y[a][i] = src[2 * i];
+                }
+            };
+            uint32_t qi[2] = {0, 0}, th[2] = {0, 0};
+            if (work) {  // fetched while the rows are
+#pragma unroll
+                for (int a = 0; a < 2; a++) qi[a] = query_of(qt, a);
+                load(qi, 0, v[0]);
+#pragma unroll
+                for (int a = 0; a < 2; a++) th[a] = thrk[qi[a]];
             }
-            nq = 0;
-        };
+            __syncthreads();  // every wave is done with the rows before
+            {
+                constexpr int kPer = kEvRows * 32 / kEvBlock;
+                uint4 y[kPer];
 #pragma unroll
-        for (int a = 0; a < mt::QF; a++) {
-            // one fragment of queries at a time, so their metadata loads stay next to their use
-            __builtin_amdgcn_sched_barrier(0);
-            const int i = mt::acc_query(a);
-            const float bound = t_bound[i];
-            const uint32_t pk = t_pq[i], wa = weight_a(pk), wb = weight_b(pk);
-            const float nratio = -(float)wa * mt::inv_sw(pk);
+                for (int i = 0; i < kPer; i++) {
+                    const uint32_t e = (uint32_t)t + kEvBlock * i;
+                    const uint64_t row = row0 + (e >> 5);
+                    y[i] = sorted[(row < n ? row : n - 1) * 32 + (e & 31)];
+                }
 #pragma unroll
-            for (int b = 0; b < mt::RF; b++) {
-                // most (query, row) pairs miss the k-th key by far: 16 rows of
-                // the lane's query at once, then four at a time, then one
-                mt::Quad v4[4];
+                for (int i = 0; i < kPer; i++) {
+                    const uint32_t e = (uint32_t)t + kEvBlock * i;
+                    *reinterpret_cast<uint4 *>(s_rows + (size_t)(e >> 5) * kEvStride + (e & 31) * 16) = y[i];
+                }
+                if (t < (int)kEvRows) s_tp[t] = row0 + t < n ? (float)tpop[row0 + t] : mt::kNoRow;
+            }
+            __syncthreads();
+            if (!work) continue;
+            const uint8_t *const rrow = s_rows + (size_t)(64 * rt + li) * kEvStride + lh * 16;
+            const float *const tp = s_tp + 64 * rt;
+            uint4 rw[2][2];              // rows' pieces: [piece pair parity][fragment]
+            mt::v8i qv[2][2], rv[2][2];  // operands: [step parity][fragment]
+            uint32_t pc[2] = {0, 0};     // |q| so far
+            auto read_r = [&](int pair) {
 #pragma unroll
-                for (int g = 0; g < 4; g++)
-                    v4[g] = mt::quad_test(acc[a][b], g, *reinterpret_cast<const float4 *>(t_tp + mt::quad_row(b, g)),
-                                          nratio);
-                const float mx = fmaxf(fmaxf(v4[0].max(), v4[1].max()), fmaxf(v4[2].max(), v4[3].max()));
-                if (ballot(mx >= bound) == 0) continue;
-                const uint32_t qk = t_qi[i], tk = t_th[i];
-                // K = |q|*wB + |t|*wA - C*(wA + wB): 24-bit multiplies (C <= 4096
-                // and wA + wB <= 4097; every term below 2^26)
-                const uint32_t P = __umul24(pk, wb);
-                const int nsw = -(int)(wa + wb);
+                for (int b = 0; b < 2; b++)
+                    rw[pair & 1][b] = *reinterpret_cast<const uint4 *>(rrow + 32 * b * kEvStride + pair * 32);
+            };
+            auto expand = [&](int S, int f) {  // fragment f of step S (mod 64): rows 0, 1, then queries
+                const int L = (S >> 4) & 3, i = (S >> 2) & 3, c = S & 3;
+                if (f < 2) {
+                    rv[S & 1][f] = mt::expand_r(word(rw[(4 * L + i) & 1][f], c));
+                } else {
+                    const uint32_t y = word(v[L & 1][f - 2][i], c);
+                    qv[S & 1][f - 2] = mt::expand_q(y);
+                    pc[f - 2] += __popc(y);
+                }
+            };
+            read_r(0);
 #pragma unroll
-                for (int g = 0; g < 4; g++) {
-                    if (ballot(v4[g].max() >= bound) == 0) continue;
-                    const int rq = mt::quad_row(b, g);
+            for (int f = 0; f < 4; f++) expand(0, f);
+            for (;;) {
+                // the wave's next unit (after the last: this one again, unused)
+                const bool more = qt + 2 < n_qt;
+                const uint32_t nqt = more ? qt + 2 : qt;
+                uint32_t nqi[2], nth[2], pcur[2];
+                mt::v16f acc[2][2];
 #pragma unroll
-                    for (int e = 0; e < 4; e++) {
-                        const bool act = v4[g].v[e] >= bound;
-                        if (ballot(act) == 0) continue;
-                        const uint32_t tpe = (uint32_t)t_tp[rq + e];
-                        const uint32_t C = mt::count(acc[a][b][4 * g + e]);
-                        const uint32_t K = (uint32_t)((int)(P + __umul24(tpe, wa)) + __mul24((int)C, nsw));
-                        const bool pass = act & (K <= tk);
-                        const u64 pm = ballot(pass);
-                        if (pass) {
-                            const uint32_t at = nq + lanes_below(pm);
-                            cq[at][0] = qk;
-                            cq[at][1] = K;
-                            cq[at][2] = (uint32_t)r0 + rq + e;
-                        }
-                        nq += (uint32_t)__popcll(pm);
+                for (int L = 0; L < 4; L++) {
+                    if (L == 0) {
+#pragma unroll
+                        for (int a = 0; a < 2; a++) nqi[a] = query_of(nqt, a);
                     }
-                    if (nq > kQueue - 256) flush();  // the next four rows add at most 4 x 64
+                    load(L < 3 ? qi : nqi, (L + 1) & 3, v[(L + 1) & 1]);
+                    if (L == 3) {
+#pragma unroll
+                        for (int a = 0; a < 2; a++) nth[a] = thrk[nqi[a]];
+                    }
+#pragma unroll
+                    for (int st = 0; st < 16; st++) {
+                        const int S = 16 * L + st;
+                        if ((S & 3) == 0) read_r((S / 4 + 1) & 15);
+                        if (S == 63) {  // from here on the next unit's queries are counted
+                            pcur[0] = pc[0];
+                            pcur[1] = pc[1];
+                            pc[0] = pc[1] = 0;
+                        }
+#pragma unroll
+                        for (int x2 = 0; x2 < 4; x2++) {
+                            const mt::v16f zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f,
+                                                   0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                            acc[x2 >> 1][x2 & 1] =
+                                mt::mma32(rv[S & 1][x2 & 1], qv[S & 1][x2 >> 1], S == 0 ? zero : acc[x2 >> 1][x2 & 1]);
+                            expand(S + 1, x2);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int a = 0; a < 2; a++) {
+                    const uint32_t pk = pcur[a] + (uint32_t)__shfl_xor((int)pcur[a], 32);  // this lane's query
+                    const uint32_t wa = weight_a(pk), wb = weight_b(pk), qk = qi[a], tk = th[a];
+                    const float bound =
+                        64 * qt + 32 * a + li < m ? mt::pass_bound(pk, wb, tk) : mt::kNoBound;
+                    const float nratio = -(float)wa * mt::inv_sw(pk);
+#pragma unroll
+                    for (int b = 0; b < 2; b++) {
+                        // most (query, row) pairs miss the k-th key by far: 16 rows of
+                        // the lane's query at once, then four at a time, then one
+                        mt::Quad v4[4];
+#pragma unroll
+                        for (int g = 0; g < 4; g++)
+                            v4[g] = mt::quad_test(acc[a][b], g,
+                                                  *reinterpret_cast<const float4 *>(tp + 32 * b + 8 * g + 4 * lh), nratio);
+                        const float mx = fmaxf(fmaxf(v4[0].max(), v4[1].max()), fmaxf(v4[2].max(), v4[3].max()));
+                        if (ballot(mx >= bound) == 0) continue;
+                        // K = |q|*wB + |t|*wA - C*(wA + wB): 24-bit multiplies (C <= 4096
+                        // and wA + wB <= 4097; every term below 2^26)
+                        const uint32_t P = __umul24(pk, wb);
+                        const int nsw = -(int)(wa + wb);
+#pragma unroll
+                        for (int g = 0; g < 4; g++) {
+                            if (ballot(v4[g].max() >= bound) == 0) continue;
+#pragma unroll
+                            for (int e = 0; e < 4; e++) {
+                                const bool act = v4[g].v[e] >= bound;
+                                if (ballot(act) == 0) continue;
+                                const int ro = 32 * b + 8 * g + 4 * lh + e;
+                                const uint32_t K = (uint32_t)((int)(P + __umul24((uint32_t)tp[ro], wa)) +
+                                                              __mul24((int)mt::count(acc[a][b][4 * g + e]), nsw));
+                                const bool pass = act & (K <= tk);
+                                const u64 pm = ballot(pass);
+                                if (pass) {
+                                    const uint32_t at = nqe + lanes_below(pm);
+                                    cq[at][0] = qk;
+                                    cq[at][1] = K;
+                                    cq[at][2] = (uint32_t)row0 + 64 * rt + ro;
+                                }
+                                nqe += (uint32_t)__popcll(pm);
+                                if (nqe > kEvQueue - 64) flush();  // the next row adds at most 64
+                            }
+                        }
+                    }
+                }
+                if (!more) break;
+                qt = nqt;
+#pragma unroll
+                for (int a = 0; a < 2; a++) {
+                    qi[a] = nqi[a];
+                    th[a] = nth[a];
                 }
             }
         }
-        if (nq > 64) {
-            flush();
-        } else {  // claim the slots now, write them during the next tile
-            if ((uint32_t)lane < nq) {
-                dpos = atomicAdd(&ccnt[cq[lane][0]], 1u);
-                dperm = perm[cq[lane][2]];
-            }
-            dn = nq;
-            nq = 0;
-        }
-        if (!more) {
-            store_claimed();
-            break;
-        }
-        par ^= 1;
-        publish(nbound, par);  // the other copy: this tile's may still be read
-        cur = info;
-        row = nrow;
-        cur_ok = nok;
-        v = vn;
     }
+    flush();
 }
 
 // After a round: merge each running query's candidates into its top k,
@@ -1488,9 +1502,8 @@ int blocked_batch(qd_tree_t t, const BlockedLayout &L, char *ws, const uint64_t 
                            cuts, qpop, top, ntop, thr, rec, frange, qround, ctr, want_stats ? qst : nullptr, nq_dev);
     }
     if (hipGetLastError() != hipSuccess) return fail(QD_ERR_DEVICE, "blocked search: launch failed");
-    // persistent matrix-core tiles: one workgroup per CU (the tile's LDS and
-    // registers leave room for one), a multiple of the 8 XCDs
-    const uint64_t eval_grid = mt::xcd_grid((uint64_t)device_cus());
+    // persistent: two workgroups per CU (LDS and registers leave room for two)
+    const uint64_t eval_grid = 2 * (uint64_t)device_cus();
     const uint64_t short_grid = mt::xcd_grid((uint64_t)device_cus() * 8);
     // tile records: at most ceil(nqb / 256) tiles per block
     const uint64_t info_grid = std::min<uint64_t>((nblk * (nqp / mt::MA) + 255) / 256, (uint64_t)device_cus() * 8);
@@ -1545,9 +1558,9 @@ int blocked_batch(qd_tree_t t, const BlockedLayout &L, char *ws, const uint64_t 
         }
         {
             KernelTimer timer("tree_block_eval", s);
-            hipLaunchKernelGGL(eval_kernel, dim3((uint32_t)eval_grid), dim3(mt::kThreads), 0, s, q4,
+            hipLaunchKernelGGL(eval_kernel, dim3((uint32_t)eval_grid), dim3(kEvBlock), 0, s, q4,
                                reinterpret_cast<const uint4 *>(t->d_sorted), n, nqp, ctr + 2, list, tinfo, t->d_pop,
-                               t->d_perm, qpop, thr, ccnt, cand);
+                               t->d_perm, thr, ctr + kNextItem, ccnt, cand);
         }
         {
             KernelTimer timer("tree_block_eval_short", s);
