@@ -39,7 +39,7 @@ namespace {
 constexpr int kBlock = 256;
 // Which kernel splits a node.  One block per node up to kSmall rows: its
 // threads share one set of counters, and a level of such nodes is one launch;
-// several blocks per node take ten launches (some 50 us of a level's time even
+// several blocks per node take eight launches (some 50 us of a level's time even
 // for a few nodes).  Above kMid the block has 512 threads, because a million
 // rows are then only 500 to 2,000 blocks (1,950-row nodes: 0.46 ms per million
 // rows, 0.71 with 256 threads).  Up to kKept rows they stay in registers
@@ -572,6 +572,15 @@ struct BigCut {
     uint32_t all;    // 1: every bit is banded; 2: in the second try
 };
 
+// Where a large node's counts come from.  Of a large parent's children only the
+// one of fewer rows is counted; the other's counts are the parent's less those
+// (1M rows: 0.51 ms for the counts of all levels, 0.92 when every large node was
+// counted).
+struct CountSource {
+    uint32_t job;     // counted node, among the level's counted ones
+    uint32_t parent;  // kNoKey: the job counted this node; else its parent's slot, one level up
+};
+
 // A node's counts are stored by (bit % 16, bit / 16): thread t of a block
 // owns bits 16t .. 16t + 15 and its accesses stay consecutive over t.
 __device__ __forceinline__ uint32_t count_at(uint32_t t, uint32_t i) { return i * kBlock + t; }
@@ -611,21 +620,30 @@ constexpr uint32_t kMaskWords = (kBandPlanes + 1) * (QD_BITS / 32);  // a node's
 
 // Band the least popular bits of a node by count: `lambda` times the members'
 // worth of them, or all (lambda 0, the second try: only where the first fell
-// short).  The first half of the bands holds a quarter of the counts.  One block per large node,
+// short).  Also completes the node's counts.  The first half of the bands holds a quarter of the counts.  One block per large node,
 // 1,024 threads because it is a chain of short steps.
-__global__ __launch_bounds__(1024) void big_band_kernel(const uint32_t *__restrict__ gcnt,
+__global__ __launch_bounds__(1024) void big_band_kernel(const CountSource *__restrict__ src,
+                                                        const uint32_t *__restrict__ counted,
+                                                        const uint32_t *__restrict__ above, uint32_t *__restrict__ gcnt,
                                                         const uint32_t *__restrict__ ncount, uint32_t lambda,
                                                         uint32_t *__restrict__ mask, uint32_t *__restrict__ bhist,
-                                                        BigCut *__restrict__ cuts) {
+                                                        BigCut *__restrict__ cuts, uint32_t *__restrict__ any_redo) {
     constexpr uint32_t kBins = 256;
     __shared__ uint32_t bits[kBandPlanes + 1][QD_BITS / 32];
     __shared__ uint32_t bins[kBins];
     __shared__ u64 sums[32];
     const uint32_t slot = blockIdx.x, t = threadIdx.x, m = ncount[slot];
     if (!lambda && !cuts[slot].redo) return;  // whole block
+    const CountSource from = src[slot];
     uint32_t cnt[4];
 #pragma unroll
-    for (int i = 0; i < 4; i++) cnt[i] = gcnt[(uint64_t)slot * QD_BITS + count_at(t & 255, 4 * (t >> 8) + i)];
+    for (int i = 0; i < 4; i++) {
+        const uint32_t at = count_at(t & 255, 4 * (t >> 8) + i);
+        cnt[i] = counted[(uint64_t)from.job * QD_BITS + at];
+        if (from.parent != kNoKey) cnt[i] = above[(uint64_t)from.parent * QD_BITS + at] - cnt[i];
+        gcnt[(uint64_t)slot * QD_BITS + at] = cnt[i];
+    }
+    if (lambda && slot == 0 && t == 0) *any_redo = 0;
     for (uint32_t i = t; i < kMaskWords; i += 1024) (&bits[0][0])[i] = 0;
     if (t < kBins) bins[t] = 0;
     const uint32_t cmax = lambda ? count_threshold<16, false>(cnt, m, (u64)m * lambda, sums) : m;
@@ -723,7 +741,8 @@ __global__ __launch_bounds__(1024) void big_rank_kernel(const uint32_t *__restri
                                                         const uint32_t *__restrict__ mask,
                                                         const uint32_t *__restrict__ bhist, uint32_t again,
                                                         uint16_t *__restrict__ rank, uint32_t *__restrict__ ghist,
-                                                        BigCut *__restrict__ cuts, uint32_t *__restrict__ nd_out) {
+                                                        BigCut *__restrict__ cuts, uint32_t *__restrict__ nd_out,
+                                                        uint32_t *__restrict__ any_redo) {
     __shared__ u64 keys[QD_BITS];
     __shared__ uint32_t hist[kBands];
     __shared__ uint32_t counter;
@@ -739,6 +758,7 @@ __global__ __launch_bounds__(1024) void big_rank_kernel(const uint32_t *__restri
         if (t == 0) {
             cuts[slot] = {1, cb, 0, lower, all ? 0u : 1u, all};
             nd_out[slot] = lower;
+            if (!all) *any_redo = 1;
         }
         return;
     }
@@ -1081,22 +1101,26 @@ int tree_build_impl(const uint64_t *d_db, uint64_t n, const qd_build_params *par
         bytes += (b + 255) & ~(size_t)255;
         return at;
     };
-    const size_t o_pa = take(n * 4), o_pb = take(n * 4), o_fr = take(n * 2), o_begin = take(max_split * 8),
-                 o_count = take(max_split * 4), o_nd = take(max_split * 4), o_items = take(max_items * sizeof(Item)),
-                 o_dc = take(max_items * 4), o_gc = take(max_big * QD_BITS * 4), o_gh = take(max_big * QD_BITS * 4),
-                 o_rank = take(max_big * QD_BITS * 2), o_mask = take(max_big * kMaskWords * 4),
-                 o_bh = take(max_big * kBands * 4), o_cuts = take(max_big * sizeof(BigCut));
+    // a level's lists, uploaded in one piece: begins and counts of the split
+    // nodes; of the large ones the items and count sources, and the counted
+    // nodes' begins and items
+    const uint64_t max_up = max_split * 12 + max_items * 2 * sizeof(Item) + max_big * (8 + sizeof(CountSource)) + 128;
+    const size_t o_pa = take(n * 4), o_pb = take(n * 4), o_fr = take(n * 2), o_up = take(max_up),
+                 o_nd = take((max_split + 1) * 4), o_dc = take(max_items * 4), o_ga = take(max_big * QD_BITS * 4),
+                 o_gb = take(max_big * QD_BITS * 4), o_jc = take(max_big * QD_BITS * 4),
+                 o_gh = take(max_big * QD_BITS * 4), o_rank = take(max_big * QD_BITS * 2),
+                 o_mask = take(max_big * kMaskWords * 4), o_bh = take(max_big * kBands * 4),
+                 o_cuts = take(max_big * sizeof(BigCut));
     std::unique_ptr<qd_tree_s, void (*)(qd_tree_s *)> tree(new qd_tree_s(), tree_release);
     QD_HIP_CHECK(hipMalloc((void **)&tree->d_sorted, std::max<size_t>(n * 512, bytes)));
     QD_HIP_CHECK(hipMalloc((void **)&tree->d_perm, n * 4));
     char *const scratch = (char *)tree->d_sorted;
-    uint64_t *const d_begin = (uint64_t *)(scratch + o_begin);
-    uint32_t *const d_count = (uint32_t *)(scratch + o_count), *const d_nd = (uint32_t *)(scratch + o_nd),
-             *const dc = (uint32_t *)(scratch + o_dc), *const gc = (uint32_t *)(scratch + o_gc),
-             *const gh = (uint32_t *)(scratch + o_gh), *const mask = (uint32_t *)(scratch + o_mask),
-             *const bh = (uint32_t *)(scratch + o_bh);
+    char *const d_up = scratch + o_up;
+    uint32_t *const d_nd = (uint32_t *)(scratch + o_nd), *const dc = (uint32_t *)(scratch + o_dc),
+             *const counted = (uint32_t *)(scratch + o_jc), *const gh = (uint32_t *)(scratch + o_gh),
+             *const mask = (uint32_t *)(scratch + o_mask), *const bh = (uint32_t *)(scratch + o_bh);
+    uint32_t *gc = (uint32_t *)(scratch + o_ga), *above = (uint32_t *)(scratch + o_gb);  // this level's counts, the last's
     uint16_t *const fr_pos = (uint16_t *)(scratch + o_fr), *const rank = (uint16_t *)(scratch + o_rank);
-    Item *const d_items = (Item *)(scratch + o_items);
     BigCut *const cuts = (BigCut *)(scratch + o_cuts);
     uint32_t *pin = (uint32_t *)(scratch + o_pa), *pout = (uint32_t *)(scratch + o_pb);
     hipLaunchKernelGGL(identity_kernel, dim3((uint32_t)std::min<uint64_t>((n + kBlock - 1) / kBlock, 4096)),
@@ -1106,6 +1130,7 @@ int tree_build_impl(const uint64_t *d_db, uint64_t n, const qd_build_params *par
     std::vector<uint32_t> count{(uint32_t)n};
     std::vector<int32_t> child{-1, -1};
     std::vector<uint32_t> level_first{0};
+    std::vector<uint32_t> last_big;  // per pair of the level's nodes, the parent's slot (kNoKey: not large)
     uint64_t lv0 = 0, lv1 = 1;
     while (lv0 < lv1) {
         if (abort_requested()) {  // between levels: nothing of this level is queued yet
@@ -1125,18 +1150,52 @@ int tree_build_impl(const uint64_t *d_db, uint64_t n, const qd_build_params *par
         if (small.empty() && big.empty()) break;
         QD_HIP_CHECK(hipMemcpyAsync(pout, pin, n * sizeof(uint32_t), hipMemcpyDeviceToDevice, s));
         const size_t nsplit = small.size() + big.size();
+        std::vector<Item> items, count_items;
+        std::vector<CountSource> sources;
+        std::vector<uint64_t> jobs;  // the counted nodes' begins
+        auto add_items = [](std::vector<Item> &to, size_t slot, uint32_t m) {
+            for (uint32_t f = 0; f < m; f += kChunk) to.push_back({(uint32_t)slot, f, std::min(kChunk, m - f), 0});
+        };
+        for (size_t i = 0; i < big.size(); i++) {
+            const uint32_t node = big[i];
+            add_items(items, i, count[node]);
+            if (node == 0) {  // the root is counted itself
+                sources.push_back({0, kNoKey});
+                jobs.push_back(0);
+                add_items(count_items, 0, count[0]);
+                continue;
+            }
+            // a level's nodes are pairs of siblings; the pair's first large node starts its job
+            const uint64_t first = lv0 + ((node - lv0) & ~1ull), few = first + (count[first + 1] < count[first] ? 1 : 0);
+            if (node == first || count[first] <= kSmall) {
+                add_items(count_items, jobs.size(), count[few]);
+                jobs.push_back(begin[few]);
+            }
+            sources.push_back({(uint32_t)jobs.size() - 1, node == few ? kNoKey : last_big[(first - lv0) / 2]});
+        }
+        std::vector<char> up;
+        auto put = [&](const void *from, size_t b) {
+            const size_t at = up.size();
+            up.resize((at + b + 15) & ~(size_t)15);
+            if (b) memcpy(up.data() + at, from, b);
+            return at;
+        };
         std::vector<uint64_t> hb(nsplit);
         std::vector<uint32_t> hc(nsplit);
-        for (size_t i = 0; i < small.size(); i++) {
-            hb[i] = begin[small[i]];
-            hc[i] = count[small[i]];
+        for (size_t i = 0; i < nsplit; i++) {
+            const uint32_t node = i < small.size() ? small[i] : big[i - small.size()];
+            hb[i] = begin[node];
+            hc[i] = count[node];
         }
-        for (size_t i = 0; i < big.size(); i++) {
-            hb[small.size() + i] = begin[big[i]];
-            hc[small.size() + i] = count[big[i]];
-        }
-        QD_HIP_CHECK(hipMemcpyAsync(d_begin, hb.data(), nsplit * 8, hipMemcpyHostToDevice, s));
-        QD_HIP_CHECK(hipMemcpyAsync(d_count, hc.data(), nsplit * 4, hipMemcpyHostToDevice, s));
+        const size_t u_begin = put(hb.data(), nsplit * 8), u_count = put(hc.data(), nsplit * 4),
+                     u_items = put(items.data(), items.size() * sizeof(Item)),
+                     u_cit = put(count_items.data(), count_items.size() * sizeof(Item)),
+                     u_jobs = put(jobs.data(), jobs.size() * 8),
+                     u_src = put(sources.data(), sources.size() * sizeof(CountSource));
+        if (up.size() > max_up) return fail(QD_ERR_DEVICE, "tree build: level lists past their bound");
+        QD_HIP_CHECK(hipMemcpyAsync(d_up, up.data(), up.size(), hipMemcpyHostToDevice, s));
+        const uint64_t *const d_begin = (const uint64_t *)(d_up + u_begin);
+        const uint32_t *const d_count = (const uint32_t *)(d_up + u_count);
         auto split = [&](auto kernel, uint32_t threads, size_t first, size_t last) {
             if (first < last)
                 hipLaunchKernelGGL(kernel, dim3((uint32_t)(last - first)), dim3(threads), 0, s, db4, pin, pout,
@@ -1146,51 +1205,56 @@ int tree_build_impl(const uint64_t *d_db, uint64_t n, const qd_build_params *par
         split(split_small_kernel<4, kMid, false>, 256, nkept, nmid);
         split(split_small_kernel<8, kSmall, false>, 512, nmid, small.size());
         QD_HIP_CHECK(hipGetLastError());
-        std::vector<Item> items;  // (the uploads' host copies live until the wait below)
-        if (!big.empty()) {
-            const size_t nbig = big.size();
-            for (size_t i = 0; i < nbig; i++) {
-                const uint32_t m = count[big[i]];
-                for (uint32_t f = 0; f < m; f += kChunk) items.push_back({(uint32_t)i, f, std::min(kChunk, m - f), 0});
-            }
-            const size_t ni = items.size();
-            QD_HIP_CHECK(hipMemcpyAsync(d_items, items.data(), ni * sizeof(Item), hipMemcpyHostToDevice, s));
-            QD_HIP_CHECK(hipMemsetAsync(gc, 0, nbig * QD_BITS * 4, s));
-            const uint64_t *bbeg = d_begin + small.size();
-            const uint32_t *bcnt = d_count + small.size();
-            uint32_t *bnd_out = d_nd + small.size();
-            hipLaunchKernelGGL(big_count_kernel, dim3((uint32_t)ni), dim3(kBlock), 0, s, db4, pin, bbeg, d_items,
-                               gc);
-            // with the least popular bits; then, where they reach too few
-            // members, with all bits (elsewhere these kernels end at once)
-            for (uint32_t again = 0; again < 2; again++) {
-                hipLaunchKernelGGL(big_band_kernel, dim3((uint32_t)nbig), dim3(1024), 0, s, gc, bcnt,
-                                   again ? 0u : kLambdaBig, mask, bh, cuts);
-                hipLaunchKernelGGL(big_first_kernel, dim3((uint32_t)ni), dim3(kBlock), 0, s, db4, pin, bbeg, d_items,
-                                   mask, cuts, again, fr_pos, bh);
-                hipLaunchKernelGGL(big_rank_kernel, dim3((uint32_t)nbig), dim3(1024), 0, s, gc, bcnt, mask, bh,
-                                   again, rank, gh, cuts, bnd_out);
-                hipLaunchKernelGGL(big_refine_kernel, dim3((uint32_t)ni), dim3(kBlock), 0, s, db4, pin, bbeg, d_items,
-                                   rank, mask, cuts, again, fr_pos, gh);
-                hipLaunchKernelGGL(big_cut_kernel, dim3((uint32_t)nbig), dim3(kBlock), 0, s, gh, bcnt, again, cuts,
-                                   bnd_out);
-            }
-            hipLaunchKernelGGL(big_dcount_kernel, dim3((uint32_t)ni), dim3(kBlock), 0, s, bbeg, d_items, cuts,
-                               fr_pos, dc);
+        const size_t nbig = big.size(), ni = items.size();
+        const Item *const d_items = (const Item *)(d_up + u_items);
+        const uint64_t *const bbeg = d_begin + small.size();
+        const uint32_t *const bcnt = d_count + small.size();
+        uint32_t *const bnd_out = d_nd + small.size(), *const any_redo = d_nd + nsplit;
+        // with the least popular bits, or, where they reach too few members, with all
+        auto split_big = [&](uint32_t again) {
+            hipLaunchKernelGGL(big_band_kernel, dim3((uint32_t)nbig), dim3(1024), 0, s,
+                               (const CountSource *)(d_up + u_src), counted, above, gc, bcnt, again ? 0u : kLambdaBig,
+                               mask, bh, cuts, any_redo);
+            hipLaunchKernelGGL(big_first_kernel, dim3((uint32_t)ni), dim3(kBlock), 0, s, db4, pin, bbeg, d_items, mask,
+                               cuts, again, fr_pos, bh);
+            hipLaunchKernelGGL(big_rank_kernel, dim3((uint32_t)nbig), dim3(1024), 0, s, gc, bcnt, mask, bh, again,
+                               rank, gh, cuts, bnd_out, any_redo);
+            hipLaunchKernelGGL(big_refine_kernel, dim3((uint32_t)ni), dim3(kBlock), 0, s, db4, pin, bbeg, d_items,
+                               rank, mask, cuts, again, fr_pos, gh);
+            hipLaunchKernelGGL(big_cut_kernel, dim3((uint32_t)nbig), dim3(kBlock), 0, s, gh, bcnt, again, cuts,
+                               bnd_out);
+            hipLaunchKernelGGL(big_dcount_kernel, dim3((uint32_t)ni), dim3(kBlock), 0, s, bbeg, d_items, cuts, fr_pos,
+                               dc);
             hipLaunchKernelGGL(big_scatter_kernel, dim3((uint32_t)ni), dim3(kBlock), 0, s, pin, pout, bbeg, bcnt,
                                d_items, cuts, bnd_out, fr_pos, dc);
+        };
+        if (nbig) {
+            QD_HIP_CHECK(hipMemsetAsync(counted, 0, jobs.size() * QD_BITS * 4, s));
+            hipLaunchKernelGGL(big_count_kernel, dim3((uint32_t)count_items.size()), dim3(kBlock), 0, s, db4, pin,
+                               (const uint64_t *)(d_up + u_jobs), (const Item *)(d_up + u_cit), counted);
+            split_big(0);
             QD_HIP_CHECK(hipGetLastError());
         }
-        std::vector<uint32_t> hnd(nsplit);
-        QD_HIP_CHECK(hipMemcpyAsync(hnd.data(), d_nd, nsplit * 4, hipMemcpyDeviceToHost, s));
+        std::vector<uint32_t> hnd(nsplit + 1, 0);
+        const size_t n_back = (nsplit + (nbig ? 1 : 0)) * 4;  // and the flag of a large node's second try
+        QD_HIP_CHECK(hipMemcpyAsync(hnd.data(), d_nd, n_back, hipMemcpyDeviceToHost, s));
         QD_HIP_CHECK(hipStreamSynchronize(s));
+        if (hnd[nsplit]) {
+            split_big(1);
+            QD_HIP_CHECK(hipGetLastError());
+            QD_HIP_CHECK(hipMemcpyAsync(hnd.data(), d_nd, n_back, hipMemcpyDeviceToHost, s));
+            QD_HIP_CHECK(hipStreamSynchronize(s));
+        }
         // children in breadth-first order: parents in id order, similar first
-        std::vector<uint32_t> nd_of(lv1 - lv0, 0);
+        std::vector<uint32_t> nd_of(lv1 - lv0, 0), slot_of(lv1 - lv0, kNoKey);
         for (size_t i = 0; i < nsplit; i++) nd_of[(i < small.size() ? small[i] : big[i - small.size()]) - lv0] = hnd[i];
+        for (size_t i = 0; i < nbig; i++) slot_of[big[i] - lv0] = (uint32_t)i;
+        last_big.clear();
         const uint64_t next0 = begin.size();
         for (uint64_t node = lv0; node < lv1; node++) {
             const uint32_t nd = nd_of[node - lv0], m = count[node];
             if (nd == 0 || nd >= m) continue;  // no split possible: the node stays a leaf
+            last_big.push_back(slot_of[node - lv0]);
             const int32_t sid = (int32_t)begin.size();
             begin.push_back(begin[node]);
             count.push_back(m - nd);
@@ -1204,6 +1268,7 @@ int tree_build_impl(const uint64_t *d_db, uint64_t n, const qd_build_params *par
             child.push_back(-1);
         }
         std::swap(pin, pout);
+        std::swap(gc, above);
         lv0 = next0;
         lv1 = begin.size();
         if (lv1 > lv0) level_first.push_back((uint32_t)lv0);
