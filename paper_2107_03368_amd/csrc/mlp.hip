@@ -623,8 +623,9 @@ __global__ __launch_bounds__(kBlock) void dw2_sum_kernel(const float *__restrict
 // 256.  It walks the half tiles (32 pairs, as the masks are kept) its chunk
 // meets; pairs outside the chunk are masked out.  Wave w owns units 32w ..
 // +31 as everywhere here; d2 is formed once per half tile, as the left
-// operand in LDS.  Bound by the latency of a half tile's loads; 307,000 pairs
-// 0.25 ms against 0.63 ms for a GEMM and a reduction over its stored result.
+// operand in LDS.  Bound by the chain of a half tile (d2, barrier, multiply), the
+// next half tile's loads being in flight meanwhile (0.25 ms without); 307,000 pairs
+// 0.21 ms against 0.63 ms for a GEMM and a reduction over its stored result.
 constexpr uint32_t kL1PartLen = (NF + 1) * H;  // gf[NF][H], su[H]
 // Chunks per query: enough blocks to fill the chip, more only for few queries.
 inline uint32_t l1_chunks(uint32_t nq) {
@@ -660,38 +661,45 @@ __global__ __launch_bounds__(kMlpBlock, 2) void layer1_partial_kernel(
 #pragma unroll
             for (int k = 0; k < 8; k++) wf[k][n] = load_frag(w + OFF_W2 + (size_t)(col + 16 * n) * H + 32 * k + 8 * lg);
         }
-        int buf = 0;
-        for (uint64_t x = p0 / 32; x * 32 < p1; x++, buf ^= 1) {
-            // this lane's pairs (m, r) of the half tile that lie in the chunk
-            u64 in[2][4];
-            float d[2][4];
+        // a half tile's ds and features (row = feature, k of step (m, r) = the
+        // lane group's pair), fetched one half tile ahead
+        float4 nd[2];
+        float nf[2][2][4];
+        auto fetch = [&](uint64_t x) {
 #pragma unroll
             for (int m = 0; m < 2; m++) {
-                const float4 v = *reinterpret_cast<const float4 *>(ds + x * 32 + 16 * m + 4 * lg);
-                d[m][0] = v.x;
-                d[m][1] = v.y;
-                d[m][2] = v.z;
-                d[m][3] = v.w;
-#pragma unroll
-                for (int r = 0; r < 4; r++) {
-                    const uint64_t p = x * 32 + 16 * m + 4 * lg + r;
-                    in[m][r] = ballot(p >= p0 && p < p1);
-                }
-            }
-            // features: row = feature, k of step (m, r) = the lane group's pair
-            float f[2][2][4];
-#pragma unroll
-            for (int m = 0; m < 2; m++)
+                nd[m] = *reinterpret_cast<const float4 *>(ds + x * 32 + 16 * m + 4 * lg);
 #pragma unroll
                 for (int r = 0; r < 4; r++) {
                     uint64_t p = x * 32 + 16 * m + 4 * lg + r;
                     p = p < n_pairs ? p : n_pairs - 1;
 #pragma unroll
-                    for (int a = 0; a < 2; a++) {
-                        const float v = feat[p * NF + 16 * a + li];
-                        f[a][m][r] = __builtin_amdgcn_inverse_ballot_w64(in[m][r]) ? v : 0.f;
-                    }
+                    for (int a = 0; a < 2; a++) nf[a][m][r] = feat[p * NF + 16 * a + li];
                 }
+            }
+        };
+        int buf = 0;
+        fetch(p0 / 32);
+        for (uint64_t x = p0 / 32; x * 32 < p1; x++, buf ^= 1) {
+            // this lane's pairs (m, r) of the half tile that lie in the chunk
+            u64 in[2][4];
+            float d[2][4], f[2][2][4];
+#pragma unroll
+            for (int m = 0; m < 2; m++) {
+                d[m][0] = nd[m].x;
+                d[m][1] = nd[m].y;
+                d[m][2] = nd[m].z;
+                d[m][3] = nd[m].w;
+#pragma unroll
+                for (int r = 0; r < 4; r++) {
+                    const uint64_t p = x * 32 + 16 * m + 4 * lg + r;
+                    in[m][r] = ballot(p >= p0 && p < p1);
+#pragma unroll
+                    for (int a = 0; a < 2; a++)
+                        f[a][m][r] = __builtin_amdgcn_inverse_ballot_w64(in[m][r]) ? nf[a][m][r] : 0.f;
+                }
+            }
+            fetch((x + 1) * 32 < p1 ? x + 1 : x);
             const u64 *w1m = m1 + (x >> 1) * kMaskWords + (x & 1) * 8 * (H / 16) + 2 * wv;
             const u64 *w2m = m2 + (x >> 1) * kMaskWords + (x & 1) * 8 * (H / 16) + 2 * wv;
             uint16_t *dst = s_d2[buf];
@@ -709,6 +717,13 @@ __global__ __launch_bounds__(kMlpBlock, 2) void layer1_partial_kernel(
                     dst[(16 * (e >> 2) + 4 * lg + (e & 3)) * kStride + col + 16 * n] =
                         (uint16_t)(o[e >> 1] >> (16 * (e & 1)));
             }
+            u64 mk[2][2][4];  // h1 > 0, fetched while the multiplications run
+#pragma unroll
+            for (int m = 0; m < 2; m++)
+#pragma unroll
+                for (int r = 0; r < 4; r++)
+#pragma unroll
+                    for (int n = 0; n < 2; n++) mk[n][m][r] = w1m[(m * 4 + r) * (H / 16) + n];
             __syncthreads();  // (the other copy was read by every wave before this)
             f32x4 dz[2][2];
 #pragma unroll
@@ -731,8 +746,7 @@ __global__ __launch_bounds__(kMlpBlock, 2) void layer1_partial_kernel(
                 for (int r = 0; r < 4; r++)
 #pragma unroll
                     for (int n = 0; n < 2; n++) {
-                        const u64 mk = w1m[(m * 4 + r) * (H / 16) + n] & in[m][r];
-                        const float v = __builtin_amdgcn_inverse_ballot_w64(mk) ? dz[m][n][r] : 0.f;
+                        const float v = __builtin_amdgcn_inverse_ballot_w64(mk[n][m][r] & in[m][r]) ? dz[m][n][r] : 0.f;
                         su[n] += v;
 #pragma unroll
                         for (int a = 0; a < 2; a++) gf[a][n] = mfma_f32(f[a][m][r], v, gf[a][n]);
