@@ -1,5 +1,8 @@
-// Overlap counts on the matrix cores: for a tile of 256 queries and 256 rows
-// (database rows or bit summaries) of 4096 bits each, C[i][j] =
+// Overlap counts on the matrix cores: the encoding and the pass test that every
+// matrix kernel uses, and a tile of 256 queries x 256 rows in a workgroup (the
+// blocked search's block bounds; scan_mfma_kernel, eval_kernel and
+// objscan_kernel stream one side past the other without it).  For queries and
+// rows (database rows or bit summaries) of 4096 bits each, C[i][j] =
 // popcount(query i AND row j), the term every weighted distance and every
 // node bound of Eq. 1 is built from.  Over the 4096 bit positions this is a
 // dense {0,1} matrix product.  It runs as the FP4 (e2m1) matrix instruction
@@ -37,7 +40,8 @@
 // one runs, and a step's operands are expanded between the multiplications of
 // the step before it, so neither wave of a SIMD ever has only vector work.
 //
-// Measured (1M rows x 4,096 queries, kernel time): 7.5 ms with 16 x 16 x 128,
+// Measured with the sequential search on this tile (1M rows x 4,096 queries,
+// kernel time; streamed past each other it takes 4.6 ms): 7.5 ms with 16 x 16 x 128,
 // scales and each step's expansion before its multiplications; 6.8 ms with
 // 32 x 32 x 64 without scales; 5.8 ms with the epilogue's test by row
 // (pass_bound below); 5.4 ms with the expansion between the multiplications.
@@ -50,8 +54,7 @@
 // rows against the query's own bound lane by lane, and a minimum over the
 // rows needs no exchange until its end.
 //
-// A missing row reads as zeros.  The tile is the same whether rows are contiguous
-// (block bounds) or gathered through a list (object scores).
+// A missing row reads as zeros.
 #pragma once
 
 #include "qd.h"
@@ -166,15 +169,6 @@ __device__ __forceinline__ Quad quad_test(const v16f &acc, int g, const float4 &
 // Exact count held by an accumulator entry.
 __device__ __forceinline__ uint32_t count(float c) { return (uint32_t)c; }
 
-// Tiles in a row, streamed: while a tile's last two windows run, the next
-// tile's first two windows are loaded and stored, and the words of its first
-// step are read, so a tile that follows another starts without waiting for
-// its loads.  `Stream` carries that state from one tile to the next.
-struct Stream {
-    int cur;                 // buffer holding window 0 of the next tile to run
-    uint64_t r0[QF + RF];    // the words of that tile's first double step
-};
-
 // Rows: this thread's row (32 x 16 bytes), always a readable global row; when
 // the zero flag is set its bits count as 0 (a missing row past the end of
 // the input), read from a row of zeros, so the loaded words need no mask.  A
@@ -194,39 +188,9 @@ __device__ __forceinline__ int frag_offset(int f) {
     return (row + (lane & 31)) * RST + (lane >> 5) * 8;
 }
 
-// Stage the first two windows of a stream's first tile.
-__device__ __forceinline__ void stream_begin(const uint4 *row, bool zero, Smem &sm, Stream &st) {
-    const int tid = threadIdx.x;
-    const uint4 *src = row_or_zero(row, zero);
-#pragma unroll
-    for (int v = 0; v < 2; v++) {
-        uint2 *d = reinterpret_cast<uint2 *>(sm.rw[v] + tid * RST);
-#pragma unroll
-        for (int c = 0; c < 4; c++) {
-            const uint4 p = src[4 * v + c];
-            d[2 * c] = make_uint2(p.x, p.y);
-            d[2 * c + 1] = make_uint2(p.z, p.w);
-        }
-    }
-    __syncthreads();
-    st.cur = 0;
-#pragma unroll
-    for (int f = 0; f < QF + RF; f++) st.r0[f] = *reinterpret_cast<const uint64_t *>(sm.rw[0] + frag_offset(f));
-}
-
-// Multiply the stream's current tile (rows `row`) while staging the first two
-// windows of the next one (rows `next`, read when windows 6 and 7 load them,
-// so the hook may still set them; the current rows again after the last
-// tile: in bounds, never used).  idle (the same in a whole wave): the wave
-// stages its rows as always but multiplies nothing, its accumulators stay
-// zero (a wave whose queries hold no listed one).  hook(win) runs after window win's barrier,
-// win = 0..7, for the kernel's own work on the next tile (such as a chain of
-// dependent metadata loads, one link per window, which then never stalls a
-// wave: a whole window passes between a load and its use).
-template <class Hook>
-__device__ __forceinline__ void stream_tile(const uint4 *row, bool zero, const uint4 *const &next,
-                                            const bool &next_zero, Smem &sm, Stream &st, Acc &acc,
-                                            Hook &&hook, bool idle = false) {
+// The counts of one tile: this thread's row is `row` (zero: a missing one).
+// Every wave has read the LDS windows when it returns.
+__device__ __forceinline__ void overlap_tile(const uint4 *row, bool zero, Smem &sm, Acc &acc) {
     const int tid = threadIdx.x;
 #pragma unroll
     for (int a = 0; a < QF; a++)
@@ -250,13 +214,18 @@ __device__ __forceinline__ void stream_tile(const uint4 *row, bool zero, const u
         d[6] = make_uint2(p3.x, p3.y);
         d[7] = make_uint2(p3.z, p3.w);
     };
+    // the first two windows
+#pragma unroll
+    for (int v = 0; v < 2; v++)
+        stage(sm.rw[v], own_src[4 * v], own_src[4 * v + 1], own_src[4 * v + 2], own_src[4 * v + 3]);
+    __syncthreads();
     constexpr int kWins = 4096 / WIN;
     int roff[QF + RF];
 #pragma unroll
     for (int f = 0; f < QF + RF; f++) roff[f] = frag_offset(f);
     uint64_t r[2][QF + RF];  // the words of this double step and of the next
 #pragma unroll
-    for (int f = 0; f < QF + RF; f++) r[0][f] = st.r0[f];
+    for (int f = 0; f < QF + RF; f++) r[0][f] = *reinterpret_cast<const uint64_t *>(sm.rw[0] + roff[f]);
     // Operands of the two steps of a double step.  While a step's eight
     // multiplications run, the other step's operands are expanded between
     // them, one fragment after each, so a wave always has a multiplication to
@@ -279,21 +248,17 @@ __device__ __forceinline__ void stream_tile(const uint4 *row, bool zero, const u
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    if (!idle) {
 #pragma unroll
-        for (int f = 0; f < QF + RF; f++) expand(0, f, lo(r[0], f));
-    }
+    for (int f = 0; f < QF + RF; f++) expand(0, f, lo(r[0], f));
     // Every window runs the same code, so the compiler keeps one loop instead
     // of peeling its end (a peeled end spilled registers in the kernels).
-    int cur = st.cur;  // buffer of window win; window win + 1 is in the next, win + 2 goes to the one after
+    // (The last two stage the row's first windows again: in bounds, never used.)
+    int cur = 0;  // buffer of window win; window win + 1 is in the next, win + 2 goes to the one after
     for (int win = 0; win < kWins; win++) {
         const int nxt = cur == NBUF - 1 ? 0 : cur + 1, stg = nxt == NBUF - 1 ? 0 : nxt + 1;
         const uint8_t *buf = sm.rw[cur];
-        // window win + 2 of this tile, or window win - 6 of the next
-        const bool own = win + 2 < kWins;
-        const uint4 *src = own ? own_src : row_or_zero(next, next_zero);
-        const int nb = (4 * win + 8) & 31;
-        const uint4 n0 = src[nb], n1 = src[nb + 1], n2 = src[nb + 2], n3 = src[nb + 3];
+        const int nb = (4 * win + 8) & 31;  // window win + 2
+        const uint4 n0 = own_src[nb], n1 = own_src[nb + 1], n2 = own_src[nb + 2], n3 = own_src[nb + 3];
 #pragma unroll
         for (int s = 0; s < 4; s++) {
             // the next step's words: from this window, or the first of the next
@@ -303,29 +268,16 @@ __device__ __forceinline__ void stream_tile(const uint4 *row, bool zero, const u
             for (int f = 0; f < QF + RF; f++) r[(s + 1) & 1][f] = *reinterpret_cast<const uint64_t *>(from + roff[f]);
             // the next double step's reads go out before this one's work
             __builtin_amdgcn_sched_barrier(0);
-            if (!idle) {
-                multiply(0, [&](int f) { return hi(r[s & 1], f); });
-                multiply(1, [&](int f) { return lo(r[(s + 1) & 1], f); });
-            }
+            multiply(0, [&](int f) { return hi(r[s & 1], f); });
+            multiply(1, [&](int f) { return lo(r[(s + 1) & 1], f); });
             __builtin_amdgcn_sched_barrier(0);
         }
         // the buffer of window win - 1: every wave finished reading it before
         // the previous barrier
         stage(sm.rw[stg], n0, n1, n2, n3);
         __syncthreads();
-        hook(win);
         cur = nxt;
     }
-    st.cur = cur;
-#pragma unroll
-    for (int f = 0; f < QF + RF; f++) st.r0[f] = r[0][f];
-}
-
-// One tile on its own.
-__device__ __forceinline__ void overlap_tile(const uint4 *row, bool zero, Smem &sm, Acc &acc) {
-    Stream st;
-    stream_begin(row, zero, sm, st);
-    stream_tile(row, zero, row, zero, sm, st, acc, [](int) {});
 }
 
 }  // namespace mt

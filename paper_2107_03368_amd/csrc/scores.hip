@@ -4,12 +4,11 @@
 // each descriptor's distance (Eq. 1) to its nearest descriptor of o.
 //
 // Stage 1 groups the database rows by object (a counting sort of row ids: one
-// histogram, one scan that also numbers each object's 256-row tiles, one
-// scatter, one record per tile).  Stage 2 is a sequential search in which every row tile belongs
-// to one object: work item (256-descriptor tile, row tile) runs the shared
-// overlap tile (mfma_tile.h) on the gathered rows, takes each descriptor's
-// smallest key over the tile, reduces it over the tile's lanes and waves, and
-// folds it into minK[descriptor][object] with one atomic minimum per
+// histogram, one scan that also numbers each object's 64-row tiles, one
+// scatter, one record per tile).  Stage 2 is a sequential search on the matrix
+// cores (encoding of mfma_tile.h) in which every row tile belongs to one
+// object: a wave keeps its 64 descriptors' smallest keys over an object's tiles
+// and folds them into minK[descriptor][object] with one atomic minimum per
 // descriptor; the minimum does not depend on the order of the tiles.  Stage 3
 // gives every (query object, object) pair one thread, which adds the terms
 // minK / (wA wB) in float64, descriptor after descriptor.  Query descriptors
@@ -29,8 +28,8 @@ int popcount_rows_launch(const uint64_t *d_db, uint64_t n, uint16_t *d_pop, hipS
 namespace {
 
 constexpr int kBlock = 256;
-constexpr int MQ = mt::MA;  // descriptors per tile
-constexpr int MR = mt::MB;  // rows per tile
+constexpr int MQ = 256;  // descriptors of a batch come in multiples of it
+constexpr int MR = 64;   // rows per tile
 constexpr uint32_t kNoKey = 0xFFFFFFFFu;       // above every key (keys are < 2^24)
 constexpr uint64_t kMinKBytes = 1ull << 30;    // minK of one batch
 constexpr uint64_t kMaxBatch = 1ull << 18;     // query descriptors per batch
@@ -258,159 +257,211 @@ __global__ __launch_bounds__(kBlock) void obj_tiles_kernel(const uint64_t *__res
     }
 }
 
-// Tile (qt, rt) = (tile % n_qtiles, tile / n_qtiles) in a persistent grid:
-// workgroup x takes tiles x, x + G, ..., so the tiles running at a time share
-// their row tiles.  The tiles are streamed: the next tile's first two windows
-// are staged during the current tile's last two, and its metadata is fetched
-// during the current tile, one dependent load per window (the row tile's
-// record, the row's id, its popcount).  The metadata of consecutive tiles
-// alternates between two LDS copies, and a tile's minima go out after the
-// next tile's first barrier, so no barrier closes a tile.
-// Measured (13,700 descriptors x 1.5M rows): 38.0 ms with the 16 x 16 x 128
-// tile, 30.4 ms with the present one, each tile searching its object and
-// waiting for its first loads; 25.1 ms streamed.
-__global__ __launch_bounds__(mt::kThreads) void objscan_kernel(
-    const uint4 *__restrict__ db, const uint32_t *__restrict__ order, const uint16_t *__restrict__ tpop,
-    const uint4 *__restrict__ rec, const uint32_t *__restrict__ n_rtiles, uint32_t n_obj, const uint4 *__restrict__ q,
-    uint32_t nq, const uint16_t *__restrict__ qpop, uint32_t n_qtiles, uint32_t *__restrict__ minK) {
-    __shared__ mt::Smem sm;
-    __shared__ uint32_t s_pq[2][MQ], s_min[2][MQ];
-    __shared__ __align__(16) float s_tp[2][MR];
-    const uint32_t n_rt = *n_rtiles;
-    const int r = mt::own_row(), lane = r & 63, wq = r >> 8;  // wq: the half of the descriptors this wave multiplies
-    const bool arow = r < MQ;  // the same in a whole wave
-    // the tile (qt, rt) being fetched, and the step to the workgroup's next one
-    uint32_t qt = blockIdx.x % n_qtiles, rt = blockIdx.x / n_qtiles;
-    const uint32_t dq = gridDim.x % n_qtiles, dr = gridDim.x / n_qtiles;
-    if (rt >= n_rt) return;  // whole workgroup
-    // a lane-varying zero: keeps the record load a vector load (a scalar load
+// The smallest key of every (descriptor, object) pair, on the matrix cores: the
+// sequential search's matrix pass with the rows gathered in object order.  A
+// workgroup keeps a group of up to 256 descriptors packed in LDS; a wave streams
+// 64 rows of one object at a time from memory into the operand registers,
+// against 64 of the descriptors (2 x 2 fragments; line layout, bit order and
+// expansion as in scan_mfma_kernel, |t| counted from the words).  The work is
+// cut into units, (group, 64-row tile, 64-descriptor tile of the group); every
+// workgroup takes an equal run of row tiles and its 8 waves take the run's units
+// in turn, so with 1, 2 or 4 descriptor tiles a wave keeps its descriptors and
+// meets an object's tiles one after another: the minima stay in registers until
+// the object (or the descriptors) change, and only then go to memory.
+// Bound by the matrix units: 13,700 descriptors x 1.5M rows 23.1 ms, 7.3 PFLOP/s;
+// 25.1 ms (and 0.12 for the rows' popcounts) with a streamed 256 x 256 tile per
+// workgroup, 38.0 with tiles that waited for their loads and 16 x 16 x 128
+// instructions.
+constexpr int kScanBlock = 512, kScanWaves = kScanBlock / 64;
+constexpr uint32_t kGroupD = 256;       // descriptors of a group
+constexpr int kDescStride = 512 + 16;   // bytes per descriptor in LDS: 16-byte reads of 32 on distinct banks
+struct ScanSmem {
+    uint32_t pop[kGroupD];         // |q|
+    float tp[kScanWaves][MR];      // per wave: its rows' |t|
+};
+inline size_t scan_lds_bytes(uint32_t nq) {
+    return sizeof(ScanSmem) + (size_t)(nq < kGroupD ? (nq + 63) / 64 * 64 : kGroupD) * kDescStride;
+}
+__global__ __launch_bounds__(kScanBlock, 2) void objscan_kernel(const uint4 *__restrict__ db,
+                                                                const uint32_t *__restrict__ order,
+                                                                const uint4 *__restrict__ rec,
+                                                                const uint32_t *__restrict__ n_rtiles, uint32_t n_obj,
+                                                                const uint4 *__restrict__ q, uint32_t nq,
+                                                                uint32_t *__restrict__ minK) {
+    extern __shared__ __align__(16) uint8_t s_raw[];
+    ScanSmem &sm = *reinterpret_cast<ScanSmem *>(s_raw);
+    uint8_t *s_q = s_raw + sizeof(ScanSmem);
+    static_assert(sizeof(ScanSmem) % 16 == 0, "the descriptors are read 16 bytes at a time");
+    const uint64_t tiles = *n_rtiles;
+    const int lane = threadIdx.x & 63, wv = (int)readfirst(threadIdx.x >> 6);
+    const int li = lane & 31, lh = lane >> 5;
+    float *tpw = sm.tp[wv];
+    // a lane-varying zero: keeps the record loads vector loads (a scalar load
     // shares its completion counter with the LDS reads)
     const uint32_t vz = __builtin_amdgcn_mbcnt_lo(0u, 0u);
-    // a tile's fetch: record -> row id -> popcount (queries: popcount).  Every
-    // load is unconditional and in bounds (a row past the tile's end reads its
-    // last row and is masked when used).
-    uint4 pa, info;
-    uint32_t pb, pc, t = 0, p = 0;
-    bool ok = false;
-    uint32_t q0 = qt * MQ;  // its first descriptor
-    auto issue_a = [&]() { pa = rec[rt + vz]; };
-    auto issue_b = [&]() {
-        const uint32_t i = (uint32_t)(r & (MR - 1));
-        pb = order[info.x + (i < info.y ? i : info.y - 1)];
-    };
-    auto take_b = [&]() {
-        ok = arow ? q0 + r < nq : (uint32_t)(r - MQ) < info.y;
-        t = arow ? (ok ? q0 + r : 0) : pb;
-    };
-    auto issue_c = [&]() { pc = *((arow ? qpop : tpop) + t); };
-    auto row_of = [&]() { return (arow ? q : db) + (uint64_t)t * 32; };
-    auto publish = [&](int h) {  // read after the next barrier
-        if (arow)
-            s_pq[h][r] = ok ? p : 0;
-        else
-            s_tp[h][r - MQ] = ok ? (float)p : 32767.f;
-    };
-    if (arow) s_min[0][r] = s_min[1][r] = kNoKey;
-    // the first tile: fetched here, waiting for each load
-    issue_a();
-    info = pa;
-    issue_b();
-    take_b();
-    issue_c();
-    p = pc;
-    const uint4 *row = row_of();
-    bool cur_ok = ok;
-    uint32_t cur_q0 = q0, cur_o = info.z, old_q0 = 0, old_o = 0;
-    int h = 0;  // the current tile's metadata copy
-    publish(h);
-    bool first = true;
-    mt::Stream st;
-    mt::stream_begin(row, !cur_ok, sm, st);  // its barrier also publishes the metadata
-    // the previous tile's minima: every wave has folded its own into s_min
-    // before the barrier that precedes this
-    auto store_minima = [&](int hh) {
-        if (arow && old_q0 + r < nq) atomicMin(&minK[(uint64_t)(old_q0 + r) * n_obj + old_o], s_min[hh][r]);
-        if (arow) s_min[hh][r] = kNoKey;
-    };
-    for (;;) {
-        const uint32_t wrap = qt + dq >= n_qtiles ? n_qtiles : 0;
-        const uint32_t rn = rt + dr + (wrap ? 1u : 0u);
-        const bool more = rn < n_rt;
-        if (more) {  // (after the last tile: this one again, unused)
-            qt += dq - wrap;
-            rt = rn;
+    // this workgroup's units [ua, ub) of all groups' (each group: its
+    // descriptor tiles x tiles), rounded down to whole row tiles at both ends
+    const uint32_t n_qt = (nq + 63) / 64;
+    const uint64_t units = tiles * n_qt;
+    const uint64_t ua = units / gridDim.x * blockIdx.x + min((uint64_t)blockIdx.x, units % gridDim.x);
+    const uint64_t ub = ua + units / gridDim.x + (blockIdx.x < units % gridDim.x ? 1 : 0);
+    const uint64_t per_group = 4 * tiles;  // units of a full group
+    if (tiles == 0) return;                // whole workgroup
+    for (uint64_t g0 = ua / per_group * per_group; g0 < ub; g0 += per_group) {
+        const uint32_t q0 = (uint32_t)(g0 / per_group) * kGroupD;  // the group's first descriptor
+        const uint32_t gqt = min(4u, n_qt - q0 / 64);              // its descriptor tiles
+        const uint64_t ra = (ua > g0 ? ua - g0 : 0) / gqt;         // its row tiles here
+        const uint64_t rb = min((ub - g0) / gqt, tiles);
+        __syncthreads();  // every wave is done with the group before
+        for (uint32_t e = threadIdx.x; e < gqt * 64 * 32; e += kScanBlock) {
+            const uint32_t qi = q0 + (e >> 5);
+            const uint4 x = qi < nq ? q[(uint64_t)qi * 32 + (e & 31)] : make_uint4(0, 0, 0, 0);
+            *reinterpret_cast<uint4 *>(s_q + (size_t)(e >> 5) * kDescStride + (e & 31) * 16) = x;
+            const uint32_t pq = sum32_half(popc4(x));  // a half wave holds one descriptor
+            if ((e & 31) == 0) sm.pop[e >> 5] = pq;
         }
-        q0 = qt * MQ;
-        const uint4 *nrow = row;
-        bool nok = false, nzero = true;
-        // the waves of descriptors 128..255 have nothing to multiply in a
-        // batch's short last tile
-        const bool idle = wq == 1 && nq - cur_q0 <= (uint32_t)(MQ / 2);
-        mt::Acc acc;
-        mt::stream_tile(row, !cur_ok, nrow, nzero, sm, st, acc, [&](int win) {
-            if (win == 0 && !first) store_minima(h ^ 1);
-            if (win == 1) info = pa;
-            if (win == 2) take_b();
-            if (win == 3) {
-                p = pc;
-                nrow = row_of();
-                nok = ok;
-                nzero = !more || !ok;
+        __syncthreads();
+        // the wave's units wv, wv + 8, ... of (rb - ra) row tiles x gqt descriptor tiles
+        const uint64_t un = rb > ra ? (rb - ra) * gqt : 0;
+        uint64_t u = (uint64_t)wv;
+        if (u >= un) continue;
+        uint32_t qt = (uint32_t)wv % gqt;
+        uint64_t rt = ra + (uint32_t)wv / gqt;
+        // a tile's record, then its rows: fragment b's is lane li's (past the
+        // end: the tile's last row, masked in the test)
+        auto row_of = [&](const uint4 &r, int b) {
+            const uint32_t i = 32 * b + (uint32_t)li;
+            return order[r.x + (i < r.y ? i : r.y - 1)];
+        };
+        uint4 v[2][2][4];  // [line parity][fragment][piece pair]
+        auto load = [&](const uint32_t (&row)[2], int L, uint4 (&x)[2][4]) {
+#pragma unroll
+            for (int b = 0; b < 2; b++) {
+                const uint4 *src = db + (uint64_t)row[b] * 32 + 8 * L + lh;
+#pragma unroll
+                for (int i = 0; i < 4; i++) x[b][i] = src[2 * i];
             }
-            issue_a();
-            issue_b();
-            issue_c();
-        }, idle);
-        first = false;
-
-        // this lane's 4 descriptors x 32 rows: smallest key per descriptor.
-        // K = |q|*wB - (C*(wA + wB) - |t|*wA), so the smallest K is |q|*wB
-        // minus the largest C*(wA + wB) - |t|*wA; rows past the tile's end
-        // have |t| = 32767, which no real row's value can lose to.  In fp32
-        // every value is exact: integers below 2^24, but for C = 4096 and
-        // |q| = 4096, where C*(wA + wB) = 4096 * 4097 < 2^25 is even.
-        float wa[mt::QF], sw[mt::QF], vmax[mt::QF];
+        };
+        auto q_row = [&](uint32_t t) { return s_q + (size_t)(t * 64 + li) * kDescStride + lh * 16; };
+        auto word = [](const uint4 &x, int c) { return c == 0 ? x.x : c == 1 ? x.y : c == 2 ? x.z : x.w; };
+        const uint8_t *qrow = q_row(qt);
+        uint4 qw[2][2];              // descriptors' pieces: [piece pair parity][fragment]
+        mt::v8i qv[2][2], rv[2][2];  // operands: [step parity][fragment]
+        uint32_t tp[2] = {0, 0};
+        auto read_q = [&](const uint8_t *row, int pair) {
 #pragma unroll
-        for (int a = 0; a < mt::QF; a++) {
-            const uint32_t pq = s_pq[h][mt::acc_query(a)];
-            const uint32_t w = pq > 1 ? pq : 1;
-            wa[a] = -(float)w;
-            sw[a] = (float)(w + ((QD_BITS - pq) > 1 ? QD_BITS - pq : 1));
-            vmax[a] = -1e30f;
-        }
-#pragma unroll
-        for (int b = 0; b < mt::RF; b++)
-#pragma unroll
-            for (int g = 0; g < 4; g++) {
-                const float4 t4 = *reinterpret_cast<const float4 *>(&s_tp[h][mt::quad_row(b, g)]);
-                const float tp[4] = {t4.x, t4.y, t4.z, t4.w};
-#pragma unroll
-                for (int a = 0; a < mt::QF; a++)
-#pragma unroll
-                    for (int e = 0; e < 4; e++)
-                        vmax[a] = fmaxf(vmax[a], __builtin_fmaf(tp[e], wa[a], acc[a][b][4 * g + e] * sw[a]));
+            for (int a = 0; a < 2; a++)
+                qw[pair & 1][a] = *reinterpret_cast<const uint4 *>(row + 32 * a * kDescStride + pair * 32);
+        };
+        auto expand = [&](int S, int f) {  // fragment f of step S (mod 64): rows 0, 1, then descriptors
+            const int L = (S >> 4) & 3, i = (S >> 2) & 3, c = S & 3;
+            if (f < 2) {
+                const uint32_t x = word(v[L & 1][f][i], c);
+                rv[S & 1][f] = mt::expand_r(x);
+                tp[f] += __popc(x);
+            } else {
+                qv[S & 1][f - 2] = mt::expand_q(word(qw[(4 * L + i) & 1][f - 2], c));
             }
+        };
+        // the minima so far: K = |q|*wB - (C*(wA + wB) - |t|*wA), so the smallest
+        // K is |q|*wB minus the largest C*(wA + wB) - |t|*wA.  In fp32 every
+        // value is exact: integers below 2^24, but for C = |q| = 4096, where
+        // C*(wA + wB) = 4096 * 4097 < 2^25 is even.
+        float vmax[2] = {-1e38f, -1e38f};
+        auto store_minima = [&](uint32_t o) {
 #pragma unroll
-        for (int a = 0; a < mt::QF; a++) {
-            const int ai = mt::acc_query(a);
-            const float v = fmaxf(vmax[a], __shfl_xor(vmax[a], 32));  // the other 32 rows of the wave
-            const uint32_t pq = s_pq[h][ai];
-            const int32_t m = (int32_t)(pq * ((QD_BITS - pq) > 1 ? QD_BITS - pq : 1)) - (int32_t)v;
-            if (lane < 32) atomicMin(&s_min[h][ai], (uint32_t)m);  // the 4 waves of this descriptor half
+            for (int a = 0; a < 2; a++) {
+                const uint32_t qs = qt * 64 + 32 * a + li, pq = sm.pop[qs];
+                const float m = fmaxf(vmax[a], __shfl_xor(vmax[a], 32));  // the other 16 rows of each fragment
+                const int32_t K = (int32_t)(pq * ((QD_BITS - pq) > 1 ? QD_BITS - pq : 1)) - (int32_t)m;
+                if (lh == 0 && q0 + qs < nq) atomicMin(&minK[(uint64_t)(q0 + qs) * n_obj + o], (uint32_t)K);
+                vmax[a] = -1e38f;
+            }
+        };
+        uint4 cur = rec[rt + vz];
+        uint32_t row[2];
+#pragma unroll
+        for (int b = 0; b < 2; b++) row[b] = row_of(cur, b);
+        load(row, 0, v[0]);
+        read_q(qrow, 0);
+#pragma unroll
+        for (int f = 0; f < 4; f++) expand(0, f);
+        for (;;) {
+            // the wave's next unit (after the last: this one again, unused)
+            const bool more = u + kScanWaves < un;
+            uint32_t nqt = qt + kScanWaves % gqt;
+            const uint32_t wrap = nqt >= gqt ? 1 : 0;
+            nqt -= wrap ? gqt : 0;
+            const uint64_t nrt = more ? rt + kScanWaves / gqt + wrap : rt;  // row tile, then descriptor tile
+            const uint8_t *nqrow = q_row(more ? nqt : qt);
+            uint4 nrec;
+            uint32_t nrow[2], tcur[2];
+            mt::v16f acc[2][2];
+#pragma unroll
+            for (int L = 0; L < 4; L++) {
+                if (L == 0) nrec = rec[nrt + vz];
+                if (L == 2) {
+#pragma unroll
+                    for (int b = 0; b < 2; b++) nrow[b] = row_of(nrec, b);
+                }
+                load(L < 3 ? row : nrow, (L + 1) & 3, v[(L + 1) & 1]);
+#pragma unroll
+                for (int st = 0; st < 16; st++) {
+                    const int S = 16 * L + st;
+                    if ((S & 3) == 0) read_q(S < 60 ? qrow : nqrow, (S / 4 + 1) & 15);
+                    if (S == 63) {  // from here on the next unit's rows are counted
+                        tcur[0] = tp[0];
+                        tcur[1] = tp[1];
+                        tp[0] = tp[1] = 0;
+                    }
+#pragma unroll
+                    for (int m = 0; m < 4; m++) {
+                        const mt::v16f zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f,
+                                               0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                        acc[m >> 1][m & 1] =
+                            mt::mma32(rv[S & 1][m & 1], qv[S & 1][m >> 1], S == 0 ? zero : acc[m >> 1][m & 1]);
+                        expand(S + 1, m);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+            }
+            // |t| of the tile's rows, to every lane through the wave's LDS
+#pragma unroll
+            for (int b = 0; b < 2; b++) {
+                tcur[b] += (uint32_t)__shfl_xor((int)tcur[b], 32);
+                if (lh == b) tpw[32 * b + li] = 32 * b + (uint32_t)li < cur.y ? (float)tcur[b] : mt::kNoRow;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+            for (int a = 0; a < 2; a++) {
+                const uint32_t pq = sm.pop[qt * 64 + 32 * a + li];  // this lane's descriptor
+                const uint32_t wa = pq > 1 ? pq : 1;
+                const float nwa = -(float)wa, sw = (float)(wa + ((QD_BITS - pq) > 1 ? QD_BITS - pq : 1));
+#pragma unroll
+                for (int b = 0; b < 2; b++)
+#pragma unroll
+                    for (int g = 0; g < 4; g++) {
+                        const float4 t4 = *reinterpret_cast<const float4 *>(tpw + 32 * b + 8 * g + 4 * lh);
+                        const float t[4] = {t4.x, t4.y, t4.z, t4.w};
+#pragma unroll
+                        for (int e = 0; e < 4; e++)
+                            vmax[a] = fmaxf(vmax[a], __builtin_fmaf(t[e], nwa, acc[a][b][4 * g + e] * sw));
+                    }
+            }
+            const uint32_t o = readfirst(cur.z);
+            if (!more || nqt != qt || readfirst(nrec.z) != o) store_minima(o);
+            if (!more) break;
+            u += kScanWaves;
+            qt = nqt;
+            rt = nrt;
+            qrow = nqrow;
+            cur = nrec;
+            row[0] = nrow[0];
+            row[1] = nrow[1];
         }
-        old_q0 = cur_q0;
-        old_o = cur_o;
-        if (!more) break;
-        h ^= 1;
-        ok = nok;
-        publish(h);  // the other copy: this tile's may still be read
-        row = nrow;
-        cur_ok = nok;
-        cur_q0 = q0;
-        cur_o = info.z;
     }
-    __syncthreads();
-    store_minima(h);
 }
 
 // Thread (g, o) for the query objects that overlap this batch, descriptors
@@ -541,9 +592,8 @@ extern "C" int qd_object_scores(const uint64_t *d_db, uint64_t n, const uint16_t
     if (nb_max < (uint64_t)MQ) nb_max = MQ;
     if (nb_max > kMaxBatch) nb_max = kMaxBatch;
     if (nb_max > n_qdesc) nb_max = n_qdesc;
-    // scratch: row order, row popcounts, counts / cursors, offsets, batch popcounts, minK
-    const size_t o_order = 0, o_tpop = o_order + ((n * 4 + 255) & ~255ull);
-    const size_t o_cnt = o_tpop + ((n * 2 + 255) & ~255ull);
+    // scratch: row order, counts / cursors, offsets, batch popcounts, minK
+    const size_t o_order = 0, o_cnt = o_order + ((n * 4 + 255) & ~255ull);
     const size_t o_cur = o_cnt + (((size_t)n_obj * 4 + 255) & ~255ull);
     const size_t o_roff = o_cur + (((size_t)n_obj * 4 + 255) & ~255ull);
     const size_t o_toff = o_roff + ((((size_t)n_obj + 1) * 8 + 255) & ~255ull);
@@ -556,7 +606,6 @@ extern "C" int qd_object_scores(const uint64_t *d_db, uint64_t n, const uint16_t
     char *ws = nullptr;
     QD_HIP_CHECK(hipMallocAsync((void **)&ws, bytes, s));
     uint32_t *order = reinterpret_cast<uint32_t *>(ws + o_order);
-    uint16_t *tpop = reinterpret_cast<uint16_t *>(ws + o_tpop);
     uint32_t *cnt = reinterpret_cast<uint32_t *>(ws + o_cnt);
     uint32_t *cursor = reinterpret_cast<uint32_t *>(ws + o_cur);
     uint64_t *roff = reinterpret_cast<uint64_t *>(ws + o_roff);
@@ -594,8 +643,6 @@ extern "C" int qd_object_scores(const uint64_t *d_db, uint64_t n, const uint16_t
                                n_obj, rec);
         }
         if (hipGetLastError() != hipSuccess) return done(fail(QD_ERR_DEVICE, "object grouping launch failed"));
-        const int rc = popcount_rows_launch(d_db, n, tpop, s);
-        if (rc != QD_OK) return done(rc);
     }
     for (uint64_t d0 = 0; d0 < n_qdesc; d0 += nb_max) {
         const uint32_t nb = (uint32_t)(n_qdesc - d0 < nb_max ? n_qdesc - d0 : nb_max);
@@ -606,12 +653,12 @@ extern "C" int qd_object_scores(const uint64_t *d_db, uint64_t n, const uint16_t
             const uint64_t m = (uint64_t)nb * n_obj;
             hipLaunchKernelGGL(fill_u32_kernel, dim3(blocks_for(m, cap)), dim3(kBlock), 0, s, minK, m, kNoKey);
             KernelTimer timer("object_scan", s);
-            const uint32_t n_qtiles = (nb + MQ - 1) / MQ;
-            // persistent: one workgroup per CU (the tile's LDS and registers leave room for one)
-            const uint64_t grid = std::min<uint64_t>((uint64_t)n_qtiles * row_tiles_max, (uint64_t)device_cus());
-            hipLaunchKernelGGL(objscan_kernel, dim3((uint32_t)grid), dim3(mt::kThreads), 0, s,
-                               reinterpret_cast<const uint4 *>(d_db), order, tpop, rec, toff + n_obj, n_obj,
-                               reinterpret_cast<const uint4 *>(qb), nb, qpop, n_qtiles, minK);
+            // persistent: one workgroup per CU (LDS and registers leave room for one)
+            const uint64_t n_units = (uint64_t)((nb + 63) / 64) * row_tiles_max;
+            const uint64_t grid = std::min<uint64_t>((n_units + kScanWaves - 1) / kScanWaves, (uint64_t)device_cus());
+            hipLaunchKernelGGL(objscan_kernel, dim3((uint32_t)grid), dim3(kScanBlock), scan_lds_bytes(nb), s,
+                               reinterpret_cast<const uint4 *>(d_db), order, rec, toff + n_obj, n_obj,
+                               reinterpret_cast<const uint4 *>(qb), nb, minK);
             if (hipGetLastError() != hipSuccess) return done(fail(QD_ERR_DEVICE, "object scan launch failed"));
         }
         {
