@@ -932,12 +932,10 @@ __global__ __launch_bounds__(kEvBlock, 2) void eval_kernel(const uint4 *__restri
         nqe = 0;
     };
     auto word = [](const uint4 &x, int c) { return c == 0 ? x.x : c == 1 ? x.y : c == 2 ? x.z : x.w; };
-    for (;;) {
-        __syncthreads();  // every wave is done with the item before
-        if (t == 0) s_item = atomicAdd(next, 1u);
-        __syncthreads();
-        const uint32_t item = readfirst(s_item);
-        if (item >= n_items) break;
+    // the first item by the workgroup's number (a pass without work, as most of a
+    // captured search's are, ends here), the others from the counter
+    uint32_t item = blockIdx.x;
+    while (item < n_items) {
         const uint32_t xe = min((item >> 1) * per + per, total);
         for (uint32_t x = (item >> 1) * per; x < xe;) {
             // the item's tiles of one block: consecutive parts of its list, all but the last full
@@ -1109,6 +1107,10 @@ __global__ __launch_bounds__(kEvBlock, 2) void eval_kernel(const uint4 *__restri
                 }
             }
         }
+        __syncthreads();  // every wave has read this item's number
+        if (t == 0) s_item = gridDim.x + atomicAdd(next, 1u);
+        __syncthreads();
+        item = readfirst(s_item);
     }
     flush();
 }
