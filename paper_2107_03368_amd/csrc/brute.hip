@@ -323,14 +323,14 @@ __global__ __launch_bounds__(kBlock) void merge_emit_kernel(const u64 *__restric
         if (h[i] != KEY_NONE && h[i] <= U1) cand[atomicAdd(&nleft, 1u)] = h[i];
     __syncthreads();
     const uint32_t nh = nleft;
-    u64 U = KEY_NONE;
+    u64 U = U1;  // (the k heads themselves where exactly k are left)
     if (nh > k) {
         sort_keys(cand, nh);
         U = cand[k - 1];
     }
 #pragma unroll
     for (uint32_t i = 0; i < kHeads; i++)
-        if (h[i] != KEY_NONE && h[i] <= U && h[i] <= U1) qual[atomicAdd(&nqual, 1u)] = (uint16_t)(i * kBlock + tid);
+        if (h[i] != KEY_NONE && h[i] <= U) qual[atomicAdd(&nqual, 1u)] = (uint16_t)(i * kBlock + tid);
     __syncthreads();  // also: every thread has read U before cand is rewritten
     const uint32_t nl = nqual;  // <= k
     for (uint32_t i = tid; i < nl * k; i += kBlock) {
