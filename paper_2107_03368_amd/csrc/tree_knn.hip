@@ -83,28 +83,35 @@ struct Scores {
     uint32_t n_scored;    // nodes 0 .. n_scored-1 carry a score
 };
 
-// Smaller trees deal their tasks query by query from one counter: their rows
-// are in the caches in any order, and a query's searches that run together
-// share its k-th key early.  Dealt by subtree on each XCD instead, depth-first,
+// Smaller trees, and batches of fewer than two tasks per wave, deal their tasks
+// query by query from one counter: there is little to reuse, and a query's
+// searches that run together share its k-th key early.  Dealt by subtree on each XCD instead, depth-first,
 // k = 10: 10k rows 509 queries 0.62 -> 0.77 ms, 2,048 1.86 -> 1.99; 30k rows
 // 0.88 -> 0.86 and 2.81 -> 2.15; 60k rows 1.53 -> 1.19 and 5.17 -> 3.17.
-constexpr uint64_t kByQueryRows = 20000;
+// At k = 1 a close neighbour ends most searches, so sharing the key early counts
+// more: 60k rows, 1,200 queries 1.4 ms either way, 223k rows 2.9 -> 2.5.
+constexpr uint64_t kByQueryRows = 20000, kByQueryRows1 = 100000;
+// Words between the XCDs' counters: a cache line each, because thousands of
+// waves add to all of them when the tasks have run out.
+constexpr uint32_t kCounterStride = 32;
 constexpr uint32_t kMaxSplit = 16;        // a caller's choice
 constexpr uint32_t kFineSplit = kMaxCut;  // the library's (one list per lane in merge_kernel)
 // The tasks' area, one allocation for nq_max queries of n tasks each:
 // subtree roots (n int32, -1: an empty task) | per query, the least k-th key
-// its tasks have published | per task, its k-list (k keys) | their payloads
+// its tasks have published | per query, the work of its first bound (nodes
+// expanded << 16 | rows; dealt by subtree only) | per task, its k-list (k keys) | their payloads
 // (A | B << 16) | its statistics (nodes visited, leaves, bounds, distances,
 // |q|; 8 words).  Byte offsets from the area's start; the kernels take the
 // start alone and compute the rest, so few pointers stay in registers.
 struct SplitLayout {
-    uint64_t kshared, key, pay, stat, bytes;
+    uint64_t kshared, seed, key, pay, stat, bytes;
 };
 __host__ __device__ inline SplitLayout split_layout(uint64_t nq_max, uint32_t n, uint32_t k) {
     const uint64_t nt = nq_max * n;
     SplitLayout L;
     L.kshared = 256;
-    L.key = L.kshared + (nq_max * 4 + 255) / 256 * 256;
+    L.seed = L.kshared + (nq_max * 4 + 255) / 256 * 256;
+    L.key = L.seed + (nq_max * 4 + 255) / 256 * 256;
     L.pay = L.key + nt * k * 8;
     L.stat = L.pay + (nt * k * 4 + 255) / 256 * 256;
     L.bytes = L.stat + nt * 32;
@@ -112,6 +119,23 @@ __host__ __device__ inline SplitLayout split_layout(uint64_t nq_max, uint32_t n,
 }
 
 __device__ __forceinline__ uint32_t sum32(uint32_t v) { return sum32_half(v); }
+
+// Bound of node c (each half-wave one node) from its images (chunk lane % 32)
+// and, when stored, its rows' popcount range.
+__device__ __forceinline__ uint32_t node_bound(const TreeView &T, const uint4 &qn, const uint4 &nqn, uint32_t pq,
+                                               uint32_t wa, uint32_t wb, int32_t c) {
+    const uint64_t at = (uint64_t)c * 32 + (lane_id() & 31);
+    const uint32_t ov = sum32(popc_and4(qn, T.orimg[at]));
+    uint32_t bl = 0;
+    if (T.andimg) bl = sum32(popc_and4(nqn, T.andimg[at]));
+    uint32_t al = pq - ov;
+    if (T.pmin) {
+        const uint32_t lo = T.pmin[c], hi = T.pmax[c];
+        al = pq - (ov < hi ? ov : hi);
+        bl = lo > ov && lo - ov > bl ? lo - ov : bl;
+    }
+    return al * wb + bl * wa;
+}
 
 // Bound by reading the visited leaves' rows (22 on average) and by the latency
 // of one visit after another.  A leaf's rows are loaded in groups of 8, kGroups
@@ -139,9 +163,9 @@ __global__ __launch_bounds__(kBlock, kBest && kGroups == 4 ? 3 : 4) void tree_kn
     uint32_t *bstate = bstate_all + (kBest ? wave * kBuckets : 0);
     u64 *stack = stack_all + wave * (kBest ? kHot : kMaxStack);
     u64 *sinfo = sinfo_all + wave * (kBest ? kHot : kMaxStack);
-    const bool has_and = T.andimg != nullptr;
     const uint32_t nq_max = nq;  // the tasks' area is laid out for nq queries
     if (nq_dev) nq = readfirst(*nq_dev);  // size given on the device (captured graphs)
+    if (nq == 0) return;                  // (the blocked search's fallback, nearly always)
     const uint32_t tsh = (uint32_t)__builtin_ctz(nsplit);  // tasks per query = 1 << tsh
     uint32_t *const kshared = reinterpret_cast<uint32_t *>(sw + 256);  // the layout's first offset
 
@@ -149,9 +173,9 @@ __global__ __launch_bounds__(kBlock, kBest && kGroups == 4 ? 3 : 4) void tree_kn
     // XCD s % 8 (blocks go to the XCDs in turn), whose waves take all queries of
     // one subtree, then of the next, and then help the other XCDs.  The rows that
     // run together are then a few subtrees', which caches hold: 64 subtrees of
-    // 1M rows are 8 MB each, 11.8 ms for 509 queries; 12.6 with the subtrees in
-    // the same order on every XCD, 13.4 with one counter.  n_homes 1: one counter,
-    // a query's tasks together.
+    // 1M rows are 8 MB each, 11.8 ms for 509 queries (before 16 waves per CU);
+    // 12.6 with the subtrees in the same order on every XCD, 13.4 with one
+    // counter.  n_homes 1: one counter, a query's tasks together.
     for (;;) {
         // every lane takes part in the atomic (lane 0 adds 1, the others 0) so
         // that no lane-dependent branch guards the loop head; control values
@@ -161,12 +185,8 @@ __global__ __launch_bounds__(kBlock, kBest && kGroups == 4 ? 3 : 4) void tree_kn
         uint32_t home, turn, other = 0;
         do {
             home = readfirst((blockIdx.x + other) & (n_homes - 1));
-            const uint32_t limit = nq * ((nsplit + n_homes - 1 - home) / n_homes);  // below 2^31
-            // (another XCD's counter is read first: thousands of waves adding to
-            // counters that have run out would take turns for 0.3 ms)
-            turn = other ? readfirst(__hip_atomic_load(next_task + home, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) : 0;
-            if (turn < limit) turn = readfirst(atomicAdd(next_task + home, lane == 0 ? 1u : 0u));
-            if (turn < limit) break;
+            turn = readfirst(atomicAdd(next_task + home * kCounterStride, lane == 0 ? 1u : 0u));
+            if (turn < (uint64_t)nq * ((nsplit + n_homes - 1 - home) / n_homes)) break;
             other = readfirst(other + 1);
         } while (other < n_homes);
         if (other >= n_homes) break;
@@ -221,6 +241,12 @@ __global__ __launch_bounds__(kBlock, kBest && kGroups == 4 ? 3 : 4) void tree_kn
         uint32_t ucut = nsplit == 1 ? kNone : readfirst(lane == 0 ? atomicMin(&kshared[qi], kNone) : 0u);
         uint32_t uret = kNone;
         uint32_t visited = 0, leaves = 0, bounds = 0, dists = 0;
+        if (n_homes > 1 && sub == 0) {  // with the work of the query's first bound
+            const uint32_t w = readfirst(reinterpret_cast<const uint32_t *>(sw + split_layout(nq_max, nsplit, k).seed)[qi]);
+            visited = w >> 16;
+            bounds = 2 * visited;
+            dists = w & 0xFFFFu;
+        }
 
         // frontier
         u64 occ = 0;        // best-first: bucket occupancy bits 64*lane .. 64*lane+63
@@ -230,21 +256,6 @@ __global__ __launch_bounds__(kBlock, kBest && kGroups == 4 ? 3 : 4) void tree_kn
         int sp = 0;         // depth-first: stack depth; best-first: entries of the hot bucket in LDS
         uint32_t hot_b = kNone;  // best-first: the bucket whose new entries go to LDS
 
-        // bound of node c from its images (each half-wave holds one node's
-        // 32 chunks) and, when stored, its rows' popcount range
-        auto node_bound = [&](int32_t c) -> uint32_t {
-            const uint4 o = T.orimg[(uint64_t)c * 32 + (lane & 31)];
-            const uint32_t ov = sum32(popc_and4(qn, o));
-            uint32_t bl = 0;
-            if (has_and) bl = sum32(popc_and4(nqn, T.andimg[(uint64_t)c * 32 + (lane & 31)]));
-            uint32_t al = pq - ov;
-            if (T.pmin) {
-                const uint32_t lo = T.pmin[c], hi = T.pmax[c];
-                al = pq - (ov < hi ? ov : hi);
-                bl = lo > ov && lo - ov > bl ? lo - ov : bl;
-            }
-            return al * wb + bl * wa;
-        };
         // what a node's expansion needs, fetched when the node is bounded (in
         // parallel with its images) and kept with its queue entry, so popping
         // it waits for no load: a leaf's row range (bit 63 set) or its children
@@ -255,7 +266,7 @@ __global__ __launch_bounds__(kBlock, kBest && kGroups == 4 ? 3 : 4) void tree_kn
         };
         auto bound_pair = [&](int32_t c0, int32_t c1, uint32_t &kb0, uint32_t &kb1, u64 &in0, u64 &in1) {
             const int32_t c = lane < 32 ? c0 : c1;
-            const uint32_t kb = node_bound(c);
+            const uint32_t kb = node_bound(T, qn, nqn, pq, wa, wb, c);
             const u64 in = info_of(c);
             kb0 = readlane(kb, 0);
             kb1 = readlane(kb, 32);
@@ -324,7 +335,7 @@ __global__ __launch_bounds__(kBlock, kBest && kGroups == 4 ? 3 : 4) void tree_kn
 
         // the task's subtree root (the tree's root without a split)
         {
-            const uint32_t kb = readlane(node_bound(root), 0);
+            const uint32_t kb = readlane(node_bound(T, qn, nqn, pq, wa, wb, root), 0);
             const u64 in = readlane64(info_of(root), 0);
             bounds++;
             if (kBest) hot_b = readfirst(kb / (kBucketLevels * wb) < (uint32_t)kBuckets ? kb / (kBucketLevels * wb)
@@ -485,6 +496,81 @@ __global__ __launch_bounds__(kBlock, kBest && kGroups == 4 ? 3 : 4) void tree_kn
             atomicAdd(&gstats[2], (unsigned long long)bounds);
             atomicAdd(&gstats[3], (unsigned long long)dists);
         }
+    }
+}
+
+// First bound on a query's k-th key, before its searches start: from the root
+// down to the child of lower bound (ties: the similar child) until a node
+// holds at most kSeedRows rows, and the k-th smallest key of those rows (kNone
+// if they are fewer).  One wave per query.  Its work is counted with the
+// query's first search.  For searches dealt by subtree: the subtrees that come
+// first would otherwise be searched with no bound, which counts most at k = 1
+// (1M rows, 1,200 queries, depth-first: 11,400 nodes per query and 9.2 ms
+// without, 8,300 and 6.8 ms with; k = 10: 5% fewer nodes, the same time).
+constexpr uint32_t kSeedRows = 2048;
+__global__ __launch_bounds__(kBlock) void seed_kernel(TreeView T, const uint4 *__restrict__ q, uint32_t nq,
+                                                      const uint32_t *__restrict__ nq_dev, uint32_t k,
+                                                      char *__restrict__ sw, uint32_t nsplit) {
+    const int lane = lane_id(), g = lane >> 3, j = lane & 7;
+    const uint32_t qi = blockIdx.x * kWaves + (threadIdx.x >> 6);
+    const SplitLayout SL = split_layout(nq, nsplit, k);  // laid out for nq queries
+    if (nq_dev) nq = min(nq, *nq_dev);
+    if (qi >= nq) return;  // the whole wave
+    uint4 qv[4];
+    uint32_t s = 0;
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        qv[i] = q[(uint64_t)qi * 32 + j + 8 * i];
+        s += popc4(qv[i]);
+    }
+    const uint32_t pq = readfirst(sum8(s));
+    const uint4 qn = q[(uint64_t)qi * 32 + (lane & 31)];
+    const uint4 nqn = make_uint4(~qn.x, ~qn.y, ~qn.z, ~qn.w);
+    const uint32_t wa = pq > 1 ? pq : 1, wb = (QD_BITS - pq) > 1 ? QD_BITS - pq : 1;
+    uint32_t node = 0, m = readfirst(T.count[0]), visited = 0;
+    while (m > kSeedRows) {
+        const int32_t c0 = T.child[2 * (uint64_t)node], c1 = T.child[2 * (uint64_t)node + 1];
+        if (c0 < 0) break;
+        const uint32_t kb = node_bound(T, qn, nqn, pq, wa, wb, lane < 32 ? c0 : c1);
+        node = readfirst(readlane(kb, 32) < readlane(kb, 0) ? (uint32_t)c1 : (uint32_t)c0);
+        m = readfirst(T.count[node]);
+        visited++;
+    }
+    const uint64_t b0 = T.begin[node];
+    const uint32_t rows = m < kSeedRows ? m : kSeedRows;  // (a leaf may be larger)
+    uint32_t list = kNone, kth = kNone;                  // lane r: the r-th smallest key
+    for (uint32_t base = 0; base < rows; base += 32) {
+        uint32_t cs[4], tps[4];
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+            const uint32_t r = base + 8 * u + (uint32_t)g;
+            const uint64_t pos = b0 + (r < rows ? r : 0);
+            uint4 tv[4];
+#pragma unroll
+            for (int i = 0; i < 4; i++) tv[i] = T.sorted[pos * 32 + j + 8 * i];
+            cs[u] = popc_and4(tv[0], qv[0]) + popc_and4(tv[1], qv[1]) + popc_and4(tv[2], qv[2]) +
+                    popc_and4(tv[3], qv[3]);
+            tps[u] = T.pop[pos];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+            const uint32_t c = sum8(cs[u]);
+            const uint32_t K = (pq - c) * wb + (tps[u] - c) * wa;
+            u64 mk = ballot(j == 0 && base + 8 * u + (uint32_t)g < rows && K < kth);
+            while (mk) {
+                const uint32_t cand = readlane(K, __builtin_ctzll(mk));
+                mk &= mk - 1;
+                if (cand >= kth) continue;
+                const int pos = __popcll(ballot(list <= cand));
+                const uint32_t up = (uint32_t)__builtin_amdgcn_ds_bpermute((lane > 0 ? lane - 1 : 0) << 2, (int)list);
+                list = lane < pos ? list : lane == pos ? cand : up;
+                kth = readlane(list, (int)k - 1);
+            }
+        }
+    }
+    if (lane == 0) {
+        reinterpret_cast<uint32_t *>(sw + SL.kshared)[qi] = kth;
+        reinterpret_cast<uint32_t *>(sw + SL.seed)[qi] = visited << 16 | rows;
     }
 }
 
@@ -649,7 +735,7 @@ TreeLaunch tree_launch_shape(qd_tree_t t, uint32_t nq_max, uint32_t k, int order
     // and one per bucket touched never run out.
     const uint64_t sub = t->split_nodes[__builtin_ctz(split)];
     L.pool_chunks = order == QD_ORDER_BEST_FIRST ? sub / kChunk + std::min<uint64_t>(kBuckets, sub) + 2 : 1;
-    L.head = 256;  // [counter | pad | stats x4 | pad]
+    L.head = 8 * kCounterStride * 4;  // per XCD a counter; after the first, the stats x4
     L.prev_bytes = (size_t)(L.slots * L.pool_chunks * 8 + 255) / 256 * 256;  // prev + free list
     L.pool_bytes = (size_t)L.slots * L.pool_chunks * kChunk * 16;  // 16-byte records: entry, node info
     L.split_bytes = split_layout(nq_max ? nq_max : 1, split, k).bytes;  // the tasks' lists, also unsplit
@@ -673,18 +759,25 @@ int tree_launch(qd_tree_t t, const TreeLaunch &L, char *ws, const uint64_t *d_q,
     Scores S{d_scores, d_scores ? n_scored : 0};
     if (L.split > 1 && d_trace) return fail(QD_ERR_INVALID, "a traced search runs unsplit");
     char *sw = ws + L.head + L.prev_bytes + L.pool_bytes;  // the tasks' area
+    // by subtree only where a wave takes several searches; unsplit, there is one subtree
+    const uint32_t n_homes =
+        L.split == 1 || t->n < (k == 1 ? kByQueryRows1 : kByQueryRows) || (uint64_t)nq * L.split < 2 * L.slots ? 1 : 8;
     if (L.split > 1) {
         hipLaunchKernelGGL(roots_kernel, dim3(1), dim3(64), 0, s, t->d_split_roots, L.split,
                            reinterpret_cast<int32_t *>(sw));
-        const uint32_t fg = (nq + 255) / 256;
-        hipLaunchKernelGGL(fill_words_kernel, dim3(fg < 1 ? 1 : fg < 1024 ? fg : 1024), dim3(256), 0, s,
-                           reinterpret_cast<uint32_t *>(sw + split_layout(nq, L.split, k).kshared), (uint64_t)nq,
-                           kNone);
+        if (n_homes > 1) {
+            KernelTimer timer("tree_seed", s);
+            hipLaunchKernelGGL(seed_kernel, dim3((nq + kWaves - 1) / kWaves), dim3(kBlock), 0, s, T,
+                               reinterpret_cast<const uint4 *>(d_q), nq, nq_dev, k, sw, L.split);
+        } else {
+            const uint32_t fg = (nq + 255) / 256;
+            hipLaunchKernelGGL(fill_words_kernel, dim3(fg < 1 ? 1 : fg < 1024 ? fg : 1024), dim3(256), 0, s,
+                               reinterpret_cast<uint32_t *>(sw + split_layout(nq, L.split, k).kshared), (uint64_t)nq,
+                               kNone);
+        }
     }
     {
         KernelTimer timer("tree_knn", s);
-        // dealt by query too while every search has a wave from the start
-        const uint32_t n_homes = t->n < kByQueryRows || (uint64_t)nq * L.split <= L.slots ? 1 : 8;
         auto launch = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, dim3((uint32_t)L.blocks), dim3(kBlock), 0, s, T,
                                reinterpret_cast<const uint4 *>(d_q), nq, k, counter, pool, chunk_prev, L.pool_chunks,

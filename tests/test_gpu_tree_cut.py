@@ -13,7 +13,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("n, nq, k", [(1, 3, 5), (40, 5, 64), (700, 9, 10), (19_999, 200, 64), (20_000, 200, 10),
                                       (33_000, 128, 64), (66_000, 64, 1), (66_000, 65, 10), (270_000, 130, 10),
-                                      (530_000, 70, 20)])
+                                      (530_000, 70, 20),
+                                      (19_999, 600, 10), (20_000, 600, 64), (99_999, 600, 1), (100_000, 600, 1)])
 def test_default_cut_matches_oracle(n, nq, k):
     import paper_2107_03368_amd as qd
     import torch
