@@ -891,9 +891,11 @@ __global__ __launch_bounds__(256) void eval_short_kernel(const uint4 *__restrict
 // Work is dealt from a counter: up to kEvTiles consecutive tile records (one
 // block's share their rows), each once per half of the rows.
 // Bound by the matrix units and, a fifth, by the changes of rows: 10M rows x
-// 8,192 queries, k = 10 (15.0e9 pairs) take 20.8 ms, 5.9 PFLOP/s; 21.1 / 22.1 /
-// 23.9 ms with 4 / 2 / 1 records per item, and 23.1 with a 256 x 256 tile per
-// workgroup of 8 waves (queries and rows staged in LDS, a barrier per 512 bits).
+// 8,192 queries, k = 10 (15.0e9 pairs) take 20.7 ms, 5.9 PFLOP/s (21.1 with the
+// fill's addresses and the rows' |t| kept over the loop: 64 spilled registers,
+// now 26, most of them those of the next unit's loads); 1.5 / 6 / 15% more with
+// 4 / 2 / 1 records per item, 11% with a 256 x 256 tile per workgroup of 8 waves
+// (queries and rows staged in LDS, a barrier per 512 bits).
 // A wave's passing pairs are appended to its queue in LDS and written out
 // together, so the candidate slots' atomics overlap.
 constexpr int kEvBlock = 256, kEvWaves = kEvBlock / 64;
@@ -975,19 +977,19 @@ __global__ __launch_bounds__(kEvBlock, 2) void eval_kernel(const uint4 *__restri
             }
             __syncthreads();  // every wave is done with the rows before
             {
-                constexpr int kPer = kEvRows * 32 / kEvBlock;
+                // piece t % 32 of rows t / 32, + 8, + 16, ..
+                constexpr int kPer = kEvRows * 32 / kEvBlock, kStep = kEvBlock / 32;
+                uint32_t first = (uint32_t)t >> 5;
+                asm volatile("" : "+v"(first));  // (16 addresses kept over the loop would spill)
                 uint4 y[kPer];
 #pragma unroll
                 for (int i = 0; i < kPer; i++) {
-                    const uint32_t e = (uint32_t)t + kEvBlock * i;
-                    const uint64_t row = row0 + (e >> 5);
-                    y[i] = sorted[(row < n ? row : n - 1) * 32 + (e & 31)];
+                    const uint64_t row = row0 + first + kStep * i;
+                    y[i] = sorted[(row < n ? row : n - 1) * 32 + (t & 31)];
                 }
+                uint8_t *const to = s_rows + first * kEvStride + (t & 31) * 16;
 #pragma unroll
-                for (int i = 0; i < kPer; i++) {
-                    const uint32_t e = (uint32_t)t + kEvBlock * i;
-                    *reinterpret_cast<uint4 *>(s_rows + (size_t)(e >> 5) * kEvStride + (e & 31) * 16) = y[i];
-                }
+                for (int i = 0; i < kPer; i++) *reinterpret_cast<uint4 *>(to + kStep * i * kEvStride) = y[i];
                 if (t < (int)kEvRows) s_tp[t] = row0 + t < n ? (float)tpop[row0 + t] : mt::kNoRow;
             }
             __syncthreads();
@@ -1020,6 +1022,8 @@ __global__ __launch_bounds__(kEvBlock, 2) void eval_kernel(const uint4 *__restri
                 const bool more = qt + 2 < n_qt;
                 const uint32_t nqt = more ? qt + 2 : qt;
                 uint32_t nqi[2], nth[2], pcur[2];
+                uint32_t unit0 = 0;
+                asm volatile("" : "+v"(unit0));  // (the rows' |t| read where they are needed, not kept over the loop)
                 mt::v16f acc[2][2];
 #pragma unroll
                 for (int L = 0; L < 4; L++) {
@@ -1082,7 +1086,7 @@ __global__ __launch_bounds__(kEvBlock, 2) void eval_kernel(const uint4 *__restri
                                 const bool act = v4[g].v[e] >= bound;
                                 if (ballot(act) == 0) continue;
                                 const int ro = 32 * b + 8 * g + 4 * lh + e;
-                                const uint32_t K = (uint32_t)((int)(P + __umul24((uint32_t)tp[ro], wa)) +
+                                const uint32_t K = (uint32_t)((int)(P + __umul24((uint32_t)tp[ro + unit0], wa)) +
                                                               __mul24((int)mt::count(acc[a][b][4 * g + e]), nsw));
                                 const bool pass = act & (K <= tk);
                                 const u64 pm = ballot(pass);
