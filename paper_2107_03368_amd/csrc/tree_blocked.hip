@@ -891,11 +891,11 @@ __global__ __launch_bounds__(256) void eval_short_kernel(const uint4 *__restrict
 // Work is dealt from a counter: up to kEvTiles consecutive tile records (one
 // block's share their rows), each once per half of the rows.
 // Bound by the matrix units and, a fifth, by the changes of rows: 10M rows x
-// 8,192 queries, k = 10 (15.0e9 pairs) take 20.7 ms, 5.9 PFLOP/s (21.1 with the
-// fill's addresses and the rows' |t| kept over the loop: 64 spilled registers,
-// now 26, most of them those of the next unit's loads); 1.5 / 6 / 15% more with
-// 4 / 2 / 1 records per item, 11% with a 256 x 256 tile per workgroup of 8 waves
-// (queries and rows staged in LDS, a barrier per 512 bits).
+// 8,192 queries, k = 10 (15.0e9 pairs) take 19.3 ms, 6.4 PFLOP/s (21.1 with the
+// fill's addresses and the rows' |t| and numbers kept over the loop: 64 spilled
+// registers, now none); 1.5 / 6 / 15% more with 4 / 2 / 1 records per item, 11%
+// more than those 21.1 with a 256 x 256 tile per workgroup of 8 waves (queries
+// and rows staged in LDS, a barrier per 512 bits).
 // A wave's passing pairs are appended to its queue in LDS and written out
 // together, so the candidate slots' atomics overlap.
 constexpr int kEvBlock = 256, kEvWaves = kEvBlock / 64;
@@ -1022,8 +1022,8 @@ __global__ __launch_bounds__(kEvBlock, 2) void eval_kernel(const uint4 *__restri
                 const bool more = qt + 2 < n_qt;
                 const uint32_t nqt = more ? qt + 2 : qt;
                 uint32_t nqi[2], nth[2], pcur[2];
-                uint32_t unit0 = 0;
-                asm volatile("" : "+v"(unit0));  // (the rows' |t| read where they are needed, not kept over the loop)
+                uint32_t unit0 = 0;  // (rows' |t| and numbers formed where they are needed, not kept over the loop)
+                asm volatile("" : "+v"(unit0));
                 mt::v16f acc[2][2];
 #pragma unroll
                 for (int L = 0; L < 4; L++) {
@@ -1094,7 +1094,7 @@ __global__ __launch_bounds__(kEvBlock, 2) void eval_kernel(const uint4 *__restri
                                     const uint32_t at = nqe + lanes_below(pm);
                                     cq[at][0] = qk;
                                     cq[at][1] = K;
-                                    cq[at][2] = (uint32_t)row0 + 64 * rt + ro;
+                                    cq[at][2] = (uint32_t)row0 + 64 * rt + (ro + unit0);
                                 }
                                 nqe += (uint32_t)__popcll(pm);
                                 if (nqe > kEvQueue - 64) flush();  // the next row adds at most 64
