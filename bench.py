@@ -57,13 +57,13 @@ TRAIN_QUERIES, TRAIN_BATCH, TRAIN_EPOCHS, TRAIN_LR, N_SCORED = 4096, 32, 8, 2e-3
 # what they read for a 1 GiB device copy (FETCH 524,316 KiB, WRITE 1,048,576
 # KiB); drop an entry when its kernel changes
 TRAFFIC_DETAIL = {
-    # scan_mfma_kernel at 10M x 8,192: the main launch (not the threshold sample's)
-    "scan_mfma_kernel": {"read_bytes": 20_080_471 * 2 * 1024, "write_bytes": 543_341 * 1024,
+    # scan_mfma_kernel at 10M x 8,192: the two parts of one search's pass, timed as one (not the sample's)
+    "scan_mfma_kernel": {"read_bytes": 2_541_321 * 2 * 1024, "write_bytes": 208_845 * 1024,
                          "algorithmic_read_bytes": 5.124e9, "counter_scale": {"FETCH_SIZE": 2.0, "WRITE_SIZE": 1.0}},
     # eval_kernel at 10M x 8,192, k = 10: one search's launches together (a
     # direct search launches it once per pass, passes without tiles included),
     # divided below by the launches per search, as the achieved rate is
-    "eval_kernel": {"read_bytes_per_search": 12_856_190 * 2 * 1024, "write_bytes_per_search": 522_619 * 1024,
+    "eval_kernel": {"read_bytes_per_search": 13_363_977 * 2 * 1024, "write_bytes_per_search": 593_030 * 1024,
                     "counter_scale": {"FETCH_SIZE": 2.0, "WRITE_SIZE": 1.0}},
 }
 TRAFFIC = {kname: d["read_bytes"] + d["write_bytes"] for kname, d in TRAFFIC_DETAIL.items() if "read_bytes" in d}
