@@ -11,7 +11,9 @@
 // key) up to the bound in a per-query candidate buffer; the exact top k are
 // all among them.  A long pass runs in parts: after the first (an eighth of the
 // rows) the bounds are tightened to the k-th key found so far, so the rest
-// lists about 7 k rows per query.  A final kernel selects each query's k best
+// lists about 7 k rows per query.  A bound is a full key (K << 32 | row): of
+// rows with equal K (repeated or blank descriptors, a blank query) only those
+// up to the bound's row are kept, so ties do not fill the buffer.  A final kernel selects each query's k best
 // candidates and writes the results; queries whose buffer overflowed are
 // searched again by the register-tiled scan, so the result is exact in every
 // case.
@@ -54,7 +56,8 @@ constexpr uint32_t kMaxGroups = 8192;  // sample minima per query
 // the ends of units too.  |t| is counted from the same words.
 // kSample: instead of listing the rows that pass, the smallest key of the
 // lane's 32 rows of each query goes to minima[(2 i + h) * nq + query], i the
-// tile's number in this pass.
+// tile's number in this pass, as (K << 5 | the row's number among the lane's;
+// all ones without a row; K < 2^25).
 // Bound: the rows' bytes for up to 64 queries (5.8 TB/s), the matrix units above
 // (7.2 PFLOP/s at 256 queries; they reach about 8.1 at the clock they run at).
 // 10M rows, k = 10, whole calls with 32 / 64 / 128 / 256 queries: 0.97 / 0.99 /
@@ -232,8 +235,9 @@ __global__ __launch_bounds__(kMidBlock, 2) void scan_mfma_kernel(const uint4 *__
                 if (kSample) {
                     // K = |q|*wB - (C*(wA + wB) - |t|*wA), exact in fp32 (integers
                     // below 2^24, but for C = |q| = 4096: 4096 * 4097 is even)
+                    // (a row past the end: -2^25, below every value)
                     const float sw = (float)(wa + wb), nwa = -(float)wa;
-                    float vmax = -1e38f;
+                    int32_t best = INT32_MIN;
 #pragma unroll
                     for (int b = 0; b < 2; b++)
 #pragma unroll
@@ -241,12 +245,14 @@ __global__ __launch_bounds__(kMidBlock, 2) void scan_mfma_kernel(const uint4 *__
                             const float4 t4 = *reinterpret_cast<const float4 *>(tpw + 32 * b + 8 * g + 4 * lh);
                             const float t[4] = {t4.x, t4.y, t4.z, t4.w};
 #pragma unroll
-                            for (int e = 0; e < 4; e++)
-                                vmax = fmaxf(vmax, __builtin_fmaf(t[e], nwa, acc[a][b][4 * g + e] * sw));
+                            for (int e = 0; e < 4; e++) {
+                                const float v = __builtin_fmaf(t[e], nwa, acc[a][b][4 * g + e] * sw);
+                                best = max(best, (int32_t)fmaxf(v, -33554432.f) * 32 + (31 - (16 * b + 4 * g + e)));
+                            }
                         }
                     if (q0 + qs < nq)
                         minima[(2 * rt + lh) * nq_max + q0 + qs] =
-                            vmax < -1e20f ? 0xFFFFFFFFu : __umul24(pq, wb) - (uint32_t)(int32_t)vmax;
+                            best < -33554431 * 32 ? 0xFFFFFFFFu : 32 * __umul24(pq, wb) + 31 - (uint32_t)best;
                     continue;
                 }
                 const float nratio = -(float)wa * mt::inv_sw(pq);
@@ -338,6 +344,34 @@ struct Pick {
         }
         return lo;
     }
+    // the need-th smallest row(i) of the candidates i of K = kth (at least need >= 1 of them)
+    template <class F>
+    __device__ __forceinline__ uint32_t nth_row(uint32_t kth, uint32_t need, F &&row) {
+        uint32_t rv[R];
+#pragma unroll
+        for (int j = 0; j < R; j++) rv[j] = kv[j] == kth ? row(threadIdx.x + (uint32_t)kBlock * j) : 0xFFFFFFFFu;
+        uint32_t lo = 0, hi = 0xFFFFFFFFu;
+        while (lo < hi) {
+            const uint32_t mid = lo + (hi - lo) / 2;
+            if (count([&](int j) { return rv[j] <= mid; }) >= need)
+                hi = mid;
+            else
+                lo = mid + 1;
+        }
+        return lo;
+    }
+    // the k-th smallest (K << 32 | row(i)) of the candidates (at least k of them)
+    template <class F>
+    __device__ __forceinline__ u64 kth_key(uint32_t k, F &&row) {
+        const uint32_t K = kth(k), below = count([&](int j) { return kv[j] < K; });
+        if (count([&](int j) { return kv[j] == K; }) > 1) return ((u64)K << 32) | nth_row(K, k - below, row);
+        __shared__ uint32_t s_row;  // the only one, as nearly always
+#pragma unroll
+        for (int j = 0; j < R; j++)
+            if (kv[j] == K) s_row = row(threadIdx.x + (uint32_t)kBlock * j);
+        __syncthreads();
+        return ((u64)K << 32) | s_row;
+    }
 };
 
 // After a part of a pass: the k-th smallest key found so far bounds the rest
@@ -352,8 +386,9 @@ __global__ __launch_bounds__(kBlock) void tighten_kernel(const uint32_t *__restr
     if (m < k || m > kCap) return;
     const u64 *c = cand + (uint64_t)qi * kCap;
     auto key = [&](uint32_t i) { return (uint32_t)(c[i] >> 32); };
-    const uint32_t kth = m <= 4 * kBlock ? Pick<4>(key, m, s_part).kth(k) : Pick<kCap / kBlock>(key, m, s_part).kth(k);
-    const u64 t = ((u64)kth << 32) | 0xFFFFFFFFu;
+    auto row = [&](uint32_t i) { return (uint32_t)c[i]; };
+    const u64 t = m <= 4 * kBlock ? Pick<4>(key, m, s_part).kth_key(k, row)
+                                  : Pick<kCap / kBlock>(key, m, s_part).kth_key(k, row);
     if (threadIdx.x == 0 && t < thr[qi]) thr[qi] = t;
 }
 
@@ -368,21 +403,7 @@ __device__ __forceinline__ void pick_keys(const u64 *cand, uint32_t m, uint32_t 
     uint32_t last = 0xFFFFFFFFu;  // rows above it with K = kth are left out
     if (P.count([&](int j) { return P.kv[j] <= kth; }) > (uint32_t)kBlock) {
         const uint32_t need = k - P.count([&](int j) { return P.kv[j] < kth; });
-        uint32_t rv[R];
-#pragma unroll
-        for (int j = 0; j < R; j++) {
-            const uint32_t i = threadIdx.x + (uint32_t)kBlock * j;
-            rv[j] = i < m ? (uint32_t)cand[i] : 0xFFFFFFFFu;
-        }
-        uint32_t lo = 0, hi = 0xFFFFFFFFu;
-        while (lo < hi) {
-            const uint32_t mid = lo + (hi - lo) / 2;
-            if (P.count([&](int j) { return P.kv[j] == kth && rv[j] <= mid; }) >= need)
-                hi = mid;
-            else
-                lo = mid + 1;
-        }
-        last = lo;
+        last = P.nth_row(kth, need, [&](uint32_t i) { return (uint32_t)cand[i]; });
     }
 #pragma unroll
     for (int j = 0; j < R; j++) {
@@ -431,11 +452,11 @@ __global__ __launch_bounds__(kBlock) void select_emit_kernel(const uint32_t *__r
     emit_rows(keys, nk < k ? nk : k, k, q + (uint64_t)qi * 32, db, (uint64_t)qi * k, idx, missed, extra, dist);
 }
 
-// thr[q] = the k-th smallest of the query's m <= kMaxGroups sample minima (none
-// if fewer are rows'); clears the pass's candidate counts and its overflow
-// count.  One block per query.
+// thr[q] = the k-th smallest key (K << 32 | row) of the query's m <= kMaxGroups
+// sample minima (none if fewer are rows'); clears the pass's candidate counts
+// and its overflow count.  Every tstep-th row tile was sampled.  One block per query.
 __global__ __launch_bounds__(kBlock) void sample_threshold_kernel(const uint32_t *__restrict__ minima, uint32_t m,
-                                                                  uint32_t nq, uint32_t k, u64 *__restrict__ thr,
+                                                                  uint64_t tstep, uint32_t nq, uint32_t k, u64 *__restrict__ thr,
                                                                   uint32_t *__restrict__ cnt,
                                                                   uint32_t *__restrict__ n_redo,
                                                                   const uint32_t *__restrict__ nq_dev) {
@@ -446,10 +467,14 @@ __global__ __launch_bounds__(kBlock) void sample_threshold_kernel(const uint32_t
         if (qi == 0) *n_redo = 0;
     }
     if (nq_dev && qi >= *nq_dev) return;  // whole block
-    auto key = [&](uint32_t i) { return minima[(uint64_t)i * nq + qi]; };
+    constexpr uint32_t kNoRowK = 0xFFFFFFFFu >> 5;
+    auto key = [&](uint32_t i) { return minima[(uint64_t)i * nq + qi] >> 5; };
+    auto row = [&](uint32_t i) {  // of group i = (tile i / 2, lane half i % 2), as scan_mfma_kernel's lanes hold them
+        const uint32_t e = minima[(uint64_t)i * nq + qi] & 31;
+        return (uint32_t)((i >> 1) * tstep * kMidR + 32 * (e >> 4) + 8 * ((e >> 2) & 3) + 4 * (i & 1) + (e & 3));
+    };
     auto bound = [&](auto &&P) -> u64 {
-        if (P.count([&](int j) { return P.kv[j] != 0xFFFFFFFFu; }) < k) return KEY_NONE;
-        return ((u64)P.kth(k) << 32) | 0xFFFFFFFFu;
+        return P.count([&](int j) { return P.kv[j] < kNoRowK; }) < k ? KEY_NONE : P.kth_key(k, row);
     };
     const u64 t = m <= 4 * kBlock ? bound(Pick<4>(key, m, s_part)) : bound(Pick<kMaxGroups / kBlock>(key, m, s_part));
     if (threadIdx.x == 0) thr[qi] = t;
@@ -531,7 +556,7 @@ int mfma_run(const MfmaLayout &L, char *ws, const uint64_t *d_db, const uint64_t
         hipLaunchKernelGGL(scan_mfma_kernel<true>, grid(L.sample_tiles), dim3(kMidBlock), lds, s, db4, n, 0ull,
                            L.sample_tiles, L.sample_step, q4, nq, nullptr, nullptr, nullptr, minima, nq_dev);
         hipLaunchKernelGGL(sample_threshold_kernel, dim3(nq), dim3(kBlock), 0, s, minima,
-                           (uint32_t)(2 * L.sample_tiles), nq, k, thr, cnt, n_redo, nq_dev);
+                           (uint32_t)(2 * L.sample_tiles), L.sample_step, nq, k, thr, cnt, n_redo, nq_dev);
     }
     {
         KernelTimer timer("wh_scan_mfma", s);
