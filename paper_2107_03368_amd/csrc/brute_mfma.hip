@@ -4,8 +4,8 @@
 // form a dense {0,1} matrix product C = Q T^T over the 4096 bit positions;
 // scan_mfma_kernel computes them in the encoding of mfma_tile.h.
 //
-// Selection, in three passes of the same kernel: a sample of the rows (tiles
-// spread evenly over them) gives each query the smallest key of every group of
+// Selection, in three passes of the same kernel: a sample of the rows (spread
+// evenly over them, sample_row) gives each query the smallest key of every group of
 // 32 sampled rows; the k-th smallest of those bounds the query's k-th key from
 // above (k distinct rows reach it).  The matrix pass then keeps every (row,
 // key) up to the bound in a per-query candidate buffer; the exact top k are
@@ -56,8 +56,7 @@ constexpr uint32_t kMaxGroups = 8192;  // sample minima per query
 // the ends of units too.  |t| is counted from the same words.
 // kSample: instead of listing the rows that pass, the smallest key of the
 // lane's 32 rows of each query goes to minima[(2 i + h) * nq + query], i the
-// tile's number in this pass, as (K << 5 | the row's number among the lane's;
-// all ones without a row; K < 2^25).
+// tile's number in this pass, as (K << 5 | the row's number among the lane's; K < 2^25).
 // Bound: the rows' bytes for up to 64 queries (5.8 TB/s), the matrix units above
 // (7.2 PFLOP/s at 256 queries; they reach about 8.1 at the clock they run at).
 // 10M rows, k = 10, whole calls with 32 / 64 / 128 / 256 queries: 0.97 / 0.99 /
@@ -71,6 +70,21 @@ constexpr int kMidQ = 64, kMidR = 64;     // queries and rows of a unit
 constexpr uint32_t kGroupQ = 4 * kMidQ;   // queries of a group
 constexpr uint32_t kMidQueue = 128;       // passing pairs per wave: room for one row's 64 past the flush mark
 constexpr int kMidStride = 512 + 16;      // bytes per query in LDS: 16-byte reads of 32 rows on distinct banks
+
+// Row of the sample's entry i: one out of every n / entries rows, at a place
+// that a hash of i picks, so that no period of the rows meets the sample's.
+// step = n / entries in 32.32 fixed point, at least 1.  Entry i of the sample
+// goes to its tile i % tiles: the 64 rows of a tile lie far apart, and near rows
+// (rows of one object, rows in order of distance, repeated rows) in different
+// groups, of which each adds one key to the bound.  With whole tiles sampled
+// a run of tied or similar rows filled few groups, and up to 16,000 of its rows
+// passed: 64 queries x 10M rows that are all equal 1.4 ms, 17 then.
+__device__ __forceinline__ uint64_t sample_row(uint32_t i, uint64_t step) {
+    const uint32_t a = (uint32_t)((i * step) >> 32), b = (uint32_t)(((uint64_t)(i + 1) * step) >> 32);
+    uint32_t h = i * 2654435761u;  // multiplicative hashing by the golden ratio, twice
+    h = (h ^ (h >> 16)) * 2654435761u;
+    return a + __umulhi(h, b - a);
+}
 
 // LDS, sized by the queries of the largest group.
 struct MidSmem {
@@ -87,7 +101,7 @@ inline size_t mid_lds_bytes(uint32_t nq) {
 
 template <bool kSample>
 __global__ __launch_bounds__(kMidBlock, 2) void scan_mfma_kernel(const uint4 *__restrict__ db, uint64_t n, uint64_t t0,
-                                                                 uint64_t tiles, uint64_t tstep,
+                                                                 uint64_t tiles, uint64_t sample_step,
                                                                  const uint4 *__restrict__ q, uint32_t nq,
                                                                  const u64 *__restrict__ thr, uint32_t *__restrict__ cnt,
                                                                  u64 *__restrict__ cand, uint32_t *__restrict__ minima,
@@ -102,7 +116,7 @@ __global__ __launch_bounds__(kMidBlock, 2) void scan_mfma_kernel(const uint4 *__
     const int li = lane & 31, lh = lane >> 5;
     float *tpw = sm.tp[wv];
     uint32_t (*cq)[3] = sm.queue[wv];
-    // the pass's row tiles: t0 + i * tstep, i < tiles
+    // the pass's row tiles: t0 + i, i < tiles (kSample: the sample's)
     const uint32_t nq_max = nq_given, n_qt = (nq + kMidQ - 1) / kMidQ;
     // this workgroup's units [ua, ub) of all groups' (each group: its query
     // tiles x tiles), rounded down to whole row tiles at both ends
@@ -151,7 +165,8 @@ __global__ __launch_bounds__(kMidBlock, 2) void scan_mfma_kernel(const uint4 *__
         auto load = [&](uint64_t r, int L, uint4 (&x)[2][4]) {
 #pragma unroll
             for (int b = 0; b < 2; b++) {
-                uint64_t row = (t0 + r * tstep) * kMidR + 32 * b + li;
+                uint64_t row = kSample ? sample_row((uint32_t)((32 * b + li) * tiles + r), sample_step)
+                                       : (t0 + r) * kMidR + 32 * b + li;
                 row = row < n ? row : n - 1;
                 const uint4 *src = db + row * 32 + 8 * L + lh;
 #pragma unroll
@@ -217,11 +232,11 @@ __global__ __launch_bounds__(kMidBlock, 2) void scan_mfma_kernel(const uint4 *__
                 }
             }
             // |t| of the tile's rows, to every lane through the wave's LDS
-            const uint64_t row0 = (t0 + rt * tstep) * kMidR;
+            const uint64_t row0 = (t0 + rt) * kMidR;  // (not the sample's rows, which all exist)
 #pragma unroll
             for (int b = 0; b < 2; b++) {
                 tcur[b] += (uint32_t)__shfl_xor((int)tcur[b], 32);
-                if (lh == b) tpw[32 * b + li] = row0 + 32 * b + li < n ? (float)tcur[b] : mt::kNoRow;
+                if (lh == b) tpw[32 * b + li] = kSample || row0 + 32 * b + li < n ? (float)tcur[b] : mt::kNoRow;
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
@@ -235,7 +250,6 @@ __global__ __launch_bounds__(kMidBlock, 2) void scan_mfma_kernel(const uint4 *__
                 if (kSample) {
                     // K = |q|*wB - (C*(wA + wB) - |t|*wA), exact in fp32 (integers
                     // below 2^24, but for C = |q| = 4096: 4096 * 4097 is even)
-                    // (a row past the end: -2^25, below every value)
                     const float sw = (float)(wa + wb), nwa = -(float)wa;
                     int32_t best = INT32_MIN;
 #pragma unroll
@@ -247,12 +261,11 @@ __global__ __launch_bounds__(kMidBlock, 2) void scan_mfma_kernel(const uint4 *__
 #pragma unroll
                             for (int e = 0; e < 4; e++) {
                                 const float v = __builtin_fmaf(t[e], nwa, acc[a][b][4 * g + e] * sw);
-                                best = max(best, (int32_t)fmaxf(v, -33554432.f) * 32 + (31 - (16 * b + 4 * g + e)));
+                                best = max(best, (int32_t)v * 32 + (31 - (16 * b + 4 * g + e)));
                             }
                         }
                     if (q0 + qs < nq)
-                        minima[(2 * rt + lh) * nq_max + q0 + qs] =
-                            best < -33554431 * 32 ? 0xFFFFFFFFu : 32 * __umul24(pq, wb) + 31 - (uint32_t)best;
+                        minima[(2 * rt + lh) * nq_max + q0 + qs] = 32 * __umul24(pq, wb) + 31 - (uint32_t)best;
                     continue;
                 }
                 const float nratio = -(float)wa * mt::inv_sw(pq);
@@ -363,12 +376,25 @@ struct Pick {
     // the k-th smallest (K << 32 | row(i)) of the candidates (at least k of them)
     template <class F>
     __device__ __forceinline__ u64 kth_key(uint32_t k, F &&row) {
-        const uint32_t K = kth(k), below = count([&](int j) { return kv[j] < K; });
-        if (count([&](int j) { return kv[j] == K; }) > 1) return ((u64)K << 32) | nth_row(K, k - below, row);
-        __shared__ uint32_t s_row;  // the only one, as nearly always
+        // nearly always a few candidates have the k-th K: each finds its row's rank among theirs
+        __shared__ uint32_t s_tied[64], s_n, s_row;
+        const uint32_t K = kth(k);
+        if (threadIdx.x == 0) s_n = 0;  // (read after the next count's barrier)
+        const uint32_t need = k - count([&](int j) { return kv[j] < K; });
 #pragma unroll
         for (int j = 0; j < R; j++)
-            if (kv[j] == K) s_row = row(threadIdx.x + (uint32_t)kBlock * j);
+            if (kv[j] == K) {
+                const uint32_t at = atomicAdd(&s_n, 1u);
+                if (at < 64) s_tied[at] = row(threadIdx.x + (uint32_t)kBlock * j);
+            }
+        __syncthreads();
+        const uint32_t tied = s_n;
+        if (tied > 64) return ((u64)K << 32) | nth_row(K, need, row);
+        if (threadIdx.x < tied) {
+            uint32_t rank = 0;
+            for (uint32_t j = 0; j < tied; j++) rank += s_tied[j] < s_tied[threadIdx.x];
+            if (rank == need - 1) s_row = s_tied[threadIdx.x];
+        }
         __syncthreads();
         return ((u64)K << 32) | s_row;
     }
@@ -453,10 +479,10 @@ __global__ __launch_bounds__(kBlock) void select_emit_kernel(const uint32_t *__r
 }
 
 // thr[q] = the k-th smallest key (K << 32 | row) of the query's m <= kMaxGroups
-// sample minima (none if fewer are rows'); clears the pass's candidate counts
-// and its overflow count.  Every tstep-th row tile was sampled.  One block per query.
+// sample minima (m >= k); clears the pass's candidate counts and its overflow
+// count.  One block per query.
 __global__ __launch_bounds__(kBlock) void sample_threshold_kernel(const uint32_t *__restrict__ minima, uint32_t m,
-                                                                  uint64_t tstep, uint32_t nq, uint32_t k, u64 *__restrict__ thr,
+                                                                  uint64_t sample_step, uint32_t nq, uint32_t k, u64 *__restrict__ thr,
                                                                   uint32_t *__restrict__ cnt,
                                                                   uint32_t *__restrict__ n_redo,
                                                                   const uint32_t *__restrict__ nq_dev) {
@@ -467,16 +493,14 @@ __global__ __launch_bounds__(kBlock) void sample_threshold_kernel(const uint32_t
         if (qi == 0) *n_redo = 0;
     }
     if (nq_dev && qi >= *nq_dev) return;  // whole block
-    constexpr uint32_t kNoRowK = 0xFFFFFFFFu >> 5;
     auto key = [&](uint32_t i) { return minima[(uint64_t)i * nq + qi] >> 5; };
     auto row = [&](uint32_t i) {  // of group i = (tile i / 2, lane half i % 2), as scan_mfma_kernel's lanes hold them
         const uint32_t e = minima[(uint64_t)i * nq + qi] & 31;
-        return (uint32_t)((i >> 1) * tstep * kMidR + 32 * (e >> 4) + 8 * ((e >> 2) & 3) + 4 * (i & 1) + (e & 3));
+        const uint32_t slot = 32 * (e >> 4) + 8 * ((e >> 2) & 3) + 4 * (i & 1) + (e & 3);
+        return (uint32_t)sample_row(slot * (m / 2) + (i >> 1), sample_step);
     };
-    auto bound = [&](auto &&P) -> u64 {
-        return P.count([&](int j) { return P.kv[j] < kNoRowK; }) < k ? KEY_NONE : P.kth_key(k, row);
-    };
-    const u64 t = m <= 4 * kBlock ? bound(Pick<4>(key, m, s_part)) : bound(Pick<kMaxGroups / kBlock>(key, m, s_part));
+    const u64 t = m <= 4 * kBlock ? Pick<4>(key, m, s_part).kth_key(k, row)
+                                  : Pick<kMaxGroups / kBlock>(key, m, s_part).kth_key(k, row);
     if (threadIdx.x == 0) thr[qi] = t;
 }
 
@@ -514,11 +538,15 @@ MfmaLayout mfma_layout(uint64_t n, uint32_t nq, uint32_t k) {
     // to save (512 more per query cost about 0.1 us each query, a part of a
     // pass about 30 us), else the whole pass in one part.  At least 4 k groups
     // of 32 rows are sampled, so that k groups seldom share their nearest.
+    // Where all near rows lie in the first part, it lists r of them on average;
+    // for small k the sample's bound varies (k = 1: an exponential distribution,
+    // 13% of the queries past 8,192), so a split pass samples as for k = 4.
     const bool split = nq >= 512 && tiles / 8 * n_qt >= 8ull * kMidWaves * device_cus();
-    const uint64_t rows = std::max<uint64_t>(n / (split ? 4096 : 512) * k, (uint64_t)k * 128);
+    const uint32_t ks = split ? std::max(k, 4u) : k;
+    const uint64_t rows = std::max<uint64_t>(n / (split ? 4096 : 512) * ks, (uint64_t)k * 128);
     L.sample_tiles = std::min<uint64_t>({(rows + kMidR - 1) / kMidR, tiles, kMaxGroups / 2});
-    L.sample_step = tiles / L.sample_tiles;
-    for (uint64_t end = L.sample_tiles * 512 / k; 2 * end <= tiles; end *= 8) L.ends.push_back(end);
+    L.sample_step = (n << 32) / (L.sample_tiles * kMidR);
+    for (uint64_t end = L.sample_tiles * 512 / ks; 2 * end <= tiles; end *= 8) L.ends.push_back(end);
     L.ends.push_back(tiles);
     L.fb = brute_launch_shape(n, nq, k, 16, 0);
     size_t o = 0;
@@ -553,8 +581,10 @@ int mfma_run(const MfmaLayout &L, char *ws, const uint64_t *d_db, const uint64_t
     };
     {
         KernelTimer timer("wh_scan_mfma_sample", s);
-        hipLaunchKernelGGL(scan_mfma_kernel<true>, grid(L.sample_tiles), dim3(kMidBlock), lds, s, db4, n, 0ull,
-                           L.sample_tiles, L.sample_step, q4, nq, nullptr, nullptr, nullptr, minima, nq_dev);
+        // (a small sample one unit per workgroup: its scattered rows are a chain of misses)
+        const dim3 g((uint32_t)std::min<uint64_t>(L.sample_tiles * n_qt, device_cus()));
+        hipLaunchKernelGGL(scan_mfma_kernel<true>, g, dim3(kMidBlock), lds, s, db4, n, 0ull, L.sample_tiles,
+                           L.sample_step, q4, nq, nullptr, nullptr, nullptr, minima, nq_dev);
         hipLaunchKernelGGL(sample_threshold_kernel, dim3(nq), dim3(kBlock), 0, s, minima,
                            (uint32_t)(2 * L.sample_tiles), L.sample_step, nq, k, thr, cnt, n_redo, nq_dev);
     }
@@ -564,7 +594,7 @@ int mfma_run(const MfmaLayout &L, char *ws, const uint64_t *d_db, const uint64_t
             const uint64_t t0 = i ? L.ends[i - 1] : 0, nt = L.ends[i] - t0;
             if (i)
                 hipLaunchKernelGGL(tighten_kernel, dim3(nq), dim3(kBlock), 0, s, cnt, cand, k, thr, nq_dev);
-            hipLaunchKernelGGL(scan_mfma_kernel<false>, grid(nt), dim3(kMidBlock), lds, s, db4, n, t0, nt, 1ull, q4, nq,
+            hipLaunchKernelGGL(scan_mfma_kernel<false>, grid(nt), dim3(kMidBlock), lds, s, db4, n, t0, nt, 0ull, q4, nq,
                                thr, cnt, cand, nullptr, nq_dev);
         }
     }

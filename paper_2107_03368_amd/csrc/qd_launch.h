@@ -75,7 +75,7 @@ int brute_launch(const BruteLaunch &L, u64 *part, const uint64_t *d_db, uint64_t
 // databases (mfma_eligible).
 struct MfmaLayout {
     uint64_t n = 0;
-    uint64_t sample_tiles = 0, sample_step = 1;  // every sample_step-th row tile is sampled
+    uint64_t sample_tiles = 0, sample_step = 0;  // tiles of sampled rows; n / their rows in 32.32 fixed point
     std::vector<uint64_t> ends;                  // the row tile each part of the pass ends before
     BruteLaunch fb;                              // the fallback for overflowed queries
     size_t minima = 0, thr = 0, cnt = 0, cand = 0, redo = 0, n_redo = 0, fb_part = 0, bytes = 0;
