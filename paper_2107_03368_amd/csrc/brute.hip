@@ -39,8 +39,7 @@ __global__ __launch_bounds__(kBlock) void scan_topk_kernel(const uint4 *__restri
                                                            const uint4 *__restrict__ q, uint32_t nq, uint32_t k,
                                                            uint32_t n_qtiles, uint32_t n_parts,
                                                            uint64_t rows_per_part, u64 *__restrict__ part,
-                                                           const uint32_t *__restrict__ nq_dev,
-                                                           const uint32_t *__restrict__ qmap) {
+                                                           const uint32_t *__restrict__ nq_dev) {
     if (nq_dev) {
         nq = *nq_dev;  // size given on the device (captured graphs)
         if ((blockIdx.x % n_qtiles) * QT >= nq) return;  // whole block
@@ -60,11 +59,10 @@ __global__ __launch_bounds__(kBlock) void scan_topk_kernel(const uint4 *__restri
 #pragma unroll
     for (int t = 0; t < QT; t++) {
         const uint32_t qi = qtile * QT + t;
-        const uint64_t qr = qi < nq && qmap ? qmap[qi] : qi;  // the query's row
         uint32_t s = 0;
 #pragma unroll
         for (int i = 0; i < 4; i++) {
-            qv[t][i] = qi < nq ? q[qr * 32 + j + 8 * i] : make_uint4(0, 0, 0, 0);
+            qv[t][i] = qi < nq ? q[(uint64_t)qi * 32 + j + 8 * i] : make_uint4(0, 0, 0, 0);
             s += popc4(qv[t][i]);
         }
         pq[t] = readfirst(sum8(s));
@@ -266,15 +264,13 @@ __device__ inline void sort_keys(u64 *a, uint32_t n) {
 //  2. Those heads are sorted; the first k of them name the lists.
 //  3. The lists' entries <= U are gathered (at most k * k) and sorted.
 // Bound by the latency of its three dependent loads (heads, entries, rows).
-// qmap (nullable): list set i belongs to row qmap[i] of q and of the outputs.
 // 8 queries x 2,048 lists, k = 10: 12 us; sorting every head in LDS and one
 // thread per result row took 49 us.
 __global__ __launch_bounds__(kBlock) void merge_emit_kernel(const u64 *__restrict__ part, uint32_t n_parts,
                                                             uint32_t k, const uint64_t *__restrict__ q,
                                                             const uint64_t *__restrict__ db, uint32_t *idx,
                                                             int32_t *missed, int32_t *extra, float *dist,
-                                                            const uint32_t *__restrict__ nq_dev,
-                                                            const uint32_t *__restrict__ qmap) {
+                                                            const uint32_t *__restrict__ nq_dev) {
     if (nq_dev && blockIdx.x >= *nq_dev) return;  // whole block
     constexpr uint32_t kHeads = kMaxParts / kBlock;
     __shared__ u64 least[kBlock];
@@ -341,9 +337,8 @@ __global__ __launch_bounds__(kBlock) void merge_emit_kernel(const u64 *__restric
     const uint32_t nc = ncand;
     sort_keys(cand, nc);
     // (every list entry taken is a real key: the ranks past them are padded)
-    const uint64_t qr = qmap ? qmap[qi] : qi;
-    emit_rows(cand, nc, k, reinterpret_cast<const uint4 *>(q) + qr * 32, reinterpret_cast<const uint4 *>(db), qr * k, idx,
-              missed, extra, dist);
+    emit_rows(cand, nc, k, reinterpret_cast<const uint4 *>(q) + (uint64_t)qi * 32, reinterpret_cast<const uint4 *>(db),
+              (uint64_t)qi * k, idx, missed, extra, dist);
 }
 
 __global__ __launch_bounds__(kBlock) void popcount_rows_kernel(const uint4 *__restrict__ db, uint64_t n,
@@ -387,10 +382,9 @@ uint64_t small_mfma_resident_waves(uint32_t k) {
 
 template <int QT>
 void launch_scan(dim3 grid, hipStream_t s, const uint4 *db, uint64_t n, const uint4 *q, uint32_t nq, uint32_t k,
-                 uint32_t n_qtiles, uint32_t n_parts, uint64_t rpp, u64 *part, const uint32_t *nq_dev,
-                 const uint32_t *qmap) {
+                 uint32_t n_qtiles, uint32_t n_parts, uint64_t rpp, u64 *part, const uint32_t *nq_dev) {
     hipLaunchKernelGGL(scan_topk_kernel<QT>, grid, dim3(kBlock), 0, s, db, n, q, nq, k, n_qtiles, n_parts, rpp, part,
-                       nq_dev, qmap);
+                       nq_dev);
 }
 
 }  // namespace
@@ -442,8 +436,7 @@ BruteLaunch brute_launch_shape(uint64_t n, uint32_t nq, uint32_t k, uint32_t qt_
 
 int brute_launch(const BruteLaunch &sh, u64 *part, const uint64_t *d_db, uint64_t n, const uint64_t *d_q, uint32_t nq,
                  const uint32_t *nq_dev, uint32_t k, uint32_t *d_idx, int32_t *d_missed, int32_t *d_extra,
-                 float *d_dist, hipStream_t s, bool timed, const uint32_t *qmap) {
-    if (qmap && sh.qt == QD_QUERY_TILE_MATRIX) return fail(QD_ERR_INVALID, "a query list takes the vector scan");
+                 float *d_dist, hipStream_t s, bool timed) {
     // the dispatch packet holds the grid size in work-items as a 32-bit number
     if (sh.blocks * kBlock > 0xFFFFFFFFull) return fail(QD_ERR_UNSUPPORTED, "launch too large");
     const uint4 *db4 = reinterpret_cast<const uint4 *>(d_db);
@@ -456,18 +449,18 @@ int brute_launch(const BruteLaunch &sh, u64 *part, const uint64_t *d_db, uint64_
     } else {
         KernelTimer timer(timed ? "wh_scan_topk" : nullptr, s);
         switch (sh.qt) {
-            case 1: launch_scan<1>(grid, s, db4, n, q4, nq, k, sh.n_qtiles, sh.n_parts, sh.rows_per_part, part, nq_dev, qmap); break;
-            case 2: launch_scan<2>(grid, s, db4, n, q4, nq, k, sh.n_qtiles, sh.n_parts, sh.rows_per_part, part, nq_dev, qmap); break;
-            case 4: launch_scan<4>(grid, s, db4, n, q4, nq, k, sh.n_qtiles, sh.n_parts, sh.rows_per_part, part, nq_dev, qmap); break;
-            case 8: launch_scan<8>(grid, s, db4, n, q4, nq, k, sh.n_qtiles, sh.n_parts, sh.rows_per_part, part, nq_dev, qmap); break;
-            default: launch_scan<16>(grid, s, db4, n, q4, nq, k, sh.n_qtiles, sh.n_parts, sh.rows_per_part, part, nq_dev, qmap); break;
+            case 1: launch_scan<1>(grid, s, db4, n, q4, nq, k, sh.n_qtiles, sh.n_parts, sh.rows_per_part, part, nq_dev); break;
+            case 2: launch_scan<2>(grid, s, db4, n, q4, nq, k, sh.n_qtiles, sh.n_parts, sh.rows_per_part, part, nq_dev); break;
+            case 4: launch_scan<4>(grid, s, db4, n, q4, nq, k, sh.n_qtiles, sh.n_parts, sh.rows_per_part, part, nq_dev); break;
+            case 8: launch_scan<8>(grid, s, db4, n, q4, nq, k, sh.n_qtiles, sh.n_parts, sh.rows_per_part, part, nq_dev); break;
+            default: launch_scan<16>(grid, s, db4, n, q4, nq, k, sh.n_qtiles, sh.n_parts, sh.rows_per_part, part, nq_dev); break;
         }
     }
     QD_HIP_CHECK(hipGetLastError());
     {
         KernelTimer timer(timed ? "topk_merge" : nullptr, s);
         hipLaunchKernelGGL(merge_emit_kernel, dim3(nq), dim3(kBlock), 0, s, part, sh.n_parts, k, d_q, d_db, d_idx,
-                           d_missed, d_extra, d_dist, nq_dev, qmap);
+                           d_missed, d_extra, d_dist, nq_dev);
     }
     QD_HIP_CHECK(hipGetLastError());
     return QD_OK;
@@ -479,7 +472,7 @@ int merge_launch(const u64 *part, uint32_t n_parts, uint32_t k, const uint64_t *
                                                         kMaxParts);
     KernelTimer timer("topk_merge", s);
     hipLaunchKernelGGL(merge_emit_kernel, dim3(nq), dim3(kBlock), 0, s, part, n_parts, k, d_q, d_db, d_idx, d_missed,
-                       d_extra, d_dist, nullptr, nullptr);
+                       d_extra, d_dist, nullptr);
     QD_HIP_CHECK(hipGetLastError());
     return QD_OK;
 }

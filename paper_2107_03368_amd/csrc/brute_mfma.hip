@@ -14,9 +14,11 @@
 // lists about 7 k rows per query.  A bound is a full key (K << 32 | row): of
 // rows with equal K (repeated or blank descriptors, a blank query) only those
 // up to the bound's row are kept, so ties do not fill the buffer.  A final kernel selects each query's k best
-// candidates and writes the results; queries whose buffer overflowed are
-// searched again by the register-tiled scan, so the result is exact in every
-// case.
+// candidates and writes the results.  A query whose buffer overflowed, which
+// takes rows whose order meets the sample's, is bounded by the k-th smallest of
+// the candidates it holds (rows all the same) and passed over the rows once
+// more, with the others like it only; should it overflow again, one workgroup
+// reads all rows for it, so the result is exact in every case.
 #include <algorithm>
 #include <vector>
 
@@ -26,11 +28,6 @@
 #include "qd_launch.h"
 
 namespace qd {
-
-int knn_bruteforce_impl(const uint64_t *d_db, uint64_t n, const uint64_t *d_q, uint32_t nq, uint32_t k,
-                        uint32_t *d_idx, int32_t *d_missed, int32_t *d_extra, float *d_dist, void *stream,
-                        uint32_t qt_force, uint32_t parts_force);
-int popcount_rows_launch(const uint64_t *d_db, uint64_t n, uint16_t *d_pop, hipStream_t s);
 
 namespace {
 
@@ -91,6 +88,7 @@ struct MidSmem {
     uint32_t pop[kGroupQ];            // |q|
     u64 thr[kGroupQ];                 // candidate bound
     float bound[kGroupQ];             // pass test's bound
+    uint32_t id[kGroupQ];             // kAgain: the query's number
     float tp[kMidWaves][kMidR];       // per wave: its rows' |t|
     uint32_t queue[kMidWaves][kMidQueue][3];  // per wave: passing (query, key, row)
 };
@@ -99,12 +97,15 @@ inline size_t mid_lds_bytes(uint32_t nq) {
     return sizeof(MidSmem) + (size_t)q * kMidStride;
 }
 
-template <bool kSample>
+// kAgain: the queries are those of `list`.
+enum Pass { kFirst, kSample, kAgain };
+template <Pass kPass>
 __global__ __launch_bounds__(kMidBlock, 2) void scan_mfma_kernel(const uint4 *__restrict__ db, uint64_t n, uint64_t t0,
                                                                  uint64_t tiles, uint64_t sample_step,
                                                                  const uint4 *__restrict__ q, uint32_t nq,
                                                                  const u64 *__restrict__ thr, uint32_t *__restrict__ cnt,
                                                                  u64 *__restrict__ cand, uint32_t *__restrict__ minima,
+                                                                 const uint32_t *__restrict__ list,
                                                                  const uint32_t *__restrict__ nq_dev) {
     extern __shared__ __align__(16) uint8_t s_raw[];
     MidSmem &sm = *reinterpret_cast<MidSmem *>(s_raw);
@@ -125,11 +126,14 @@ __global__ __launch_bounds__(kMidBlock, 2) void scan_mfma_kernel(const uint4 *__
     const uint64_t ub = ua + units / gridDim.x + (blockIdx.x < units % gridDim.x ? 1 : 0);
 
     uint32_t nqe = 0;  // entries in this wave's queue (the same in every lane)
-    auto flush = [&]() {
+    auto flush = [&](uint32_t q0) {
         for (uint32_t e = lane; e < nqe; e += 64) {
-            const uint32_t qk = cq[e][0];
+            const uint32_t qs = cq[e][0], qk = kPass == kAgain ? sm.id[qs] : q0 + qs;
             const uint32_t pos = atomicAdd(&cnt[qk], 1u);
-            if (pos < kCap) cand[(uint64_t)qk * kCap + pos] = ((u64)cq[e][1] << 32) | cq[e][2];
+            if (pos < kCap)
+                cand[(uint64_t)qk * kCap + pos] = ((u64)cq[e][1] << 32) | cq[e][2];
+            else  // the query is searched again: no more of its rows here
+                sm.bound[qs] = mt::kNoBound;
         }
         nqe = 0;
     };
@@ -141,16 +145,19 @@ __global__ __launch_bounds__(kMidBlock, 2) void scan_mfma_kernel(const uint4 *__
         const uint64_t rb = min((ub - g0) / gqt, tiles);
         __syncthreads();  // every wave is done with the group before
         for (uint32_t e = threadIdx.x; e < gqt * kMidQ * 32; e += kMidBlock) {
-            const uint32_t qi = q0 + (e >> 5);
-            const uint4 x = qi < nq ? q[(uint64_t)qi * 32 + (e & 31)] : make_uint4(0, 0, 0, 0);
+            uint32_t qi = q0 + (e >> 5);
+            const bool real = qi < nq;
+            if (kPass == kAgain) qi = list[real ? qi : 0];
+            const uint4 x = real ? q[(uint64_t)qi * 32 + (e & 31)] : make_uint4(0, 0, 0, 0);
             *reinterpret_cast<uint4 *>(s_q + (size_t)(e >> 5) * kMidStride + (e & 31) * 16) = x;
             const uint32_t pq = sum32_half(popc4(x));  // a half wave holds one query
             if ((e & 31) == 0) {
                 const uint32_t wb = (QD_BITS - pq) > 1 ? QD_BITS - pq : 1;
-                const u64 th = !kSample && qi < nq ? thr[qi] : 0;
+                const u64 th = kPass != kSample && real ? thr[qi] : 0;
                 sm.pop[e >> 5] = pq;
                 sm.thr[e >> 5] = th;
-                sm.bound[e >> 5] = qi < nq ? mt::pass_bound(pq, wb, (uint32_t)(th >> 32)) : mt::kNoBound;
+                if (kPass == kAgain) sm.id[e >> 5] = qi;
+                sm.bound[e >> 5] = real ? mt::pass_bound(pq, wb, (uint32_t)(th >> 32)) : mt::kNoBound;
             }
         }
         __syncthreads();
@@ -165,8 +172,8 @@ __global__ __launch_bounds__(kMidBlock, 2) void scan_mfma_kernel(const uint4 *__
         auto load = [&](uint64_t r, int L, uint4 (&x)[2][4]) {
 #pragma unroll
             for (int b = 0; b < 2; b++) {
-                uint64_t row = kSample ? sample_row((uint32_t)((32 * b + li) * tiles + r), sample_step)
-                                       : (t0 + r) * kMidR + 32 * b + li;
+                uint64_t row = kPass == kSample ? sample_row((uint32_t)((32 * b + li) * tiles + r), sample_step)
+                                                : (t0 + r) * kMidR + 32 * b + li;
                 row = row < n ? row : n - 1;
                 const uint4 *src = db + row * 32 + 8 * L + lh;
 #pragma unroll
@@ -236,7 +243,7 @@ __global__ __launch_bounds__(kMidBlock, 2) void scan_mfma_kernel(const uint4 *__
 #pragma unroll
             for (int b = 0; b < 2; b++) {
                 tcur[b] += (uint32_t)__shfl_xor((int)tcur[b], 32);
-                if (lh == b) tpw[32 * b + li] = kSample || row0 + 32 * b + li < n ? (float)tcur[b] : mt::kNoRow;
+                if (lh == b) tpw[32 * b + li] = kPass == kSample || row0 + 32 * b + li < n ? (float)tcur[b] : mt::kNoRow;
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
@@ -247,7 +254,7 @@ __global__ __launch_bounds__(kMidBlock, 2) void scan_mfma_kernel(const uint4 *__
                 const float bound = sm.bound[qs];
                 const uint32_t pq = sm.pop[qs];
                 const uint32_t wa = pq > 1 ? pq : 1, wb = (QD_BITS - pq) > 1 ? QD_BITS - pq : 1;
-                if (kSample) {
+                if (kPass == kSample) {
                     // K = |q|*wB - (C*(wA + wB) - |t|*wA), exact in fp32 (integers
                     // below 2^24, but for C = |q| = 4096: 4096 * 4097 is even)
                     const float sw = (float)(wa + wb), nwa = -(float)wa;
@@ -299,12 +306,12 @@ __global__ __launch_bounds__(kMidBlock, 2) void scan_mfma_kernel(const uint4 *__
                             const u64 pm = ballot(pass);
                             if (pass) {
                                 const uint32_t at = nqe + lanes_below(pm);
-                                cq[at][0] = q0 + qs;
+                                cq[at][0] = qs;
                                 cq[at][1] = K;
                                 cq[at][2] = row;
                             }
                             nqe += (uint32_t)__popcll(pm);
-                            if (nqe > kMidQueue - 64) flush();  // the next row adds at most 64
+                            if (nqe > kMidQueue - 64) flush(q0);  // the next row adds at most 64
                         }
                     }
                 }
@@ -315,8 +322,8 @@ __global__ __launch_bounds__(kMidBlock, 2) void scan_mfma_kernel(const uint4 *__
             rt = nrt;
             qrow = nqrow;
         }
+        flush(q0);
     }
-    flush();
 }
 
 // Selection among a query's m <= kCap candidates by the whole block: thread t
@@ -409,6 +416,7 @@ __global__ __launch_bounds__(kBlock) void tighten_kernel(const uint32_t *__restr
     const uint32_t qi = blockIdx.x;
     if (nq_dev && qi >= *nq_dev) return;  // whole block
     const uint32_t m = cnt[qi];
+    if (m > kCap && threadIdx.x == 0) thr[qi] = 0;  // searched again: nothing more is listed now
     if (m < k || m > kCap) return;
     const u64 *c = cand + (uint64_t)qi * kCap;
     auto key = [&](uint32_t i) { return (uint32_t)(c[i] >> 32); };
@@ -441,41 +449,131 @@ __device__ __forceinline__ void pick_keys(const u64 *cand, uint32_t m, uint32_t 
     }
 }
 
-// One block per query: the k best of its candidates (<= kCap), in order, and
-// their results.  Overflowed queries are left for the fallback and listed in
-// `redo`.  Selecting before sorting leaves a few keys to order: 0.08 ms for
+// The k best of a query's m <= kCap candidates into keys[0 .. result), in
+// order, by the whole block (up to kBlock of them, at least k if m is).
+// Selecting before sorting leaves a few keys to order: 0.08 ms for
 // 4,096 queries with 1,000 candidates each, where sorting them all took 0.32.
-__global__ __launch_bounds__(kBlock) void select_emit_kernel(const uint32_t *__restrict__ cnt,
-                                                             const u64 *__restrict__ cand, uint32_t k,
-                                                             const uint4 *__restrict__ q, const uint4 *__restrict__ db,
-                                                             uint32_t *idx, int32_t *missed, int32_t *extra,
-                                                             float *dist, uint32_t *redo, uint32_t *n_redo,
+__device__ __forceinline__ uint32_t best_candidates(const u64 *c, uint32_t m, uint32_t k, uint32_t (*s_part)[4],
+                                                    u64 *keys, uint32_t *s_n) {
+    uint32_t nk = m;
+    if (m <= (uint32_t)kBlock) {
+        if (threadIdx.x < m) keys[threadIdx.x] = c[threadIdx.x];
+    } else {  // m > k
+        if (threadIdx.x == 0) *s_n = 0;  // read after the selection's barriers
+        if (m <= 4 * kBlock)
+            pick_keys<4>(c, m, k, s_part, keys, s_n);
+        else
+            pick_keys<kCap / kBlock>(c, m, k, s_part, keys, s_n);
+        __syncthreads();
+        nk = *s_n;
+    }
+    __syncthreads();
+    rank_sort(keys, nk);
+    return nk;
+}
+
+// The k best of all n rows for one query, in order, into keys[0 .. k), by the
+// whole block; thr: the key of a k-th row or of a later one.  8 lanes per row,
+// 128 rows a step; the keys up to the bound are collected and cut to the k
+// smallest whenever 128 are there.  For a query that overflows twice only.
+__device__ __forceinline__ void best_of_all(const uint4 *db, uint64_t n, const uint4 *q, uint32_t k, u64 thr, u64 *keys,
+                                            uint32_t *s_n) {
+    const int g = threadIdx.x >> 3, j = threadIdx.x & 7;
+    uint4 qv[4];
+    uint32_t pq = 0;
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        qv[i] = q[j + 8 * i];
+        pq += popc4(qv[i]);
+    }
+    pq = sum8(pq);
+    const uint32_t wa = pq > 1 ? pq : 1, wb = (QD_BITS - pq) > 1 ? QD_BITS - pq : 1;
+    if (threadIdx.x == 0) *s_n = 0;
+    __syncthreads();
+    for (uint64_t base = 0; base < n; base += 4 * (kBlock / 8)) {
+        uint32_t c[4], tp[4];
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+            const uint64_t r = base + u * (kBlock / 8) + g, row = r < n ? r : n - 1;
+            c[u] = tp[u] = 0;
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const uint4 t = db[row * 32 + j + 8 * i];
+                c[u] += popc_and4(t, qv[i]);
+                tp[u] += popc4(t);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+            const uint64_t r = base + u * (kBlock / 8) + g;
+            const uint32_t o = sum8(c[u]), a = pq - o, b = sum8(tp[u]) - o;
+            const u64 key = ((u64)(a * wb + b * wa) << 32) | (uint32_t)r;
+            if (j == 0 && r < n && key <= thr) keys[atomicAdd(s_n, 1u)] = key;
+        }
+        __syncthreads();
+        const uint32_t m = *s_n;
+        __syncthreads();  // every thread has read it
+        if (m > (uint32_t)kBlock / 2 || base + 4 * (kBlock / 8) >= n) {
+            rank_sort(keys, m);
+            if (m > k) thr = keys[k - 1];
+            if (threadIdx.x == 0) *s_n = m < k ? m : k;
+            __syncthreads();
+        }
+    }
+}
+
+// One block per query: the k best of its candidates and their results.  An
+// overflowed query (its candidates held are any kCap of the rows that passed)
+// is listed in `list` for another pass, bounded by the k-th smallest of them.
+__global__ __launch_bounds__(kBlock) void select_emit_kernel(uint32_t *__restrict__ cnt, const u64 *__restrict__ cand,
+                                                             uint32_t k, const uint4 *__restrict__ q,
+                                                             const uint4 *__restrict__ db, uint32_t *idx,
+                                                             int32_t *missed, int32_t *extra, float *dist,
+                                                             u64 *__restrict__ thr, uint32_t *__restrict__ list,
+                                                             uint32_t *__restrict__ n_list,
                                                              const uint32_t *__restrict__ nq_dev) {
     __shared__ u64 keys[kBlock];
     __shared__ uint32_t s_part[2][4], s_n;
     const uint32_t qi = blockIdx.x;
     if (nq_dev && qi >= *nq_dev) return;  // whole block
     const uint32_t m = cnt[qi];
+    const u64 *c = cand + (uint64_t)qi * kCap;
     if (m > kCap) {
-        if (threadIdx.x == 0) redo[atomicAdd(n_redo, 1u)] = qi;
+        const u64 t = Pick<kCap / kBlock>([&](uint32_t i) { return (uint32_t)(c[i] >> 32); }, kCap, s_part)
+                          .kth_key(k, [&](uint32_t i) { return (uint32_t)c[i]; });
+        if (threadIdx.x == 0) {
+            list[atomicAdd(n_list, 1u)] = qi;
+            thr[qi] = t;
+            cnt[qi] = 0;
+        }
         return;
     }
-    const u64 *c = cand + (uint64_t)qi * kCap;
-    uint32_t nk = m;
-    if (m <= (uint32_t)kBlock) {
-        if (threadIdx.x < m) keys[threadIdx.x] = c[threadIdx.x];
-    } else {  // m > k
-        if (threadIdx.x == 0) s_n = 0;  // read after the selection's barriers
-        if (m <= 4 * kBlock)
-            pick_keys<4>(c, m, k, s_part, keys, &s_n);
-        else
-            pick_keys<kCap / kBlock>(c, m, k, s_part, keys, &s_n);
-        __syncthreads();
-        nk = s_n;
-    }
-    __syncthreads();
-    rank_sort(keys, nk);
+    const uint32_t nk = best_candidates(c, m, k, s_part, keys, &s_n);
     emit_rows(keys, nk < k ? nk : k, k, q + (uint64_t)qi * 32, db, (uint64_t)qi * k, idx, missed, extra, dist);
+}
+
+// The results of the queries that were passed over the rows again.
+__global__ __launch_bounds__(kBlock) void select_again_kernel(const uint32_t *__restrict__ cnt,
+                                                              const u64 *__restrict__ cand, uint32_t k,
+                                                              const uint4 *__restrict__ q,
+                                                              const uint4 *__restrict__ db, uint64_t n, uint32_t *idx,
+                                                              int32_t *missed, int32_t *extra, float *dist,
+                                                              const u64 *__restrict__ thr,
+                                                              const uint32_t *__restrict__ list,
+                                                              const uint32_t *__restrict__ n_list) {
+    __shared__ u64 keys[kBlock];
+    __shared__ uint32_t s_part[2][4], s_n;
+    const uint32_t n_again = *n_list;
+    for (uint32_t i = blockIdx.x; i < n_again; i += gridDim.x) {
+        const uint32_t qi = list[i], m = cnt[qi];
+        uint32_t nk = k;
+        if (m <= kCap)
+            nk = best_candidates(cand + (uint64_t)qi * kCap, m, k, s_part, keys, &s_n);
+        else
+            best_of_all(db, n, q + (uint64_t)qi * 32, k, thr[qi], keys, &s_n);
+        emit_rows(keys, nk < k ? nk : k, k, q + (uint64_t)qi * 32, db, (uint64_t)qi * k, idx, missed, extra, dist);
+        __syncthreads();  // the next query writes over the keys
+    }
 }
 
 // thr[q] = the k-th smallest key (K << 32 | row) of the query's m <= kMaxGroups
@@ -484,13 +582,13 @@ __global__ __launch_bounds__(kBlock) void select_emit_kernel(const uint32_t *__r
 __global__ __launch_bounds__(kBlock) void sample_threshold_kernel(const uint32_t *__restrict__ minima, uint32_t m,
                                                                   uint64_t sample_step, uint32_t nq, uint32_t k, u64 *__restrict__ thr,
                                                                   uint32_t *__restrict__ cnt,
-                                                                  uint32_t *__restrict__ n_redo,
+                                                                  uint32_t *__restrict__ n_again,
                                                                   const uint32_t *__restrict__ nq_dev) {
     __shared__ uint32_t s_part[2][4];
     const uint32_t qi = blockIdx.x;
     if (threadIdx.x == 0) {
         cnt[qi] = 0;
-        if (qi == 0) *n_redo = 0;
+        if (qi == 0) *n_again = 0;
     }
     if (nq_dev && qi >= *nq_dev) return;  // whole block
     auto key = [&](uint32_t i) { return minima[(uint64_t)i * nq + qi] >> 5; };
@@ -548,7 +646,6 @@ MfmaLayout mfma_layout(uint64_t n, uint32_t nq, uint32_t k) {
     L.sample_step = (n << 32) / (L.sample_tiles * kMidR);
     for (uint64_t end = L.sample_tiles * 512 / ks; 2 * end <= tiles; end *= 8) L.ends.push_back(end);
     L.ends.push_back(tiles);
-    L.fb = brute_launch_shape(n, nq, k, 16, 0);
     size_t o = 0;
     auto take = [&](size_t b) {
         const size_t at = o;
@@ -559,9 +656,8 @@ MfmaLayout mfma_layout(uint64_t n, uint32_t nq, uint32_t k) {
     L.thr = take((size_t)nq * 8);
     L.cnt = take((size_t)nq * 4);
     L.cand = take((size_t)nq * kCap * 8);
-    L.redo = take((size_t)nq * 4);
-    L.n_redo = take(4);
-    L.fb_part = take(L.fb.part_bytes);
+    L.again = take((size_t)nq * 4);
+    L.n_again = take(4);
     L.bytes = o;
     return L;
 }
@@ -572,7 +668,7 @@ int mfma_run(const MfmaLayout &L, char *ws, const uint64_t *d_db, const uint64_t
     const uint64_t n = L.n, n_qt = (nq + kMidQ - 1) / kMidQ;
     u64 *thr = (u64 *)(ws + L.thr), *cand = (u64 *)(ws + L.cand);
     uint32_t *minima = (uint32_t *)(ws + L.minima), *cnt = (uint32_t *)(ws + L.cnt),
-             *redo = (uint32_t *)(ws + L.redo), *n_redo = (uint32_t *)(ws + L.n_redo);
+             *again = (uint32_t *)(ws + L.again), *n_again = (uint32_t *)(ws + L.n_again);
     const uint4 *db4 = reinterpret_cast<const uint4 *>(d_db), *q4 = reinterpret_cast<const uint4 *>(d_q);
     const size_t lds = mid_lds_bytes(nq);
     // one workgroup per CU (registers), fewer when there are fewer units
@@ -583,10 +679,10 @@ int mfma_run(const MfmaLayout &L, char *ws, const uint64_t *d_db, const uint64_t
         KernelTimer timer("wh_scan_mfma_sample", s);
         // (a small sample one unit per workgroup: its scattered rows are a chain of misses)
         const dim3 g((uint32_t)std::min<uint64_t>(L.sample_tiles * n_qt, device_cus()));
-        hipLaunchKernelGGL(scan_mfma_kernel<true>, g, dim3(kMidBlock), lds, s, db4, n, 0ull, L.sample_tiles,
-                           L.sample_step, q4, nq, nullptr, nullptr, nullptr, minima, nq_dev);
+        hipLaunchKernelGGL(scan_mfma_kernel<kSample>, g, dim3(kMidBlock), lds, s, db4, n, 0ull, L.sample_tiles,
+                           L.sample_step, q4, nq, nullptr, nullptr, nullptr, minima, nullptr, nq_dev);
         hipLaunchKernelGGL(sample_threshold_kernel, dim3(nq), dim3(kBlock), 0, s, minima,
-                           (uint32_t)(2 * L.sample_tiles), L.sample_step, nq, k, thr, cnt, n_redo, nq_dev);
+                           (uint32_t)(2 * L.sample_tiles), L.sample_step, nq, k, thr, cnt, n_again, nq_dev);
     }
     {
         KernelTimer timer("wh_scan_mfma", s);
@@ -594,22 +690,23 @@ int mfma_run(const MfmaLayout &L, char *ws, const uint64_t *d_db, const uint64_t
             const uint64_t t0 = i ? L.ends[i - 1] : 0, nt = L.ends[i] - t0;
             if (i)
                 hipLaunchKernelGGL(tighten_kernel, dim3(nq), dim3(kBlock), 0, s, cnt, cand, k, thr, nq_dev);
-            hipLaunchKernelGGL(scan_mfma_kernel<false>, grid(nt), dim3(kMidBlock), lds, s, db4, n, t0, nt, 0ull, q4, nq,
-                               thr, cnt, cand, nullptr, nq_dev);
+            hipLaunchKernelGGL(scan_mfma_kernel<kFirst>, grid(nt), dim3(kMidBlock), lds, s, db4, n, t0, nt, 0ull, q4,
+                               nq, thr, cnt, cand, nullptr, nullptr, nq_dev);
         }
     }
     {
         KernelTimer timer("topk_select", s);
         hipLaunchKernelGGL(select_emit_kernel, dim3(nq), dim3(kBlock), 0, s, cnt, cand, k, q4, db4, d_idx, d_missed,
-                           d_extra, d_dist, redo, n_redo, nq_dev);
+                           d_extra, d_dist, thr, again, n_again, nq_dev);
     }
+    // the overflowed queries, whose list and count stay on the device: without
+    // any these launches find no work
+    hipLaunchKernelGGL(scan_mfma_kernel<kAgain>, grid(L.ends.back()), dim3(kMidBlock), lds, s, db4, n, 0ull,
+                       L.ends.back(), 0ull, q4, nq, thr, cnt, cand, nullptr, again, n_again);
+    hipLaunchKernelGGL(select_again_kernel, dim3(std::min<uint32_t>(nq, device_cus())), dim3(kBlock), 0, s, cnt, cand,
+                       k, q4, db4, n, d_idx, d_missed, d_extra, d_dist, thr, again, n_again);
     const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return fail(QD_ERR_DEVICE, "matrix-core scan: %s", hipGetErrorString(e));
-    // queries whose candidate buffer overflowed: searched again by the
-    // register-tiled scan; their list and count stay on the device, so an
-    // empty fallback only costs launches that find no work
-    return brute_launch(L.fb, reinterpret_cast<u64 *>(ws + L.fb_part), d_db, n, d_q, nq, n_redo, k, d_idx, d_missed,
-                        d_extra, d_dist, s, /*timed=*/false, redo);
+    return e == hipSuccess ? QD_OK : fail(QD_ERR_DEVICE, "matrix-core scan: %s", hipGetErrorString(e));
 }
 
 // Matrix-core path for large batches; returns QD_ERR_UNSUPPORTED when the

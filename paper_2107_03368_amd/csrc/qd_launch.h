@@ -64,10 +64,9 @@ struct BruteLaunch {
     size_t part_bytes = 0;
 };
 BruteLaunch brute_launch_shape(uint64_t n, uint32_t nq_max, uint32_t k, uint32_t qt_force, uint32_t parts_force);
-// qmap (nullable; vector-ALU tiles only): query i is row qmap[i] of d_q and of the outputs.
 int brute_launch(const BruteLaunch &L, u64 *part, const uint64_t *d_db, uint64_t n, const uint64_t *d_q, uint32_t nq,
                  const uint32_t *nq_dev, uint32_t k, uint32_t *d_idx, int32_t *d_missed, int32_t *d_extra,
-                 float *d_dist, hipStream_t s, bool timed = true, const uint32_t *qmap = nullptr);
+                 float *d_dist, hipStream_t s, bool timed = true);
 
 // The matrix-core sequential search on a workspace the caller owns: a sample
 // pass for the candidate bounds, then the matrix pass (brute_mfma.hip).
@@ -77,8 +76,7 @@ struct MfmaLayout {
     uint64_t n = 0;
     uint64_t sample_tiles = 0, sample_step = 0;  // tiles of sampled rows; n / their rows in 32.32 fixed point
     std::vector<uint64_t> ends;                  // the row tile each part of the pass ends before
-    BruteLaunch fb;                              // the fallback for overflowed queries
-    size_t minima = 0, thr = 0, cnt = 0, cand = 0, redo = 0, n_redo = 0, fb_part = 0, bytes = 0;
+    size_t minima = 0, thr = 0, cnt = 0, cand = 0, again = 0, n_again = 0, bytes = 0;
 };
 // Whether a batch of nq queries over n rows takes the matrix cores.
 bool mfma_eligible(uint64_t n, uint32_t nq, uint32_t k);

@@ -121,3 +121,59 @@ def test_periodic_rows(period):
     res = qd.knn_bruteforce(_t(db), _t(q), K)
     assert np.array_equal(res[0].cpu().numpy().view(np.uint32), o.idx)
     assert np.array_equal(res[3].cpu().numpy(), o.dist)
+
+
+def _sampled(n, k):
+    """The rows that bound a small batch's queries: the row scan's sample (sample_row)."""
+    tiles = min((max(n // 512 * k, 128 * k) + 63) // 64, (n + 63) // 64, 4096)
+    step = (n << 32) // (64 * tiles)
+    i = np.arange(64 * tiles + 1, dtype=np.uint64)
+    a = (i * np.uint64(step)) >> np.uint64(32)
+    m = np.uint64(0xFFFFFFFF)
+    h = (i * np.uint64(2654435761)) & m
+    h = ((h ^ (h >> np.uint64(16))) * np.uint64(2654435761)) & m
+    return (a[:-1] + ((h[:-1] * (a[1:] - a[:-1])) >> np.uint64(32))).astype(np.int64)
+
+
+# Rows that the sample misses fill the buffers: the queries are passed over the
+# rows again, and once more by one workgroup each where the rows that come first
+# in every workgroup's run are farther than the others.
+@pytest.mark.parametrize("twice", [False, True])
+@pytest.mark.parametrize("n,nq,k", [(300_000, 20, 4), (263_007, 70, 10)])
+def test_overflowing_buffers(n, nq, k, twice):
+    import torch
+    import paper_2107_03368_amd as qd
+    rng = np.random.default_rng(890)
+    db = synth.gen_db(n, 890)
+    base = db[11].copy()
+    bits = np.flatnonzero(np.unpackbits(base.view(np.uint8), bitorder="little"))
+    far = np.zeros(n, bool)
+    far[_sampled(n, k)] = True
+
+    def near(rows, lost):  # copies of the base that lack `lost` or more of its bits
+        b = np.tile(np.unpackbits(base.view(np.uint8), bitorder="little"), (len(rows), 1))
+        for i in range(lost + 3):
+            b[np.arange(len(rows)), rng.choice(bits, len(rows)) if i >= lost else bits[i]] = 0
+        db[rows] = np.packbits(b, axis=1, bitorder="little").view(np.uint64)
+
+    if twice:
+        cus = torch.cuda.get_device_properties(0).multi_processor_count
+        units = (n + 63) // 64 * ((nq + 63) // 64)
+        start = np.array([units // cus * b + min(b, units % cus) for b in range(cus + 1)]) // ((nq + 63) // 64)
+        tile = np.arange(n) // 64
+        late = tile - start[np.searchsorted(start, tile, side="right") - 1] >= 8 // ((nq + 63) // 64)
+        near(np.flatnonzero(~far & late), 1)
+        near(np.flatnonzero(~far & ~late), 20)
+    else:
+        near(rng.choice(np.flatnonzero(~far), 20_000, replace=False), 2)
+    q = np.tile(base, (nq, 1))
+    q[:, 0] ^= np.arange(nq, dtype=np.uint64)
+    q[nq // 2] = synth.gen_queries(db[:100], 1, 891, 0.1, 0.3)[0][0]
+    dbt, qt = _t(db), _t(q)
+    res = qd.knn_bruteforce(dbt, qt, k)
+    ref = qd.knn_bruteforce(dbt, qt, k, query_tile=16)
+    assert all(torch.equal(a, b) for a, b in zip(res, ref))
+    some = np.array([0, 1, nq // 2, nq - 1])
+    o = oracle.knn_brute(db, q[some], k)
+    assert np.array_equal(res[0].cpu().numpy()[some].view(np.uint32), o.idx)
+    assert np.array_equal(res[3].cpu().numpy()[some], o.dist)
