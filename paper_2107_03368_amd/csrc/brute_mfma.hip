@@ -33,6 +33,10 @@ namespace {
 
 constexpr int kBlock = 256;
 constexpr uint32_t kCap = 8192;        // candidate slots per query
+// Queries of one pass over the rows, so that the workspace (up to 96 KB each)
+// stays below 1.6 GB: a pass of so many is bound by the matrix units, and the
+// rows are read again for the next ones at no cost that can be seen.
+constexpr uint32_t kMaxBatch = 16384;
 constexpr uint32_t kMaxGroups = 8192;  // sample minima per query
 
 // ---------------------------------------------------------------------------
@@ -624,9 +628,13 @@ bool mfma_eligible(uint64_t n, uint32_t nq, uint32_t k) {
     return nq >= 17 || nq * k >= 90;
 }
 
-MfmaLayout mfma_layout(uint64_t n, uint32_t nq, uint32_t k) {
+MfmaLayout mfma_layout(uint64_t n, uint32_t nq_all, uint32_t k) {
     MfmaLayout L;
     L.n = n;
+    // batches of one size, whole groups of queries
+    const uint32_t batches = (uint32_t)(((uint64_t)nq_all + kMaxBatch - 1) / kMaxBatch);
+    const uint32_t each = (uint32_t)(((uint64_t)nq_all + batches - 1) / batches);
+    const uint32_t nq = L.qb = batches == 1 ? nq_all : (each + kGroupQ - 1) / kGroupQ * kGroupQ;
     const uint64_t tiles = (n + kMidR - 1) / kMidR, n_qt = (nq + kMidQ - 1) / kMidQ;
     // The pass's first part ends where about 512 candidates per query are
     // expected from the sample's bounds (kCap = 8,192 slots), each next one
@@ -710,15 +718,24 @@ int mfma_run(const MfmaLayout &L, char *ws, const uint64_t *d_db, const uint64_t
 }
 
 // Matrix-core path for large batches; returns QD_ERR_UNSUPPORTED when the
-// shape is not worth it (the caller then uses the register-tiled scan).
+// shape is not worth it or its workspace cannot be had (the caller then uses the
+// row scan, which needs a few MB).
 int knn_bruteforce_mfma(const uint64_t *d_db, uint64_t n, const uint64_t *d_q, uint32_t nq, uint32_t k,
                         uint32_t *d_idx, int32_t *d_missed, int32_t *d_extra, float *d_dist, void *stream) {
     hipStream_t s = (hipStream_t)stream;
     if (!mfma_eligible(n, nq, k)) return QD_ERR_UNSUPPORTED;
     const MfmaLayout L = mfma_layout(n, nq, k);
     char *ws = nullptr;
-    QD_HIP_CHECK(hipMallocAsync((void **)&ws, L.bytes, s));
-    const int rc = mfma_run(L, ws, d_db, d_q, nq, nullptr, k, d_idx, d_missed, d_extra, d_dist, s);
+    if (hipMallocAsync((void **)&ws, L.bytes, s) != hipSuccess) {
+        (void)hipGetLastError();
+        return QD_ERR_UNSUPPORTED;
+    }
+    int rc = QD_OK;
+    for (uint64_t b = 0; b < nq && rc == QD_OK; b += L.qb) {
+        const uint64_t o = b * k;
+        rc = mfma_run(L, ws, d_db, d_q + b * QD_WORDS, (uint32_t)std::min<uint64_t>(L.qb, nq - b), nullptr, k, d_idx + o,
+                      d_missed + o, d_extra + o, d_dist + o, s);
+    }
     (void)hipFreeAsync(ws, s);
     return rc;
 }

@@ -56,7 +56,7 @@ __global__ void set_sizes_kernel(uint32_t *sizes, uint32_t n_qdesc, uint32_t nqo
     sizes[1] = nqo;
 }
 
-// Blocked order: the descriptors of batch i of qb each, sizes[2 + i].
+// The descriptors of batch i of qb each, sizes[2 + i].
 __global__ void batch_sizes_kernel(uint32_t *sizes, uint32_t n_batches, uint32_t qb) {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n_batches) return;
@@ -124,18 +124,19 @@ extern "C" int qd_plan_create(qd_tree_t t, const uint64_t *d_db, uint64_t n, con
     BruteLaunch BL;
     BlockedLayout KL;
     MfmaLayout ML;
-    uint32_t n_batches = 1;
     size_t ws_bytes;
     // sequential search: the large-batch matrix-core path when the largest
     // batch is big enough (query_tile 0), else the row scan with that tile
     // (0: chosen for the largest batch as qd_knn_bruteforce would)
-    const bool mfma = !t && query_tile == 0 && mfma_eligible(n, nqmax, k);
+    bool mfma = !t && query_tile == 0 && mfma_eligible(n, nqmax, k);
+    uint32_t qb = nqmax;  // descriptors per batch
     if (blocked) {
         KL = blocked_layout(t, nqmax, k, params && params->model);
-        n_batches = (uint32_t)((nqmax + KL.qb - 1) / KL.qb);
+        qb = KL.qb;
         ws_bytes = KL.bytes;
     } else if (mfma) {
         ML = mfma_layout(n, nqmax, k);
+        qb = ML.qb;
         ws_bytes = ML.bytes;
     } else if (t) {
         TL = tree_launch_shape(t, nqmax, k, order, params ? params->waves_per_cu : 0, params ? params->query_split : 0);
@@ -144,6 +145,7 @@ extern "C" int qd_plan_create(qd_tree_t t, const uint64_t *d_db, uint64_t n, con
         BL = brute_launch_shape(n, nqmax, k, query_tile, 0);
         ws_bytes = BL.part_bytes;
     }
+    const uint32_t n_batches = (uint32_t)(((uint64_t)nqmax + qb - 1) / qb);
     // one allocation: q | qoff | sizes | nn mi ex di | votes winner used | ws
     auto al = [](size_t b) { return (b + 255) / 256 * 256; };
     const size_t o_q = 0, o_off = o_q + al(max_qdesc * 512), o_sz = o_off + al(((size_t)max_qobj + 1) * 8);
@@ -151,8 +153,16 @@ extern "C" int qd_plan_create(qd_tree_t t, const uint64_t *d_db, uint64_t n, con
     const size_t o_mi = o_nn + al(m * 4), o_ex = o_mi + al(m * 4), o_di = o_ex + al(m * 4);
     const size_t o_vo = o_di + al(m * 4), o_wi = o_vo + al((size_t)max_qobj * n_obj * 4);
     const size_t o_us = o_wi + al((size_t)max_qobj * 4), o_ws = o_us + al((size_t)max_qobj * 4);
-    const size_t total = o_ws + al(ws_bytes);
-    if (hipMalloc((void **)&p->mem, total) != hipSuccess) {
+    size_t total = o_ws + al(ws_bytes);
+    hipError_t em = hipMalloc((void **)&p->mem, total);
+    if (em != hipSuccess && mfma) {  // the row scan's lists are a few MB
+        (void)hipGetLastError();
+        mfma = false;
+        BL = brute_launch_shape(n, nqmax, k, 0, 0);
+        total = o_ws + al(BL.part_bytes);
+        em = hipMalloc((void **)&p->mem, total);
+    }
+    if (em != hipSuccess) {
         plan_release(p);
         return fail(QD_ERR_OOM, "plan allocation of %zu bytes failed", total);
     }
@@ -176,19 +186,20 @@ extern "C" int qd_plan_create(qd_tree_t t, const uint64_t *d_db, uint64_t n, con
     int rc = QD_OK;
     hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
-        if (blocked) {
-            // batches of KL.qb descriptors, each with its size on the device
+        if (blocked || mfma) {
+            // batches of qb descriptors, each with its size on the device
             hipLaunchKernelGGL(batch_sizes_kernel, dim3((n_batches + 255) / 256), dim3(256), 0, cs, p->sizes,
-                               n_batches, KL.qb);
+                               n_batches, qb);
             for (uint32_t i = 0; i < n_batches && rc == QD_OK; i++) {
-                const uint64_t b0 = (uint64_t)i * KL.qb;
-                const uint32_t nqb = (uint32_t)std::min<uint64_t>(KL.qb, nqmax - b0);
+                const uint64_t b0 = (uint64_t)i * qb;
+                const uint32_t nqb = (uint32_t)std::min<uint64_t>(qb, nqmax - b0);
                 const uint64_t o = b0 * k;
-                rc = blocked_batch(t, KL, p->ws, p->q + b0 * QD_WORDS, nqb, p->sizes + 2 + i, k, params, p->nn + o,
-                                   p->mi + o, p->ex + o, p->di + o, nullptr, nullptr, /*graph=*/true, cs);
+                const uint64_t *qi = p->q + b0 * QD_WORDS;
+                rc = blocked ? blocked_batch(t, KL, p->ws, qi, nqb, p->sizes + 2 + i, k, params, p->nn + o, p->mi + o,
+                                             p->ex + o, p->di + o, nullptr, nullptr, /*graph=*/true, cs)
+                             : mfma_run(ML, p->ws, d_db, qi, nqb, p->sizes + 2 + i, k, p->nn + o, p->mi + o, p->ex + o,
+                                        p->di + o, cs);
             }
-        } else if (mfma) {
-            rc = mfma_run(ML, p->ws, d_db, p->q, nqmax, p->sizes, k, p->nn, p->mi, p->ex, p->di, cs);
         } else if (t)
             rc = tree_launch(t, TL, p->ws, p->q, nqmax, p->sizes, k, order, nullptr, 0, p->nn, p->mi, p->ex, p->di,
                              nullptr, nullptr, 0, cs);

@@ -74,6 +74,7 @@ int brute_launch(const BruteLaunch &L, u64 *part, const uint64_t *d_db, uint64_t
 // databases (mfma_eligible).
 struct MfmaLayout {
     uint64_t n = 0;
+    uint32_t qb = 0;  // queries per batch; the workspace serves one batch at a time
     uint64_t sample_tiles = 0, sample_step = 0;  // tiles of sampled rows; n / their rows in 32.32 fixed point
     std::vector<uint64_t> ends;                  // the row tile each part of the pass ends before
     size_t minima = 0, thr = 0, cnt = 0, cand = 0, again = 0, n_again = 0, bytes = 0;
@@ -81,7 +82,8 @@ struct MfmaLayout {
 // Whether a batch of nq queries over n rows takes the matrix cores.
 bool mfma_eligible(uint64_t n, uint32_t nq, uint32_t k);
 MfmaLayout mfma_layout(uint64_t n, uint32_t nq_max, uint32_t k);
-// nq_dev (nullable): the batch's size on the device (<= nq).  Never waits for the host.
+// One batch of nq <= L.qb queries; nq_dev (nullable): its size on the device
+// (<= nq).  Never waits for the host.
 int mfma_run(const MfmaLayout &L, char *ws, const uint64_t *d_db, const uint64_t *d_q, uint32_t nq,
              const uint32_t *nq_dev, uint32_t k, uint32_t *d_idx, int32_t *d_missed, int32_t *d_extra, float *d_dist,
              hipStream_t s);

@@ -1,0 +1,93 @@
+"""Sequential search of more queries than one matrix pass takes (16,384), its
+workspace, and the row scan in its place where the workspace cannot be had."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _t(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a).view(np.int64)).to("cuda:0")
+
+
+@pytest.mark.parametrize("n,nq,k", [(8_200, 16_385, 10), (9_000, 33_000, 4)])
+def test_several_batches(n, nq, k):
+    import torch
+    import paper_2107_03368_amd as qd
+    db = synth.gen_db(n, 900)
+    q, _ = synth.gen_queries(db, nq, 901, 0.1, 0.6)
+    dbt, qt = _t(db), _t(q)
+    res = qd.knn_bruteforce(dbt, qt, k)
+    ref = qd.knn_bruteforce(dbt, qt, k, query_tile=16)
+    assert all(torch.equal(a, b) for a, b in zip(res, ref))
+    some = np.array([0, 8_191, 8_192, 16_383, 16_384, nq - 1])
+    assert np.array_equal(res[0].cpu().numpy()[some].view(np.uint32), oracle.knn_brute(db, q[some], k).idx)
+
+
+def test_plan_over_several_batches():
+    import torch
+    import paper_2107_03368_amd as qd
+    n, n_obj, per, k, most = 8_192, 32, 700, 4, 25
+    db = synth.gen_db(n, 910)
+    q, _ = synth.gen_queries(db, most * per, 911, 0.1, 0.5)
+    dbt, qt = _t(db), _t(q)
+    obj = (torch.arange(n, device="cuda:0") * n_obj // n).to(torch.int16)
+    a, b = (qd.Plan(obj, n_obj, most * per, most, k, db=dbt, query_tile=t) for t in (0, 16))
+    for objects in (25, 1, 24, 23, 25):  # 17,500 descriptors: the second batch is full, empty, part full
+        off = torch.arange(objects + 1, dtype=torch.int64, device="cuda:0") * per
+        for x, y in zip(a.run(qt[:objects * per], off), b.run(qt[:objects * per], off)):
+            assert torch.equal(x, y)
+
+
+def test_plan_memory():
+    # 64 KB of candidate slots per descriptor of the whole plan: 3.9 GB
+    import torch
+    import paper_2107_03368_amd as qd
+    dbt = _t(synth.gen_db(10_000, 920))
+    obj = torch.zeros(10_000, dtype=torch.int16, device="cuda:0")
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    plan = qd.Plan(obj, 1, 60_000, 1, 10, db=dbt)
+    held = before - torch.cuda.mem_get_info()[0]
+    del plan
+    assert held < 1.5 * 2**30
+
+
+class _Location(ctypes.Structure):
+    _fields_ = [("type", ctypes.c_int), ("id", ctypes.c_int)]
+
+
+class _PoolProps(ctypes.Structure):
+    _fields_ = [("allocType", ctypes.c_int), ("handleTypes", ctypes.c_int), ("location", _Location),
+                ("security", ctypes.c_void_p), ("maxSize", ctypes.c_size_t), ("reserved", ctypes.c_ubyte * 56)]
+
+
+def test_row_scan_without_a_workspace():
+    # the stream-ordered allocator draws on a pool of 64 MB; the pass asks for more
+    import torch
+    import paper_2107_03368_amd as qd
+    db = synth.gen_db(70_000, 930)
+    q, _ = synth.gen_queries(db, 5_000, 931, 0.1, 0.6)
+    dbt, qt = _t(db), _t(q)
+    ref = qd.knn_bruteforce(dbt, qt, 10)
+    torch.cuda.synchronize()
+    lib = next(l.split()[-1] for l in open("/proc/self/maps") if "libamdhip64" in l)
+    hip = ctypes.CDLL(lib)
+    pool, old = ctypes.c_void_p(), ctypes.c_void_p()
+    props = _PoolProps(allocType=1, location=_Location(1, 0), maxSize=64 << 20)
+    assert hip.hipDeviceGetMemPool(ctypes.byref(old), 0) == 0
+    assert hip.hipMemPoolCreate(ctypes.byref(pool), ctypes.byref(props)) == 0
+    assert hip.hipDeviceSetMemPool(0, pool) == 0
+    try:
+        res = qd.knn_bruteforce(dbt, qt, 10)
+        torch.cuda.synchronize()
+    finally:
+        assert hip.hipDeviceSetMemPool(0, old) == 0
+        assert hip.hipMemPoolDestroy(pool) == 0
+    assert all(torch.equal(a, b) for a, b in zip(res, ref))
