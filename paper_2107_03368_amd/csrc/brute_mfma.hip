@@ -19,6 +19,8 @@
 // the candidates it holds (rows all the same) and passed over the rows once
 // more, with the others like it only; should it overflow again, one workgroup
 // reads all rows for it, so the result is exact in every case.
+#include <math.h>
+
 #include <algorithm>
 #include <vector>
 
@@ -32,7 +34,7 @@ namespace qd {
 namespace {
 
 constexpr int kBlock = 256;
-constexpr uint32_t kCap = 8192;        // candidate slots per query
+constexpr uint32_t kCap = 8192;        // candidate slots per query at most
 // Queries of one pass over the rows, so that the workspace (up to 96 KB each)
 // stays below 1.6 GB: a pass of so many is bound by the matrix units, and the
 // rows are read again for the next ones at no cost that can be seen.
@@ -108,7 +110,8 @@ __global__ __launch_bounds__(kMidBlock, 2) void scan_mfma_kernel(const uint4 *__
                                                                  uint64_t tiles, uint64_t sample_step,
                                                                  const uint4 *__restrict__ q, uint32_t nq,
                                                                  const u64 *__restrict__ thr, uint32_t *__restrict__ cnt,
-                                                                 u64 *__restrict__ cand, uint32_t *__restrict__ minima,
+                                                                 u64 *__restrict__ cand, uint32_t cap,
+                                                                 uint32_t *__restrict__ minima,
                                                                  const uint32_t *__restrict__ list,
                                                                  const uint32_t *__restrict__ nq_dev) {
     extern __shared__ __align__(16) uint8_t s_raw[];
@@ -134,8 +137,8 @@ __global__ __launch_bounds__(kMidBlock, 2) void scan_mfma_kernel(const uint4 *__
         for (uint32_t e = lane; e < nqe; e += 64) {
             const uint32_t qs = cq[e][0], qk = kPass == kAgain ? sm.id[qs] : q0 + qs;
             const uint32_t pos = atomicAdd(&cnt[qk], 1u);
-            if (pos < kCap)
-                cand[(uint64_t)qk * kCap + pos] = ((u64)cq[e][1] << 32) | cq[e][2];
+            if (pos < cap)
+                cand[(uint64_t)qk * cap + pos] = ((u64)cq[e][1] << 32) | cq[e][2];
             else  // the query is searched again: no more of its rows here
                 sm.bound[qs] = mt::kNoBound;
         }
@@ -330,7 +333,7 @@ __global__ __launch_bounds__(kMidBlock, 2) void scan_mfma_kernel(const uint4 *__
     }
 }
 
-// Selection among a query's m <= kCap candidates by the whole block: thread t
+// Selection among a query's m <= cap candidates by the whole block: thread t
 // holds the K of candidates t, t + 256, ... (R of them; no candidate: all
 // ones), and the k-th smallest K is found by bisection, counting by ballots.
 template <int R>
@@ -414,15 +417,15 @@ struct Pick {
 // After a part of a pass: the k-th smallest key found so far bounds the rest
 // (those k rows are real).  One block per query.
 __global__ __launch_bounds__(kBlock) void tighten_kernel(const uint32_t *__restrict__ cnt,
-                                                         const u64 *__restrict__ cand, uint32_t k,
+                                                         const u64 *__restrict__ cand, uint32_t cap, uint32_t k,
                                                          u64 *__restrict__ thr, const uint32_t *__restrict__ nq_dev) {
     __shared__ uint32_t s_part[2][4];
     const uint32_t qi = blockIdx.x;
     if (nq_dev && qi >= *nq_dev) return;  // whole block
     const uint32_t m = cnt[qi];
-    if (m > kCap && threadIdx.x == 0) thr[qi] = 0;  // searched again: nothing more is listed now
-    if (m < k || m > kCap) return;
-    const u64 *c = cand + (uint64_t)qi * kCap;
+    if (m > cap && threadIdx.x == 0) thr[qi] = 0;  // searched again: nothing more is listed now
+    if (m < k || m > cap) return;
+    const u64 *c = cand + (uint64_t)qi * cap;
     auto key = [&](uint32_t i) { return (uint32_t)(c[i] >> 32); };
     auto row = [&](uint32_t i) { return (uint32_t)c[i]; };
     const u64 t = m <= 4 * kBlock ? Pick<4>(key, m, s_part).kth_key(k, row)
@@ -453,7 +456,7 @@ __device__ __forceinline__ void pick_keys(const u64 *cand, uint32_t m, uint32_t 
     }
 }
 
-// The k best of a query's m <= kCap candidates into keys[0 .. result), in
+// The k best of a query's m <= cap candidates into keys[0 .. result), in
 // order, by the whole block (up to kBlock of them, at least k if m is).
 // Selecting before sorting leaves a few keys to order: 0.08 ms for
 // 4,096 queries with 1,000 candidates each, where sorting them all took 0.32.
@@ -527,10 +530,10 @@ __device__ __forceinline__ void best_of_all(const uint4 *db, uint64_t n, const u
 }
 
 // One block per query: the k best of its candidates and their results.  An
-// overflowed query (its candidates held are any kCap of the rows that passed)
+// overflowed query (its candidates held are any cap of the rows that passed)
 // is listed in `list` for another pass, bounded by the k-th smallest of them.
 __global__ __launch_bounds__(kBlock) void select_emit_kernel(uint32_t *__restrict__ cnt, const u64 *__restrict__ cand,
-                                                             uint32_t k, const uint4 *__restrict__ q,
+                                                             uint32_t cap, uint32_t k, const uint4 *__restrict__ q,
                                                              const uint4 *__restrict__ db, uint32_t *idx,
                                                              int32_t *missed, int32_t *extra, float *dist,
                                                              u64 *__restrict__ thr, uint32_t *__restrict__ list,
@@ -541,9 +544,9 @@ __global__ __launch_bounds__(kBlock) void select_emit_kernel(uint32_t *__restric
     const uint32_t qi = blockIdx.x;
     if (nq_dev && qi >= *nq_dev) return;  // whole block
     const uint32_t m = cnt[qi];
-    const u64 *c = cand + (uint64_t)qi * kCap;
-    if (m > kCap) {
-        const u64 t = Pick<kCap / kBlock>([&](uint32_t i) { return (uint32_t)(c[i] >> 32); }, kCap, s_part)
+    const u64 *c = cand + (uint64_t)qi * cap;
+    if (m > cap) {
+        const u64 t = Pick<kCap / kBlock>([&](uint32_t i) { return (uint32_t)(c[i] >> 32); }, cap, s_part)
                           .kth_key(k, [&](uint32_t i) { return (uint32_t)c[i]; });
         if (threadIdx.x == 0) {
             list[atomicAdd(n_list, 1u)] = qi;
@@ -558,7 +561,7 @@ __global__ __launch_bounds__(kBlock) void select_emit_kernel(uint32_t *__restric
 
 // The results of the queries that were passed over the rows again.
 __global__ __launch_bounds__(kBlock) void select_again_kernel(const uint32_t *__restrict__ cnt,
-                                                              const u64 *__restrict__ cand, uint32_t k,
+                                                              const u64 *__restrict__ cand, uint32_t cap, uint32_t k,
                                                               const uint4 *__restrict__ q,
                                                               const uint4 *__restrict__ db, uint64_t n, uint32_t *idx,
                                                               int32_t *missed, int32_t *extra, float *dist,
@@ -571,8 +574,8 @@ __global__ __launch_bounds__(kBlock) void select_again_kernel(const uint32_t *__
     for (uint32_t i = blockIdx.x; i < n_again; i += gridDim.x) {
         const uint32_t qi = list[i], m = cnt[qi];
         uint32_t nk = k;
-        if (m <= kCap)
-            nk = best_candidates(cand + (uint64_t)qi * kCap, m, k, s_part, keys, &s_n);
+        if (m <= cap)
+            nk = best_candidates(cand + (uint64_t)qi * cap, m, k, s_part, keys, &s_n);
         else
             best_of_all(db, n, q + (uint64_t)qi * 32, k, thr[qi], keys, &s_n);
         emit_rows(keys, nk < k ? nk : k, k, q + (uint64_t)qi * 32, db, (uint64_t)qi * k, idx, missed, extra, dist);
@@ -614,18 +617,26 @@ inline size_t al256(size_t b) { return (b + 255) / 256 * 256; }
 // matrix tiles; vector tiles for 1 and 2 queries).  The row scan needs two
 // launches and no bounds, but expands every row once per 16 queries and keeps
 // k-lists per wave, whose insertions grow with k; the matrix pass has six
-// launches (about 30 us).  Measured, matrix pass / row scan, us per call:
-//   k = 10, 9 queries: 20,000 rows 60 / 66, 300,000 92 / 120, 3M 327 / 342
-//   k = 10, 6 queries: 66,000 rows 68 / 63, 1M 165 / 149 (60 = nq k stays out)
-//   k = 4, 17 queries: 20,000 rows 59 / 75, 1M 169 / 208
-//   k = 1, 64 queries: 300,000 rows 145 / 122, 1M 219 / 277
-//   k = 1, 128 queries: 150,000 rows 129 / 122, 300,000 170 / 186
-// So: for k < 4 from 2^25 pairs up; else from 17 queries, or from nq k = 90.
-// Below 8,192 rows (or 256 k) the sample would be most of the rows.
+// launches (about 30 us).  Measured, matrix pass / row scan, us per call among
+// others:
+//   k = 1, 17 queries: 30,000 rows 59 / 54, 66,000 59 / 62, 300,000 63 / 84;
+//     33: 30,000 57 / 61, 66,000 58 / 70; 44: 16,800 61 / 56
+//   k = 2, 17 queries: 8,192 rows 49 / 57, 66,000 60 / 74, 1M 139 / 182;
+//     12: 30,000 1.17 times the row scan, 66,000 1.03, 1M 1.07
+//   k = 10, 8 queries: 8,192 to 66,000 rows 0.8 to 1.0 times, 3M 0.97
+//   few queries: 6 with k = 16 8,192 and 30,000 rows 1.17 and 1.11 times, 66,000
+//     0.88, 1M 0.84, 3M 0.98, 10M 1.04; 4 with k = 24 66,000 0.99, 300,000 0.70,
+//     10M 1.05; 3 with k = 48 66,000 1.05, 300,000 0.62, 10M 1.04
+// So: from 17 queries up (k = 1: 33 and 2^20 pairs), and fewer where nq k is 90, which small
+// databases need 8 queries for and large ones, whose scan is one read of the
+// rows either way, 144.  Below 8,192 rows (or 256 k) the sample would be most of
+// the rows.
 bool mfma_eligible(uint64_t n, uint32_t nq, uint32_t k) {
-    if (n < 8192 || n < (uint64_t)k * 256 || nq < 3) return false;
-    if (k < 4) return nq >= 17 && n * nq >= (1ull << 25);
-    return nq >= 17 || nq * k >= 90;
+    if (n < 8192 || n < (uint64_t)k * 256) return false;
+    if (k == 1) return nq >= 33 && n * nq >= (1u << 20);
+    if (nq >= 17) return true;
+    if (nq >= 8) return nq * k >= 90;
+    return nq >= 3 && n >= (1u << 16) && nq * k >= (n < (1u << 21) ? 90u : 144u);
 }
 
 MfmaLayout mfma_layout(uint64_t n, uint32_t nq_all, uint32_t k) {
@@ -637,7 +648,7 @@ MfmaLayout mfma_layout(uint64_t n, uint32_t nq_all, uint32_t k) {
     const uint32_t nq = L.qb = batches == 1 ? nq_all : (each + kGroupQ - 1) / kGroupQ * kGroupQ;
     const uint64_t tiles = (n + kMidR - 1) / kMidR, n_qt = (nq + kMidQ - 1) / kMidQ;
     // The pass's first part ends where about 512 candidates per query are
-    // expected from the sample's bounds (kCap = 8,192 slots), each next one
+    // expected from the sample's bounds (of up to kCap = 8,192 slots), each next one
     // eight times further (about 7 k more).  Sampling k n / r rows puts the
     // first end at 512 n / r: r = 4,096, an eighth of the rows, where that
     // eighth fills the chip several times over and there are candidates enough
@@ -647,13 +658,30 @@ MfmaLayout mfma_layout(uint64_t n, uint32_t nq_all, uint32_t k) {
     // Where all near rows lie in the first part, it lists r of them on average;
     // for small k the sample's bound varies (k = 1: an exponential distribution,
     // 13% of the queries past 8,192), so a split pass samples as for k = 4.
+    // A pass in one part samples as for k = 16 at least, up to 32,768 rows: that
+    // many cost 10 us at most, and fewer candidates save more (64 queries, k = 4,
+    // as for k / as for 16: 66,000 rows 118 / 67 us, 1M 189 / 149).
     const bool split = nq >= 512 && tiles / 8 * n_qt >= 8ull * kMidWaves * device_cus();
     const uint32_t ks = split ? std::max(k, 4u) : k;
-    const uint64_t rows = std::max<uint64_t>(n / (split ? 4096 : 512) * ks, (uint64_t)k * 128);
+    const uint64_t rows = std::max<uint64_t>({n / (split ? 4096 : 512) * ks, (uint64_t)k * 128,
+                                              split ? 0 : std::min<uint64_t>(n / 512 * 16, 32768)});
     L.sample_tiles = std::min<uint64_t>({(rows + kMidR - 1) / kMidR, tiles, kMaxGroups / 2});
     L.sample_step = (n << 32) / (L.sample_tiles * kMidR);
     for (uint64_t end = L.sample_tiles * 512 / ks; 2 * end <= tiles; end *= 8) L.ends.push_back(end);
     L.ends.push_back(tiles);
+    // Slots: of a pass in one part, as many as a query overflows once in some ten
+    // million times.  Its candidates are those before its k-th sampled row; k n /
+    // sample of them are expected (a quarter more, as some sampled rows share a
+    // group), and the number's spread falls with k.  8,192 slots for every batch
+    // made a workspace whose allocation alone took up to 0.2 ms (1,000 queries x
+    // 8,192 rows, k = 4: 0.39 ms a call, 0.16 with the row scan); from 2 MB on an
+    // allocation after a wait takes 0.1 ms.
+    L.cap = kCap;
+    if (L.ends.size() == 1) {
+        const double many = 1.25 * (double)k * (double)n / (double)(L.sample_tiles * kMidR);
+        const double most = many * (1 + 5.2 / sqrt((double)k) + 9.0 / k);
+        L.cap = std::min<uint32_t>(kCap, ((uint32_t)most / kBlock + 1) * kBlock);
+    }
     size_t o = 0;
     auto take = [&](size_t b) {
         const size_t at = o;
@@ -663,7 +691,7 @@ MfmaLayout mfma_layout(uint64_t n, uint32_t nq_all, uint32_t k) {
     L.minima = take((size_t)L.sample_tiles * 2 * nq * 4);
     L.thr = take((size_t)nq * 8);
     L.cnt = take((size_t)nq * 4);
-    L.cand = take((size_t)nq * kCap * 8);
+    L.cand = take((size_t)nq * L.cap * 8);
     L.again = take((size_t)nq * 4);
     L.n_again = take(4);
     L.bytes = o;
@@ -688,7 +716,7 @@ int mfma_run(const MfmaLayout &L, char *ws, const uint64_t *d_db, const uint64_t
         // (a small sample one unit per workgroup: its scattered rows are a chain of misses)
         const dim3 g((uint32_t)std::min<uint64_t>(L.sample_tiles * n_qt, device_cus()));
         hipLaunchKernelGGL(scan_mfma_kernel<kSample>, g, dim3(kMidBlock), lds, s, db4, n, 0ull, L.sample_tiles,
-                           L.sample_step, q4, nq, nullptr, nullptr, nullptr, minima, nullptr, nq_dev);
+                           L.sample_step, q4, nq, nullptr, nullptr, nullptr, L.cap, minima, nullptr, nq_dev);
         hipLaunchKernelGGL(sample_threshold_kernel, dim3(nq), dim3(kBlock), 0, s, minima,
                            (uint32_t)(2 * L.sample_tiles), L.sample_step, nq, k, thr, cnt, n_again, nq_dev);
     }
@@ -697,22 +725,23 @@ int mfma_run(const MfmaLayout &L, char *ws, const uint64_t *d_db, const uint64_t
         for (size_t i = 0; i < L.ends.size(); i++) {
             const uint64_t t0 = i ? L.ends[i - 1] : 0, nt = L.ends[i] - t0;
             if (i)
-                hipLaunchKernelGGL(tighten_kernel, dim3(nq), dim3(kBlock), 0, s, cnt, cand, k, thr, nq_dev);
+                hipLaunchKernelGGL(tighten_kernel, dim3(nq), dim3(kBlock), 0, s, cnt, cand, L.cap, k, thr,
+                                   nq_dev);
             hipLaunchKernelGGL(scan_mfma_kernel<kFirst>, grid(nt), dim3(kMidBlock), lds, s, db4, n, t0, nt, 0ull, q4,
-                               nq, thr, cnt, cand, nullptr, nullptr, nq_dev);
+                               nq, thr, cnt, cand, L.cap, nullptr, nullptr, nq_dev);
         }
     }
     {
         KernelTimer timer("topk_select", s);
-        hipLaunchKernelGGL(select_emit_kernel, dim3(nq), dim3(kBlock), 0, s, cnt, cand, k, q4, db4, d_idx, d_missed,
-                           d_extra, d_dist, thr, again, n_again, nq_dev);
+        hipLaunchKernelGGL(select_emit_kernel, dim3(nq), dim3(kBlock), 0, s, cnt, cand, L.cap, k, q4, db4, d_idx,
+                           d_missed, d_extra, d_dist, thr, again, n_again, nq_dev);
     }
     // the overflowed queries, whose list and count stay on the device: without
     // any these launches find no work
     hipLaunchKernelGGL(scan_mfma_kernel<kAgain>, grid(L.ends.back()), dim3(kMidBlock), lds, s, db4, n, 0ull,
-                       L.ends.back(), 0ull, q4, nq, thr, cnt, cand, nullptr, again, n_again);
+                       L.ends.back(), 0ull, q4, nq, thr, cnt, cand, L.cap, nullptr, again, n_again);
     hipLaunchKernelGGL(select_again_kernel, dim3(std::min<uint32_t>(nq, device_cus())), dim3(kBlock), 0, s, cnt, cand,
-                       k, q4, db4, n, d_idx, d_missed, d_extra, d_dist, thr, again, n_again);
+                       L.cap, k, q4, db4, n, d_idx, d_missed, d_extra, d_dist, thr, again, n_again);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? QD_OK : fail(QD_ERR_DEVICE, "matrix-core scan: %s", hipGetErrorString(e));
 }

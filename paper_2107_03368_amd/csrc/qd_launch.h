@@ -77,6 +77,7 @@ struct MfmaLayout {
     uint32_t qb = 0;  // queries per batch; the workspace serves one batch at a time
     uint64_t sample_tiles = 0, sample_step = 0;  // tiles of sampled rows; n / their rows in 32.32 fixed point
     std::vector<uint64_t> ends;                  // the row tile each part of the pass ends before
+    uint32_t cap = 0;                            // candidate slots per query
     size_t minima = 0, thr = 0, cnt = 0, cand = 0, again = 0, n_again = 0, bytes = 0;
 };
 // Whether a batch of nq queries over n rows takes the matrix cores.
