@@ -29,6 +29,7 @@
 #include <memory>
 #include <vector>
 
+#include "band_weight.h"
 #include "qd_device.h"
 #include "qd_internal.h"
 #include "qd_tree.h"
@@ -648,11 +649,11 @@ __global__ __launch_bounds__(1024) void big_band_kernel(const CountSource *__res
     if (t < kBins) bins[t] = 0;
     const uint32_t cmax = lambda ? count_threshold<16, false>(cnt, m, (u64)m * lambda, sums) : m;
     __syncthreads();
-    // counts in 256 bins of equal width; weights in 1/256 so that all fit 32 bits
-    const uint32_t shift = max(0, 24 - __builtin_clz(cmax));
+    // counts in 256 bins of equal width; weights so that all together fit 32 bits
+    const uint32_t wshift = band_weight_shift(m), shift = max(0, 24 - __builtin_clz(cmax));
 #pragma unroll
     for (int i = 0; i < 4; i++)
-        if (cnt[i] && cnt[i] <= cmax) atomicAdd(&bins[cnt[i] >> shift], (cnt[i] >> 8) + 1);
+        if (cnt[i] && cnt[i] <= cmax) atomicAdd(&bins[cnt[i] >> shift], (cnt[i] >> wshift) + 1);
     __syncthreads();
     if (t < 64) {  // a bin's band: half the bands for the first quarter of the weight
         uint32_t x[4], s = 0;
