@@ -1,12 +1,11 @@
 """Sequential search of more queries than one matrix pass takes (16,384), its
 workspace, and the row scan in its place where the workspace cannot be had."""
-import ctypes
-
 import numpy as np
 import pytest
 
 import oracle
 import synth
+from small_pool import small_pool
 
 pytestmark = pytest.mark.gpu
 
@@ -59,15 +58,6 @@ def test_plan_memory():
     assert held < 1.5 * 2**30
 
 
-class _Location(ctypes.Structure):
-    _fields_ = [("type", ctypes.c_int), ("id", ctypes.c_int)]
-
-
-class _PoolProps(ctypes.Structure):
-    _fields_ = [("allocType", ctypes.c_int), ("handleTypes", ctypes.c_int), ("location", _Location),
-                ("security", ctypes.c_void_p), ("maxSize", ctypes.c_size_t), ("reserved", ctypes.c_ubyte * 56)]
-
-
 def test_row_scan_without_a_workspace():
     # the stream-ordered allocator draws on a pool of 32 MB; the pass asks for twice that
     import torch
@@ -76,20 +66,8 @@ def test_row_scan_without_a_workspace():
     q, _ = synth.gen_queries(db, 5_000, 931, 0.1, 0.6)
     dbt, qt = _t(db), _t(q)
     ref = qd.knn_bruteforce(dbt, qt, 10)
-    torch.cuda.synchronize()
-    lib = next(l.split()[-1] for l in open("/proc/self/maps") if "libamdhip64" in l)
-    hip = ctypes.CDLL(lib)
-    pool, old = ctypes.c_void_p(), ctypes.c_void_p()
-    props = _PoolProps(allocType=1, location=_Location(1, 0), maxSize=32 << 20)
-    assert hip.hipDeviceGetMemPool(ctypes.byref(old), 0) == 0
-    assert hip.hipMemPoolCreate(ctypes.byref(pool), ctypes.byref(props)) == 0
-    assert hip.hipDeviceSetMemPool(0, pool) == 0
-    try:
+    with small_pool(32):
         res = qd.knn_bruteforce(dbt, qt, 10)
-        torch.cuda.synchronize()
-    finally:
-        assert hip.hipDeviceSetMemPool(0, old) == 0
-        assert hip.hipMemPoolDestroy(pool) == 0
     assert all(torch.equal(a, b) for a, b in zip(res, ref))
 
 
