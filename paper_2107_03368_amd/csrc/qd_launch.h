@@ -30,10 +30,11 @@ int knn_tree_impl(qd_tree_t t, const uint64_t *d_q, uint32_t nq, uint32_t k, int
                   uint32_t n_traced, uint32_t split = 0);
 // The depth-first order's LDS stack holds the tree's depth.
 bool depth_first_fits(qd_tree_t t);
+// want_totals: the queries' statistics are summed in 4 u64 at ws + 64.
 int tree_launch(qd_tree_t t, const TreeLaunch &L, char *ws, const uint64_t *d_q, uint32_t nq,
                 const uint32_t *nq_dev, uint32_t k, int order, const float *d_scores, uint32_t n_scored,
                 uint32_t *d_idx, int32_t *d_missed, int32_t *d_extra, float *d_dist, uint32_t *d_qstats,
-                uint32_t *d_trace, uint32_t n_traced, hipStream_t s);
+                uint32_t *d_trace, uint32_t n_traced, hipStream_t s, bool want_totals = false);
 
 // The blocked tree search (QD_ORDER_BLOCKED) on a workspace the caller
 // owns: batches of up to qb queries, byte offsets of every buffer in it.

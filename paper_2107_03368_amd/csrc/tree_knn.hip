@@ -85,12 +85,13 @@ struct Scores {
 
 // Smaller trees, and batches of fewer than two tasks per wave, deal their tasks
 // query by query from one counter: there is little to reuse, and a query's
-// searches that run together share its k-th key early.  Dealt by subtree on each XCD instead, depth-first,
-// k = 10: 10k rows 509 queries 0.62 -> 0.77 ms, 2,048 1.86 -> 1.99; 30k rows
-// 0.88 -> 0.86 and 2.81 -> 2.15; 60k rows 1.53 -> 1.19 and 5.17 -> 3.17.
-// At k = 1 a close neighbour ends most searches, so sharing the key early counts
-// more: 60k rows, 1,200 queries 1.4 ms either way, 223k rows 2.9 -> 2.5.
-constexpr uint64_t kByQueryRows = 20000, kByQueryRows1 = 100000;
+// searches that run together share its k-th key early.  By query / by subtree on
+// each XCD, depth-first, ms: 5,000 rows k = 10, 509 queries 0.31 / 0.33, 2,048
+// 0.75 / 0.60; 10,000 rows 0.46 / 0.41 and 1.19 / 0.90; 30,000 rows k = 1 0.38 /
+// 0.37 and 0.94 / 0.72, k = 3 0.72 / 0.59 and 2.25 / 1.47; 60,000 rows k = 10
+// 0.92 / 0.80 (300 queries) and 5.1 / 2.9; 1M rows, each 100 times, 2,048 queries
+// 1.5 / 1.0; 128 queries are 10% slower by subtree in any tree.
+constexpr uint64_t kByQueryRows = 10000;
 // Words between the XCDs' counters: a cache line each, because thousands of
 // waves add to all of them when the tasks have run out.
 constexpr uint32_t kCounterStride = 32;
@@ -488,14 +489,6 @@ __global__ __launch_bounds__(kBlock, kBest && kGroups == 4 ? 3 : 4) void tree_kn
         }
 
         put(list, payload, visited, leaves, bounds, dists, pq);
-        if (lane == 0) {
-            // totals: after the task counter in the workspace head
-            unsigned long long *gstats = reinterpret_cast<unsigned long long *>(next_task + 16);
-            atomicAdd(&gstats[0], (unsigned long long)visited);
-            atomicAdd(&gstats[1], (unsigned long long)leaves);
-            atomicAdd(&gstats[2], (unsigned long long)bounds);
-            atomicAdd(&gstats[3], (unsigned long long)dists);
-        }
     }
 }
 
@@ -591,14 +584,17 @@ __device__ __forceinline__ u64 shfl_xor64(u64 v, int m) {
 }
 
 // A query's n task lists -> its k nearest, and its statistics summed over
-// the tasks (n = 1: a copy).  One wave per query: the lists go to LDS, then
-// k steps each take the least head among the lists (the keys are distinct:
-// the subtrees partition the rows).
+// the tasks (n = 1: a copy); totals (nullable): the queries' statistics are added
+// there.  (Added by every task instead, they were four updates of one line of
+// memory, 49 ns per task over the whole chip: the 131,072 short searches of 2,048
+// queries in a tree of repeated rows took 6.4 ms, 0.8 without.)  One wave per
+// query: the lists go to LDS, then k steps each take the least head among the
+// lists (the keys are distinct: the subtrees partition the rows).
 template <int kMergeWaves, int kLists>  // waves per block, lists per query at most
 __global__ __launch_bounds__(64 * kMergeWaves) void merge_kernel(uint32_t nq, const uint32_t *__restrict__ nq_dev,
                                                                  uint32_t k, uint32_t n, const char *__restrict__ sw,
                                                                  uint32_t *idx, int32_t *missed, int32_t *extra,
-                                                                 float *dist, uint32_t *qstats) {
+                                                                 float *dist, uint32_t *qstats, u64 *totals) {
     __shared__ u64 s_key[kMergeWaves][kLists * QD_MAX_K];
     __shared__ uint32_t s_pay[kMergeWaves][kLists * QD_MAX_K];
     const int lane = lane_id(), w = (int)(threadIdx.x >> 6);
@@ -684,6 +680,12 @@ __global__ __launch_bounds__(64 * kMergeWaves) void merge_kernel(uint32_t nq, co
         qstats[(uint64_t)qi * 4 + 2] = v2;
         qstats[(uint64_t)qi * 4 + 3] = v3;
     }
+    if (totals && lane == 0) {
+        atomicAdd(&totals[0], (u64)v0);
+        atomicAdd(&totals[1], (u64)v1);
+        atomicAdd(&totals[2], (u64)v2);
+        atomicAdd(&totals[3], (u64)v3);
+    }
 }
 
 }  // namespace
@@ -747,10 +749,11 @@ bool split_ok(uint32_t split) { return split == 0 || (split <= kMaxSplit && (spl
 int tree_launch(qd_tree_t t, const TreeLaunch &L, char *ws, const uint64_t *d_q, uint32_t nq,
                 const uint32_t *nq_dev, uint32_t k, int order, const float *d_scores, uint32_t n_scored,
                 uint32_t *d_idx, int32_t *d_missed, int32_t *d_extra, float *d_dist, uint32_t *d_qstats,
-                uint32_t *d_trace, uint32_t n_traced, hipStream_t s) {
+                uint32_t *d_trace, uint32_t n_traced, hipStream_t s, bool want_totals) {
     hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(64), 0, s, reinterpret_cast<uint32_t *>(ws),
                        (uint32_t)(L.head / 4));
-    uint32_t *counter = reinterpret_cast<uint32_t *>(ws);  // the kernel adds its totals at ws + 64
+    uint32_t *counter = reinterpret_cast<uint32_t *>(ws);
+    u64 *totals = want_totals ? reinterpret_cast<u64 *>(ws + 64) : nullptr;
     uint32_t *chunk_prev = reinterpret_cast<uint32_t *>(ws + L.head);
     u64 *pool = reinterpret_cast<u64 *>(ws + L.head + L.prev_bytes);
     TreeView T{reinterpret_cast<const uint4 *>(t->d_sorted), t->d_perm, reinterpret_cast<const uint4 *>(t->d_or),
@@ -760,8 +763,7 @@ int tree_launch(qd_tree_t t, const TreeLaunch &L, char *ws, const uint64_t *d_q,
     if (L.split > 1 && d_trace) return fail(QD_ERR_INVALID, "a traced search runs unsplit");
     char *sw = ws + L.head + L.prev_bytes + L.pool_bytes;  // the tasks' area
     // by subtree only where a wave takes several searches; unsplit, there is one subtree
-    const uint32_t n_homes =
-        L.split == 1 || t->n < (k == 1 ? kByQueryRows1 : kByQueryRows) || (uint64_t)nq * L.split < 2 * L.slots ? 1 : 8;
+    const uint32_t n_homes = L.split == 1 || t->n < kByQueryRows || (uint64_t)nq * L.split < 2 * L.slots ? 1 : 8;
     if (L.split > 1) {
         hipLaunchKernelGGL(roots_kernel, dim3(1), dim3(64), 0, s, t->d_split_roots, L.split,
                            reinterpret_cast<int32_t *>(sw));
@@ -795,10 +797,10 @@ int tree_launch(qd_tree_t t, const TreeLaunch &L, char *ws, const uint64_t *d_q,
         KernelTimer timer("tree_merge", s);
         if (L.split <= kMaxSplit)
             hipLaunchKernelGGL((merge_kernel<4, kMaxSplit>), dim3((nq + 3) / 4), dim3(256), 0, s, nq, nq_dev, k,
-                               L.split, sw, d_idx, d_missed, d_extra, d_dist, d_qstats);
+                               L.split, sw, d_idx, d_missed, d_extra, d_dist, d_qstats, totals);
         else
             hipLaunchKernelGGL((merge_kernel<1, kFineSplit>), dim3(nq), dim3(64), 0, s, nq, nq_dev, k, L.split, sw,
-                               d_idx, d_missed, d_extra, d_dist, d_qstats);
+                               d_idx, d_missed, d_extra, d_dist, d_qstats, totals);
     }
     QD_HIP_CHECK(hipGetLastError());
     return QD_OK;
@@ -836,7 +838,7 @@ int knn_tree_impl(qd_tree_t t, const uint64_t *d_q, uint32_t nq, uint32_t k, int
     if (d_trace && n_traced)
         QD_HIP_CHECK(hipMemsetAsync(d_trace, 0, (size_t)nq * ((n_traced + 31) / 32) * 4, s));
     int rc = tree_launch(t, L, ws, d_q, nq, nullptr, k, order, d_scores, n_scored, d_idx, d_missed, d_extra, d_dist,
-                         d_qstats, d_trace, n_traced, s);
+                         d_qstats, d_trace, n_traced, s, h_stats != nullptr);
     hipError_t e = hipSuccess;
     if (rc == QD_OK && h_stats) {
         unsigned long long hs[4];
