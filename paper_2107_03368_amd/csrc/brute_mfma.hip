@@ -35,10 +35,11 @@ namespace {
 
 constexpr int kBlock = 256;
 constexpr uint32_t kCap = 8192;        // candidate slots per query at most
-// Queries of one pass over the rows, so that the workspace (up to 96 KB each)
-// stays below 1.6 GB: a pass of so many is bound by the matrix units, and the
-// rows are read again for the next ones at no cost that can be seen.
-constexpr uint32_t kMaxBatch = 16384;
+// A pass takes as many queries as a workspace of 1 GB serves, at least 16,384 (up
+// to 96 KB each): so many are bound by the matrix units, and the rows are read
+// again for the next ones at no cost that can be seen.
+constexpr uint32_t kMinBatch = 16384;
+constexpr uint64_t kBatchBytes = 1ull << 30;
 constexpr uint32_t kMaxGroups = 8192;  // sample minima per query
 
 // ---------------------------------------------------------------------------
@@ -627,25 +628,25 @@ inline size_t al256(size_t b) { return (b + 255) / 256 * 256; }
 //   few queries: 6 with k = 16 8,192 and 30,000 rows 1.17 and 1.11 times, 66,000
 //     0.88, 1M 0.84, 3M 0.98, 10M 1.04; 4 with k = 24 66,000 0.99, 300,000 0.70,
 //     10M 1.05; 3 with k = 48 66,000 1.05, 300,000 0.62, 10M 1.04
-// So: from 17 queries up (k = 1: 33 and 2^20 pairs), and fewer where nq k is 90, which small
+//   8,192 rows, 1,000 queries, k = 1 / 2 / 3: 0.80 / 0.75 / 0.63 times among others,
+//     but 1.5 / 1.1 / 1.05 where each call is waited for (its allocation counts)
+// So: from 17 queries up, for k < 4 from 2^14 rows (k = 1: 33 queries and 2^20
+// pairs, or 2^18 rows), and fewer where nq k is 90, which small
 // databases need 8 queries for and large ones, whose scan is one read of the
 // rows either way, 144.  Below 8,192 rows (or 256 k) the sample would be most of
 // the rows.
 bool mfma_eligible(uint64_t n, uint32_t nq, uint32_t k) {
     if (n < 8192 || n < (uint64_t)k * 256) return false;
-    if (k == 1) return nq >= 33 && n * nq >= (1u << 20);
-    if (nq >= 17) return true;
+    if (nq >= 17) return k >= 4 || (n >= (1u << 14) && (k >= 2 || (nq >= 33 && n * nq >= (1u << 20)) || n >= (1u << 18)));
     if (nq >= 8) return nq * k >= 90;
     return nq >= 3 && n >= (1u << 16) && nq * k >= (n < (1u << 21) ? 90u : 144u);
 }
 
-MfmaLayout mfma_layout(uint64_t n, uint32_t nq_all, uint32_t k) {
+// The layout of batches of nq queries each.
+static MfmaLayout mfma_batch_layout(uint64_t n, uint32_t nq, uint32_t k) {
     MfmaLayout L;
     L.n = n;
-    // batches of one size, whole groups of queries
-    const uint32_t batches = (uint32_t)(((uint64_t)nq_all + kMaxBatch - 1) / kMaxBatch);
-    const uint32_t each = (uint32_t)(((uint64_t)nq_all + batches - 1) / batches);
-    const uint32_t nq = L.qb = batches == 1 ? nq_all : (each + kGroupQ - 1) / kGroupQ * kGroupQ;
+    L.qb = nq;
     const uint64_t tiles = (n + kMidR - 1) / kMidR, n_qt = (nq + kMidQ - 1) / kMidQ;
     // The pass's first part ends where about 512 candidates per query are
     // expected from the sample's bounds (of up to kCap = 8,192 slots), each next one
@@ -696,6 +697,15 @@ MfmaLayout mfma_layout(uint64_t n, uint32_t nq_all, uint32_t k) {
     L.n_again = take(4);
     L.bytes = o;
     return L;
+}
+
+MfmaLayout mfma_layout(uint64_t n, uint32_t nq, uint32_t k) {
+    const MfmaLayout L = mfma_batch_layout(n, nq, k);
+    const uint64_t most = std::max<uint64_t>(kMinBatch, kBatchBytes / (L.bytes / nq + 1));
+    if (nq <= most) return L;
+    // batches of one size, whole groups of queries
+    const uint64_t batches = (nq + most - 1) / most, each = (nq + batches - 1) / batches;
+    return mfma_batch_layout(n, (uint32_t)((each + kGroupQ - 1) / kGroupQ * kGroupQ), k);
 }
 
 int mfma_run(const MfmaLayout &L, char *ws, const uint64_t *d_db, const uint64_t *d_q, uint32_t nq,

@@ -1,5 +1,6 @@
-"""Sequential search of more queries than one matrix pass takes (16,384), its
-workspace, and the row scan in its place where the workspace cannot be had."""
+"""Sequential search of more queries than one matrix pass takes (16,384 where it
+runs in parts), its workspace, and the row scan in its place where the workspace
+cannot be had."""
 import numpy as np
 import pytest
 
@@ -15,7 +16,7 @@ def _t(a):
     return torch.from_numpy(np.ascontiguousarray(a).view(np.int64)).to("cuda:0")
 
 
-@pytest.mark.parametrize("n,nq,k", [(8_200, 16_385, 10), (9_000, 33_000, 4)])
+@pytest.mark.parametrize("n,nq,k", [(40_000, 16_385, 10), (45_000, 33_000, 4)])
 def test_several_batches(n, nq, k):
     import torch
     import paper_2107_03368_amd as qd
@@ -29,10 +30,22 @@ def test_several_batches(n, nq, k):
     assert np.array_equal(res[0].cpu().numpy()[some].view(np.uint32), oracle.knn_brute(db, q[some], k).idx)
 
 
+def test_many_queries_of_few_candidates():
+    # 300,000 queries of some 5 KB each: two batches
+    import torch
+    import paper_2107_03368_amd as qd
+    db = synth.gen_db(9_000, 905)
+    q, _ = synth.gen_queries(db, 3_000, 906, 0.1, 0.6)
+    dbt, qt = _t(db), _t(q)
+    ref = qd.knn_bruteforce(dbt, qt, 10, query_tile=16)
+    for a, b in zip(qd.knn_bruteforce(dbt, qt.repeat(100, 1), 10), ref):
+        assert torch.equal(a.view(100, 3_000, 10), b.expand(100, -1, -1))
+
+
 def test_plan_over_several_batches():
     import torch
     import paper_2107_03368_amd as qd
-    n, n_obj, per, k, most = 8_192, 32, 700, 4, 25
+    n, n_obj, per, k, most = 40_000, 32, 700, 4, 25
     db = synth.gen_db(n, 910)
     q, _ = synth.gen_queries(db, most * per, 911, 0.1, 0.5)
     dbt, qt = _t(db), _t(q)
@@ -110,7 +123,7 @@ def test_slots_follow_the_candidates():
     plan = qd.Plan(obj, 1, 60_000, 1, 10, db=dbt)
     held = before - torch.cuda.mem_get_info()[0]
     del plan
-    assert held < 0.3 * 2**30
+    assert held < 0.4 * 2**30
 
 
 # Few neighbours, where the number of candidates varies most, and many
