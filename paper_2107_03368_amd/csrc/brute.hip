@@ -258,9 +258,9 @@ __device__ inline void sort_keys(u64 *a, uint32_t n) {
 // above (those k heads are k distinct candidates), and only lists whose head
 // is <= U (at most k of them: keys are distinct) can hold keys <= U.
 //  1. Every thread loads its heads (i, i + 256, ...) and keeps their least;
-//     the k-th smallest K among the 256 least ones, found by bisection in
-//     every wave, bounds U, so usually only a few more than k heads are left
-//     (all of them only when they tie).
+//     the k-th smallest key among the 256 least ones, found by bisection in
+//     every wave (of K, then of the row where more tie), bounds U, so usually
+//     only a few more than k heads are left.
 //  2. Those heads are sorted; the first k of them name the lists.
 //  3. The lists' entries <= U are gathered (at most k * k) and sorted.
 // Bound by the latency of its three dependent loads (heads, entries, rows).
@@ -290,7 +290,7 @@ __global__ __launch_bounds__(kBlock) void merge_emit_kernel(const u64 *__restric
     least[tid] = mn;
     if (tid == 0) nleft = ncand = nqual = 0;
     __syncthreads();
-    // the k-th smallest K of the 256 least heads (keys are below 2^25 << 32)
+    // the k-th smallest of the 256 least heads (keys are below 2^25 << 32)
     u64 U1 = KEY_NONE;
     {
         uint32_t kv[4], real = 0;
@@ -311,7 +311,25 @@ __global__ __launch_bounds__(kBlock) void merge_emit_kernel(const u64 *__restric
                 else
                     lo = mid + 1;
             }
-            U1 = ((u64)lo << 32) | 0xFFFFFFFFu;
+            uint32_t rv[4], below = 0, tied = 0;
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                rv[i] = kv[i] == lo ? (uint32_t)least[64 * i + lane] : 0xFFFFFFFFu;
+                below += (uint32_t)__popcll(ballot(kv[i] < lo));
+                tied += (uint32_t)__popcll(ballot(kv[i] == lo));
+            }
+            uint32_t rlo = 0, rhi = below + tied > k ? 0xFFFFFFFFu : 0;
+            while (rlo < rhi) {
+                const uint32_t mid = rlo + (rhi - rlo) / 2;
+                uint32_t c = below;
+#pragma unroll
+                for (int i = 0; i < 4; i++) c += (uint32_t)__popcll(ballot(rv[i] <= mid));
+                if (c >= k)
+                    rhi = mid;
+                else
+                    rlo = mid + 1;
+            }
+            U1 = ((u64)lo << 32) | (below + tied > k ? rlo : 0xFFFFFFFFu);
         }
     }
 #pragma unroll
