@@ -336,7 +336,10 @@ __global__ __launch_bounds__(kMidBlock, 2) void scan_mfma_kernel(const uint4 *__
 
 // Selection among a query's m <= cap candidates by the whole block: thread t
 // holds the K of candidates t, t + 256, ... (R of them; no candidate: all
-// ones), and the k-th smallest K is found by bisection, counting by ballots.
+// ones).  The k-th smallest of the threads' least K, which every wave finds for
+// itself by bisection over 256 values, leaves little more than k candidates to
+// rank; where more than 256 are left (ties), the k-th K and then the row are
+// bisected over all of them, a barrier per count.
 template <int R>
 struct Pick {
     uint32_t kv[R];
@@ -388,30 +391,55 @@ struct Pick {
         }
         return lo;
     }
-    // the k-th smallest (K << 32 | row(i)) of the candidates (at least k of them)
+    // a K that k candidates or more, usually few more, do not exceed (at least k candidates, k <= 64)
+    __device__ __forceinline__ uint32_t near(uint32_t k) {
+        __shared__ uint32_t s_least[kBlock];
+        uint32_t mn = kv[0], v[4];
+#pragma unroll
+        for (int j = 1; j < R; j++) mn = min(mn, kv[j]);
+        s_least[threadIdx.x] = mn;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 4; i++) v[i] = s_least[64 * i + (threadIdx.x & 63)];
+        uint32_t lo = 0, hi = (1u << 25) - 1;
+        while (lo < hi) {
+            const uint32_t mid = (lo + hi) / 2;
+            uint32_t c = 0;
+#pragma unroll
+            for (int i = 0; i < 4; i++) c += (uint32_t)__popcll(ballot(v[i] <= mid));
+            if (c >= k)
+                hi = mid;
+            else
+                lo = mid + 1;
+        }
+        return lo;
+    }
+    // the k-th smallest (K << 32 | row(i)) of the candidates (at least k of them, k <= 64)
     template <class F>
     __device__ __forceinline__ u64 kth_key(uint32_t k, F &&row) {
-        // nearly always a few candidates have the k-th K: each finds its row's rank among theirs
-        __shared__ uint32_t s_tied[64], s_n, s_row;
-        const uint32_t K = kth(k);
-        if (threadIdx.x == 0) s_n = 0;  // (read after the next count's barrier)
-        const uint32_t need = k - count([&](int j) { return kv[j] < K; });
+        __shared__ u64 s_key[kBlock], s_kth;
+        __shared__ uint32_t s_n;
+        if (threadIdx.x == 0) s_n = 0;
+        const uint32_t U = near(k);  // (its barrier publishes s_n)
 #pragma unroll
         for (int j = 0; j < R; j++)
-            if (kv[j] == K) {
+            if (kv[j] <= U) {
                 const uint32_t at = atomicAdd(&s_n, 1u);
-                if (at < 64) s_tied[at] = row(threadIdx.x + (uint32_t)kBlock * j);
+                if (at < (uint32_t)kBlock) s_key[at] = ((u64)kv[j] << 32) | row(threadIdx.x + (uint32_t)kBlock * j);
             }
         __syncthreads();
-        const uint32_t tied = s_n;
-        if (tied > 64) return ((u64)K << 32) | nth_row(K, need, row);
-        if (threadIdx.x < tied) {
+        const uint32_t n = s_n;
+        if (n > (uint32_t)kBlock) {
+            const uint32_t K = kth(k), need = k - count([&](int j) { return kv[j] < K; });
+            return ((u64)K << 32) | nth_row(K, need, row);
+        }
+        if (threadIdx.x < n) {
             uint32_t rank = 0;
-            for (uint32_t j = 0; j < tied; j++) rank += s_tied[j] < s_tied[threadIdx.x];
-            if (rank == need - 1) s_row = s_tied[threadIdx.x];
+            for (uint32_t j = 0; j < n; j++) rank += s_key[j] < s_key[threadIdx.x];
+            if (rank == k - 1) s_kth = s_key[threadIdx.x];
         }
         __syncthreads();
-        return ((u64)K << 32) | s_row;
+        return s_kth;
     }
 };
 
@@ -435,17 +463,20 @@ __global__ __launch_bounds__(kBlock) void tighten_kernel(const uint32_t *__restr
 }
 
 // The k smallest of m candidates (all of them if fewer) into keys[0 .. *n), in
-// any order, at most kBlock of them: the keys up to the k-th K, or, when more
-// than kBlock tie there, the tied rows up to the last one needed.
+// any order, with others, at most kBlock: the keys up to near(k), or, where these
+// are more than kBlock, up to the k-th K, or, where more tie there, the tied rows
+// up to the last one needed.
 template <int R>
 __device__ __forceinline__ void pick_keys(const u64 *cand, uint32_t m, uint32_t k, uint32_t (*s_part)[4], u64 *keys,
                                           uint32_t *n) {
     Pick<R> P([&](uint32_t i) { return (uint32_t)(cand[i] >> 32); }, m, s_part);
-    const uint32_t kth = P.kth(k);
-    uint32_t last = 0xFFFFFFFFu;  // rows above it with K = kth are left out
+    uint32_t kth = P.near(k), last = 0xFFFFFFFFu;  // rows above `last` with K = kth are left out
     if (P.count([&](int j) { return P.kv[j] <= kth; }) > (uint32_t)kBlock) {
-        const uint32_t need = k - P.count([&](int j) { return P.kv[j] < kth; });
-        last = P.nth_row(kth, need, [&](uint32_t i) { return (uint32_t)cand[i]; });
+        kth = P.kth(k);
+        if (P.count([&](int j) { return P.kv[j] <= kth; }) > (uint32_t)kBlock) {
+            const uint32_t need = k - P.count([&](int j) { return P.kv[j] < kth; });
+            last = P.nth_row(kth, need, [&](uint32_t i) { return (uint32_t)cand[i]; });
+        }
     }
 #pragma unroll
     for (int j = 0; j < R; j++) {
