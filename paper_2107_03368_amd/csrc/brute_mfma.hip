@@ -77,10 +77,11 @@ constexpr int kMidStride = 512 + 16;      // bytes per query in LDS: 16-byte rea
 
 // Row of the sample's entry i: one out of every n / entries rows, at a place
 // that a hash of i picks, so that no period of the rows meets the sample's.
-// step = n / entries in 32.32 fixed point, at least 1.  Entry i of the sample
-// goes to its tile i % tiles: the 64 rows of a tile lie far apart, and near rows
-// (rows of one object, rows in order of distance, repeated rows) in different
-// groups, of which each adds one key to the bound.  With whole tiles sampled
+// step = n / entries in 32.32 fixed point, at least 1.  The sample's tile t has
+// one entry of each 64th of the rows, sample_entry: the 64 rows of a tile lie far
+// apart, and near rows (rows of one object, rows in order of distance, repeated
+// rows, one view of every object) in different groups, of which each adds one key
+// to the bound.  With whole tiles sampled
 // a run of tied or similar rows filled few groups, and up to 16,000 of its rows
 // passed: 64 queries x 10M rows that are all equal 1.4 ms, 17 then.
 __device__ __forceinline__ uint64_t sample_row(uint32_t i, uint64_t step) {
@@ -88,6 +89,15 @@ __device__ __forceinline__ uint64_t sample_row(uint32_t i, uint64_t step) {
     uint32_t h = i * 2654435761u;  // multiplicative hashing by the golden ratio, twice
     h = (h ^ (h >> 16)) * 2654435761u;
     return a + __umulhi(h, b - a);
+}
+
+// (the same place of the next 64th is 5/8 of the tiles on)
+__device__ __forceinline__ uint32_t sample_turn(uint32_t slot, uint32_t tiles) {
+    return slot * (tiles * 5 / 8 + 1) % tiles;
+}
+__device__ __forceinline__ uint32_t sample_entry(uint32_t slot, uint32_t turn, uint32_t tile, uint32_t tiles) {
+    const uint32_t x = tile + turn;
+    return slot * tiles + (x < tiles ? x : x - tiles);
 }
 
 // LDS, sized by the queries of the largest group.
@@ -125,6 +135,11 @@ __global__ __launch_bounds__(kMidBlock, 2) void scan_mfma_kernel(const uint4 *__
     const int li = lane & 31, lh = lane >> 5;
     float *tpw = sm.tp[wv];
     uint32_t (*cq)[3] = sm.queue[wv];
+    uint32_t turn[2] = {0, 0};
+    if (kPass == kSample) {
+#pragma unroll
+        for (int b = 0; b < 2; b++) turn[b] = sample_turn(32 * b + li, (uint32_t)tiles);
+    }
     // the pass's row tiles: t0 + i, i < tiles (kSample: the sample's)
     const uint32_t nq_max = nq_given, n_qt = (nq + kMidQ - 1) / kMidQ;
     // this workgroup's units [ua, ub) of all groups' (each group: its query
@@ -180,8 +195,10 @@ __global__ __launch_bounds__(kMidBlock, 2) void scan_mfma_kernel(const uint4 *__
         auto load = [&](uint64_t r, int L, uint4 (&x)[2][4]) {
 #pragma unroll
             for (int b = 0; b < 2; b++) {
-                uint64_t row = kPass == kSample ? sample_row((uint32_t)((32 * b + li) * tiles + r), sample_step)
-                                                : (t0 + r) * kMidR + 32 * b + li;
+                uint64_t row = kPass == kSample
+                                   ? sample_row(sample_entry(32 * b + li, turn[b], (uint32_t)r, (uint32_t)tiles),
+                                                sample_step)
+                                   : (t0 + r) * kMidR + 32 * b + li;
                 row = row < n ? row : n - 1;
                 const uint4 *src = db + row * 32 + 8 * L + lh;
 #pragma unroll
@@ -634,7 +651,7 @@ __global__ __launch_bounds__(kBlock) void sample_threshold_kernel(const uint32_t
     auto row = [&](uint32_t i) {  // of group i = (tile i / 2, lane half i % 2), as scan_mfma_kernel's lanes hold them
         const uint32_t e = minima[(uint64_t)i * nq + qi] & 31;
         const uint32_t slot = 32 * (e >> 4) + 8 * ((e >> 2) & 3) + 4 * (i & 1) + (e & 3);
-        return (uint32_t)sample_row(slot * (m / 2) + (i >> 1), sample_step);
+        return (uint32_t)sample_row(sample_entry(slot, sample_turn(slot, m / 2), i >> 1, m / 2), sample_step);
     };
     const u64 t = m <= 4 * kBlock ? Pick<4>(key, m, s_part).kth_key(k, row)
                                   : Pick<kMaxGroups / kBlock>(key, m, s_part).kth_key(k, row);

@@ -124,8 +124,8 @@ def test_periodic_rows(period):
 
 
 def _sampled(n, k):
-    """The rows that bound a small batch's queries: the row scan's sample (sample_row)."""
-    tiles = min((max(n // 512 * k, 128 * k) + 63) // 64, (n + 63) // 64, 4096)
+    """The rows that a pass in one part samples."""
+    tiles = min((max(n // 512 * k, 128 * k, min(n // 512 * 16, 32_768)) + 63) // 64, (n + 63) // 64, 4096)
     step = (n << 32) // (64 * tiles)
     i = np.arange(64 * tiles + 1, dtype=np.uint64)
     a = (i * np.uint64(step)) >> np.uint64(32)
@@ -177,3 +177,25 @@ def test_overflowing_buffers(n, nq, k, twice):
     o = oracle.knn_brute(db, q[some], k)
     assert np.array_equal(res[0].cpu().numpy()[some].view(np.uint32), o.idx)
     assert np.array_equal(res[3].cpu().numpy()[some], o.dist)
+
+
+@pytest.mark.parametrize("n,views", [(192_000, 3_000), (640_000, 10_000), (131_072, 2_048)])
+def test_near_rows_at_one_place_of_every_object(n, views):
+    # 64 objects of so many views; the nearest are some neighbouring views of all
+    import paper_2107_03368_amd as qd
+    import torch
+    rng = np.random.default_rng(895)
+    db = synth.gen_db(n, 895)
+    base = db[5].copy()
+    bits = np.flatnonzero(np.unpackbits(base.view(np.uint8), bitorder="little"))
+    rows = (np.arange(64)[:, None] * views + views // 3 + np.arange(60)[None]).reshape(-1)
+    b = np.tile(np.unpackbits(base.view(np.uint8), bitorder="little"), (len(rows), 1))
+    for _ in range(12):
+        b[np.arange(len(rows)), rng.choice(bits, len(rows))] = 0
+    db[rows] = np.packbits(b, axis=1, bitorder="little").view(np.uint64)
+    q = np.tile(base, (40, 1))
+    q[:, 0] ^= np.arange(40, dtype=np.uint64)
+    dbt, qt = _t(db), _t(q)
+    for k in (1, 10, 64):
+        res, ref = qd.knn_bruteforce(dbt, qt, k), qd.knn_bruteforce(dbt, qt, k, query_tile=16)
+        assert all(torch.equal(x, y) for x, y in zip(res, ref))
