@@ -58,7 +58,7 @@ TRAIN_QUERIES, TRAIN_BATCH, TRAIN_EPOCHS, TRAIN_LR, N_SCORED = 4096, 32, 8, 2e-3
 # KiB); drop an entry when its kernel changes
 TRAFFIC_DETAIL = {
     # scan_mfma_kernel at 10M x 8,192: the two parts of one search's pass, timed as one (not the sample's)
-    "scan_mfma_kernel": {"read_bytes": 2_541_321 * 2 * 1024, "write_bytes": 208_845 * 1024,
+    "scan_mfma_kernel": {"read_bytes": 2_541_744 * 2 * 1024, "write_bytes": 212_871 * 1024,
                          "algorithmic_read_bytes": 5.124e9, "counter_scale": {"FETCH_SIZE": 2.0, "WRITE_SIZE": 1.0}},
     # eval_kernel at 10M x 8,192, k = 10: one search's launches together (a
     # direct search launches it once per pass, passes without tiles included),

@@ -135,7 +135,7 @@ __global__ __launch_bounds__(kLdsBlock) void obj_count_lds_kernel(const uint16_t
 }
 
 // One block: roff = exclusive prefix of the row counts, toff = exclusive
-// prefix of the tile counts ceil(cnt / 256); both with the total at n_obj.
+// prefix of the tile counts ceil(cnt / 64); both with the total at n_obj.
 // Also clears the scatter cursors.
 __global__ __launch_bounds__(1024) void obj_offsets_kernel(const uint32_t *__restrict__ cnt, uint32_t n_obj,
                                                            uint64_t *__restrict__ roff, uint32_t *__restrict__ toff,

@@ -698,10 +698,13 @@ __global__ void zero_words_kernel(uint32_t *p, uint32_t n) {
 // and up to 64 while the subtrees keep 8,192 rows, or 1,024 where the batch would
 // leave most waves without a search, for at most 2^18 lists (the workspace).  A
 // batch ends with its longest search, which at 16 is longer than all the rest for
-// up to some 100 queries.  Measured at 16 / 32 / 64, best-first, k = 10, 1M rows:
+// up to some 100 queries.  Measured at 16 / 32 / 64 (with the searches of a query
+// dealt to any XCD and their totals counted), best-first, k = 10, 1M rows:
 // 1 query 8.2 / 5.4 / 3.2 ms, 128 queries 10.7 / 7.0 / 6.2, 509 16.6 / 14.5 /
 // 13.7, 4,096 93.3 / 91.7 / 91.7; 100k rows: 16 queries 1.03 / 0.64 / 0.49,
-// 128 1.31 / 0.98 / 1.19, 4,096 13.3 / 13.3 / 15.4.
+// 128 1.31 / 0.98 / 1.19, 4,096 13.3 / 13.3 / 15.4.  Present kernels, 16 / this
+// rule: 5.7 / 2.4, 10.4 / 5.5, 16.4 / 10.4, 69.7 / 60.7; 1.02 / 0.54, 1.50 / 1.27,
+// 10.1 / 10.0.
 static uint32_t default_split(qd_tree_t t, uint64_t nq_max) {
     uint32_t n = kMaxSplit;
     for (; n < kFineSplit; n *= 2) {
